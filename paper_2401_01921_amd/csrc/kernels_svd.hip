@@ -1,8 +1,10 @@
 // Symmetric SVD kernels (Sec. "Singular value decomposition"): the block
 // matrices of every charge sector are gathered into the tall orientation X,
-// each sector's SVD runs as one-sided Jacobi (Hestenes) in one workgroup,
-// the truncation is selected across all sectors by one workgroup, and the
-// kept columns are written into the block layouts of U and V^dagger.
+// each sector's SVD runs as one-sided Jacobi (Hestenes), the truncation is
+// selected across all sectors by one workgroup, and the kept columns are
+// written into the block layouts of U and V^dagger.  Sectors that fit a
+// workgroup's registers are rotated in kernels_svd_reg.hip; here are the paths
+// of the others.
 //
 // One-sided Jacobi: for a pair of columns (x_i, x_j) with a = |x_i|^2,
 // b = |x_j|^2, g = x_i.x_j, the plane rotation
@@ -38,17 +40,17 @@ __device__ __forceinline__ double wave_allsum(double v) {
 
 __global__ __launch_bounds__(256) void svd_gather_kernel(const SvdGather* __restrict__ jobs,
                                                          const SvdWork* __restrict__ work,
-                                                         const double* __restrict__ in, double* __restrict__ X) {
+                                                         const double* __restrict__ in, double* __restrict__ X,
+                                                         double* __restrict__ scratch) {
   const SvdWork w = work[blockIdx.x];
   const SvdGather j = jobs[w.job];
+  double* const out = (j.scratch ? scratch : X) + j.x_off;
   const int64_t total = (int64_t)j.rows * j.cols;
   for (int e = threadIdx.x; e < kSvdGatherChunk; e += 256) {
     const int64_t idx = (int64_t)w.start + e;
     if (idx >= total) break;
     const int64_t r = idx / j.cols, c = idx % j.cols;
-    const int64_t R = j.row0 + r, C = j.col0 + c;
-    const int64_t dst = j.m >= j.n ? R + C * j.m : C + R * j.n;
-    X[j.x_off + dst] = in[j.in_off + idx];
+    out[(j.row0 + r) * j.rs + (j.col0 + c) * j.cs] = in[j.in_off + idx];
   }
 }
 
@@ -134,18 +136,18 @@ __device__ int jacobi_sweeps(PX x, PV vh, int p, int r, int* rotated) {
 }
 
 __global__ __launch_bounds__(64 * kSvdWaves) void svd_jacobi_kernel(const SvdSec* __restrict__ secs, double* X,
-                                                                   double* V, double* __restrict__ sig,
+                                                                   double* __restrict__ sig,
                                                                    double* __restrict__ sorted,
                                                                    int32_t* __restrict__ perm,
-                                                                   int32_t* __restrict__ sweeps, int only) {
+                                                                   int32_t* __restrict__ sweeps, int path) {
   constexpr int NT = 64 * kSvdWaves;
   const SvdSec S = secs[blockIdx.x];
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m;
-  // only = 1: the sectors that fit (their sweeps); 2: the big ones (sigma
-  // and order after their rounds); 0: all
-  if ((only == 1 && svd_sector_is_big(S.m, S.n)) || (only == 2 && !svd_sector_is_big(S.m, S.n))) return;
+  // the sectors that fit LDS (their sweeps), or the big ones (sigma and order
+  // after their rounds)
+  if (S.path != path) return;
   double* const xg = X + S.x_off;
-  double* const vg = V + S.v_off;
+  double* const vg = X + S.v_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ int rotated;
   // X is rotated in LDS when it fits kSvdLdsBytes, and Vh with it when both
@@ -158,7 +160,7 @@ __global__ __launch_bounds__(64 * kSvdWaves) void svd_jacobi_kernel(const SvdSec
   BST_LDS double* xl = (BST_LDS double*)lds;
   BST_LDS double* vl = xl + (int64_t)p * r;
   // a big sector arrives rotated (svd_round_kernel), its sweeps counted
-  const bool pre = svd_sector_is_big(S.m, S.n);
+  const bool pre = path == kSvdPathRounds;
   if (x_lds)
     for (int64_t e = tid; e < (int64_t)p * r; e += NT) xl[e] = xg[e];
   if (v_lds)
@@ -221,8 +223,8 @@ __global__ __launch_bounds__(64 * kSvdWaves) void svd_jacobi_kernel(const SvdSec
 // and the four waves in order), the same test and rotation, both columns of
 // X and of Vh updated.  Any rotation sets the sector's flag for the sweep.
 __global__ __launch_bounds__(256) void svd_round_kernel(const SvdSec* __restrict__ secs,
-                                                        const int32_t* __restrict__ big, double* X, double* V,
-                                                        int t, int32_t* flags) {
+                                                        const int32_t* __restrict__ big, double* X, int t,
+                                                        int32_t* flags) {
   const int b = blockIdx.y;
   if (flags[2 * b + 1]) return;   // converged
   const SvdSec S = secs[big[b]];
@@ -272,8 +274,8 @@ __global__ __launch_bounds__(256) void svd_round_kernel(const SvdSec* __restrict
     xi[e] = c * u - sn * v;
     xj[e] = sn * u + c * v;
   }
-  double* const vi = V + S.v_off + (int64_t)i * r;
-  double* const vj = V + S.v_off + (int64_t)j * r;
+  double* const vi = X + S.v_off + (int64_t)i * r;
+  double* const vj = X + S.v_off + (int64_t)j * r;
   for (int e = tid; e < r; e += 256) {
     const double u = vi[e], v = vj[e];
     vi[e] = c * u - sn * v;
@@ -317,11 +319,12 @@ __global__ __launch_bounds__(256) void svd_sweep_end_kernel(int nbig, const int3
 hipError_t launch_svd_gather(const SvdLaunch& l, hipStream_t s) {
   if (l.ngwork > 0x7FFFFFFF || l.nsec < 0 || l.nbig < 0 || l.nbig > 65535) return hipErrorInvalidValue;
   if (l.ngwork > 0)
-    hipLaunchKernelGGL(svd_gather_kernel, dim3((unsigned)l.ngwork), dim3(256), 0, s, l.gjobs, l.gwork, l.in, l.X);
+    hipLaunchKernelGGL(svd_gather_kernel, dim3((unsigned)l.ngwork), dim3(256), 0, s, l.gjobs, l.gwork, l.in, l.X,
+                       l.scratch);
   if (l.nbig > 0) {
     const int64_t gx = std::min<int64_t>(std::max<int64_t>((l.vmax + 4095) / 4096, 1), 1024);
     hipLaunchKernelGGL(svd_big_init_kernel, dim3((unsigned)gx, (unsigned)l.nbig), dim3(256), 0, s, l.secs, l.big,
-                       l.V, l.flags, l.sweeps);
+                       l.X, l.flags, l.sweeps);
   }
   return hipGetLastError();
 }
@@ -331,17 +334,17 @@ hipError_t launch_svd_sweep(const SvdLaunch& l, hipStream_t s) {
   if (l.nbig > 65535 || l.pairs <= 0 || l.rounds <= 0) return hipErrorInvalidValue;
   for (int t = 0; t < l.rounds; ++t)
     hipLaunchKernelGGL(svd_round_kernel, dim3((unsigned)l.pairs, (unsigned)l.nbig), dim3(256), 0, s, l.secs, l.big,
-                       l.X, l.V, t, l.flags);
+                       l.X, t, l.flags);
   hipLaunchKernelGGL(svd_sweep_end_kernel, dim3((unsigned)((l.nbig + 255) / 256)), dim3(256), 0, s, l.nbig, l.big,
                      l.flags, l.sweeps);
   return hipGetLastError();
 }
 
-hipError_t launch_svd_finish(const SvdLaunch& l, hipStream_t s, int only) {
-  if (l.nsec < 0 || only < 0 || only > 2) return hipErrorInvalidValue;
+hipError_t launch_svd_finish(const SvdLaunch& l, hipStream_t s, int path) {
+  if (l.nsec < 0 || (path != kSvdPathLds && path != kSvdPathRounds)) return hipErrorInvalidValue;
   if (l.nsec > 0)
-    hipLaunchKernelGGL(svd_jacobi_kernel, dim3((unsigned)l.nsec), dim3(64 * kSvdWaves), 0, s, l.secs, l.X, l.V,
-                       l.sig, l.sorted, l.perm, l.sweeps, only);
+    hipLaunchKernelGGL(svd_jacobi_kernel, dim3((unsigned)l.nsec), dim3(64 * kSvdWaves), 0, s, l.secs, l.X,
+                       l.sig, l.sorted, l.perm, l.sweeps, path);
   return hipGetLastError();
 }
 
@@ -488,7 +491,7 @@ hipError_t launch_svd_select(const SvdSelectLaunch& l, hipStream_t s) {
 __global__ __launch_bounds__(256) void svd_write_kernel(const SvdWrite* __restrict__ jobs,
                                                         const SvdWriteWork* __restrict__ work,
                                                         const SvdSec* __restrict__ secs, const double* __restrict__ X,
-                                                        const double* __restrict__ V,
+                                                        const int32_t* __restrict__ rowpos,
                                                         const double* __restrict__ sorted,
                                                         const int32_t* __restrict__ perm, int absorb, double* U,
                                                         double* Vd, double* Sv) {
@@ -496,7 +499,6 @@ __global__ __launch_bounds__(256) void svd_write_kernel(const SvdWrite* __restri
   const SvdWrite j = jobs[w.job];
   const SvdSec S = secs[j.sec];
   const bool tall = S.m >= S.n;
-  const int64_t p = tall ? S.m : S.n, r = tall ? S.n : S.m;
   const int64_t total = j.kind == 2 ? j.k : (int64_t)j.ext * j.k;
   for (int e = threadIdx.x; e < kSvdGatherChunk; e += 256) {
     const int64_t idx = (int64_t)w.start + e;
@@ -514,9 +516,10 @@ __global__ __launch_bounds__(256) void svd_write_kernel(const SvdWrite* __restri
     const bool from_x = (j.kind == 0) == tall;
     double v;
     if (from_x) {
-      v = sg > 0.0 ? X[S.x_off + row + col * p] / sg : 0.0;
+      const int64_t xr = S.path == kSvdPathReg ? rowpos[S.p_off + row] : row;
+      v = sg > 0.0 ? X[S.x_off + xr * S.x_rs + col * S.x_cs] / sg : 0.0;
     } else {
-      v = V[S.v_off + row + col * r];
+      v = X[S.v_off + row * S.v_rs + col * S.v_cs];
     }
     if ((j.kind == 0 && absorb == 1) || (j.kind == 1 && absorb == 2)) v *= sg;
     (j.kind == 0 ? U : Vd)[j.out_off + idx] = v;
@@ -526,7 +529,7 @@ __global__ __launch_bounds__(256) void svd_write_kernel(const SvdWrite* __restri
 hipError_t launch_svd_write(const SvdWriteLaunch& l, hipStream_t s) {
   if (l.nwork <= 0) return hipSuccess;
   if (l.nwork > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(svd_write_kernel, dim3((unsigned)l.nwork), dim3(256), 0, s, l.jobs, l.work, l.secs, l.X, l.V,
+  hipLaunchKernelGGL(svd_write_kernel, dim3((unsigned)l.nwork), dim3(256), 0, s, l.jobs, l.work, l.secs, l.X, l.rowpos,
                      l.sorted, l.perm, l.absorb, l.U, l.Vd, l.S);
   return hipGetLastError();
 }

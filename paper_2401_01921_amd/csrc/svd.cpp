@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 
@@ -46,9 +47,14 @@ struct SvdPlanData {
   std::vector<Sector> secs;
   int64_t nvalues = 0;
   // workspace layout (bytes)
-  size_t ws_tab = 0, ws_secs = 0, ws_gjobs = 0, ws_gwork = 0, ws_x = 0, ws_v = 0, ws_sig = 0, ws_sorted = 0,
+  size_t ws_tab = 0, ws_secs = 0, ws_gjobs = 0, ws_gwork = 0, ws_x = 0, ws_scratch = 0, ws_sig = 0, ws_sorted = 0,
          ws_perm = 0, ws_sweeps = 0, ws_kept = 0, ws_serr = 0, ws_mb = 0, ws_wtab = 0, ws_bytes = 0;
   size_t wtab_cap = 0;   // bytes reserved for the write tables
+  // sectors of the register path
+  std::vector<int32_t> reg;
+  size_t ws_reg = 0, ws_rowpos = 0, ws_ctrl = 0;
+  int32_t panels = 0, logcap = kSvdLogSweeps, nlds = 0;
+  int64_t trail_rows = 0, reg_cols = 0;
   // sectors rotated a round per launch (X larger than the LDS budget)
   std::vector<int32_t> big;
   size_t ws_big = 0, ws_flags = 0;
@@ -57,9 +63,9 @@ struct SvdPlanData {
   std::vector<uint8_t> blob;   // sector and gather tables
   int64_t ngwork = 0;
   void* uploaded = nullptr;
-  // a second stream (default priority) on which the sectors that fit LDS
-  // run their sweeps beside the big sectors' rounds; made on first use, on
-  // the device then current
+  // a second stream (default priority) on which the sectors of one workgroup
+  // each run beside the big sectors' rounds, and those of the LDS path beside
+  // the register path's; made on first use, on the device then current
   hipStream_t aux = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   int aux_dev = -1;
@@ -178,20 +184,49 @@ void build(SvdPlanData& P) {
     if (s.m > 0 && s.n > 0) kept.push_back(std::move(s));
   P.secs = std::move(kept);
   // device layout of the sector matrices
-  int64_t xo = 0, vo = 0, so = 0;
+  if (const char* e = std::getenv("BST_SVD_LOG_SWEEPS"))
+    P.logcap = std::max(1, std::min(std::atoi(e), kSvdLogSweeps));
+  int64_t xo = 0, so = 0, lo = 0, po = 0;
   std::vector<SvdSec> dsecs;
-  for (auto& s : P.secs) {
+  for (size_t k = 0; k < P.secs.size(); ++k) {
+    Sector& s = P.secs[k];
     if (s.m > 0x7FFFFFFF || s.n > 0x7FFFFFFF) fail(BST_E_INVALID, "sector matrix too large");
-    const int64_t rr = std::min(s.m, s.n);
-    s.dev.x_off = xo;
-    s.dev.v_off = vo;
-    s.dev.s_off = so;
-    s.dev.m = (int32_t)s.m;
-    s.dev.n = (int32_t)s.n;
-    xo += s.m * s.n;
-    vo += rr * rr;
+    const int64_t p = std::max(s.m, s.n), rr = std::min(s.m, s.n);
+    SvdSec& d = s.dev;
+    d.path = svd_path(s.m, s.n);
+    d.s_off = so;
+    d.m = (int32_t)s.m;
+    d.n = (int32_t)s.n;
+    d.x_off = xo;
+    if (d.path == kSvdPathReg) {
+      // rows of X, then of Vh, each of the padded column count
+      d.pairs = rr <= kSvdRegCols1 ? 1 : 2;
+      const int64_t ld = (rr + 2 * d.pairs - 1) / (2 * d.pairs) * (2 * d.pairs);
+      d.ld = (int32_t)ld;
+      d.x_rs = d.v_rs = (int32_t)ld;
+      d.x_cs = d.v_cs = 1;
+      d.v_off = xo + p * ld;
+      xo += (p + rr) * ld;
+      const bool whole = (p + rr) * svd_panel_ld(ld) * (int64_t)sizeof(double) <= kSvdPanelLds;
+      d.nb = (int32_t)(whole ? rr : std::min<int64_t>(kSvdPanelRefl, rr - 1));
+      P.panels = std::max(P.panels, (int32_t)((rr + d.nb - 1) / d.nb));
+      if (!whole) P.trail_rows = std::max(P.trail_rows, p + rr - d.nb);
+      P.reg_cols = std::max(P.reg_cols, rr);
+      d.log_off = lo;
+      lo += (std::max((p + rr) * ld, P.logcap * svd_log_sweep(ld, d.pairs)) + 31) / 32 * 32;
+      d.p_off = po;
+      po += 2 * p;
+      P.reg.push_back((int32_t)k);
+    } else {
+      d.x_rs = d.v_rs = 1;
+      d.x_cs = (int32_t)p;
+      d.v_cs = (int32_t)rr;
+      d.v_off = xo + p * rr;
+      xo += p * rr + rr * rr;
+      if (d.path == kSvdPathLds) ++P.nlds;
+    }
     so += rr;
-    dsecs.push_back(s.dev);
+    dsecs.push_back(d);
   }
   P.nvalues = so;
   if (so > 0x7FFFFFFF) fail(BST_E_INVALID, "too many singular values");
@@ -200,7 +235,7 @@ void build(SvdPlanData& P) {
   P.vmax = 0;
   for (size_t k = 0; k < P.secs.size(); ++k) {
     const int64_t m = P.secs[k].m, n = P.secs[k].n;
-    if (!svd_sector_is_big(m, n)) continue;
+    if (P.secs[k].dev.path != kSvdPathRounds) continue;
     const int64_t r = std::min(m, n), rr = r + (r & 1);
     P.big.push_back((int32_t)k);
     P.rounds = (int32_t)std::max<int64_t>(P.rounds, rr - 1);
@@ -208,6 +243,7 @@ void build(SvdPlanData& P) {
     P.vmax = std::max(P.vmax, r * r);
   }
   if (P.big.size() > 65535) fail(BST_E_INVALID, "more than 65535 sector matrices above the LDS budget");
+  if (P.reg.size() > 65535) fail(BST_E_INVALID, "more than 65535 sector matrices");
   // gather jobs: every block of T into its sector matrix
   std::vector<SvdGather> gj;
   std::vector<SvdWork> gw;
@@ -226,13 +262,16 @@ void build(SvdPlanData& P) {
     const Sector& s = P.secs[ri->second.first];
     SvdGather g{};
     g.in_off = T.offset[b];
-    g.x_off = s.dev.x_off;
+    const SvdSec& d = s.dev;
+    g.scratch = d.path == kSvdPathReg ? 1 : 0;
+    g.x_off = g.scratch ? d.log_off : d.x_off;
+    const bool tall = s.m >= s.n;   // M_q's rows are X's rows
+    g.rs = tall ? d.x_rs : d.x_cs;
+    g.cs = tall ? d.x_cs : d.x_rs;
     g.rows = (int32_t)extent(T, 0, rt1);
     g.cols = (int32_t)extent(T, r, ct1);
     g.row0 = (int32_t)ri->second.second;
     g.col0 = (int32_t)ci->second.second;
-    g.m = s.dev.m;
-    g.n = s.dev.n;
     const int32_t jid = (int32_t)gj.size();
     gj.push_back(g);
     const int64_t total = (int64_t)g.rows * g.cols;
@@ -244,6 +283,7 @@ void build(SvdPlanData& P) {
   P.ws_gjobs = put(P.blob, gj);
   P.ws_gwork = put(P.blob, gw);
   P.ws_big = put(P.blob, P.big);
+  P.ws_reg = put(P.blob, P.reg);
   size_t off = align256(P.blob.size());
   P.ws_tab = 0;
   auto take = [&](size_t bytes) {
@@ -252,7 +292,9 @@ void build(SvdPlanData& P) {
     return o;
   };
   P.ws_x = take(sizeof(double) * (size_t)xo);
-  P.ws_v = take(sizeof(double) * (size_t)vo);
+  P.ws_scratch = take(sizeof(double) * (size_t)lo);
+  P.ws_rowpos = take(sizeof(int32_t) * (size_t)po);
+  P.ws_ctrl = take(sizeof(int32_t) * 2 * P.reg.size());
   P.ws_sig = take(sizeof(double) * (size_t)so);
   P.ws_sorted = take(sizeof(double) * (size_t)so);
   P.ws_perm = take(sizeof(int32_t) * (size_t)so);
@@ -375,7 +417,16 @@ bst_status bst_svd_execute(bst_svd* p, const void* M, void* ws, void* stream) {
   l.nsec = (int32_t)P.secs.size();
   l.in = static_cast<const double*>(M);
   l.X = at<double>(ws, P.ws_x);
-  l.V = at<double>(ws, P.ws_v);
+  l.scratch = at<double>(ws, P.ws_scratch);
+  l.rowpos = at<int32_t>(ws, P.ws_rowpos);
+  l.reg = at<const int32_t>(ws, P.ws_reg);
+  l.nreg = (int32_t)P.reg.size();
+  l.panels = P.panels;
+  l.trail_rows = P.trail_rows;
+  l.reg_cols = P.reg_cols;
+  l.logcap = P.logcap;
+  l.ctrl = at<int32_t>(ws, P.ws_ctrl);
+  l.nlds = P.nlds;
   l.sig = at<double>(ws, P.ws_sig);
   l.sorted = at<double>(ws, P.ws_sorted);
   l.perm = at<int32_t>(ws, P.ws_perm);
@@ -387,10 +438,12 @@ bst_status bst_svd_execute(bst_svd* p, const void* M, void* ws, void* stream) {
   l.vmax = P.vmax;
   l.flags = at<int32_t>(ws, P.ws_flags);
   check_hip(launch_svd_gather(l, s), "svd gather");
-  if (l.nbig == 0) {
-    check_hip(launch_svd_finish(l, s, 0), "svd");
+  if (l.nbig == 0 && (l.nreg == 0 || l.nlds == 0)) {
+    check_hip(launch_svd_reg(l, s), "svd");
+    if (l.nlds > 0) check_hip(launch_svd_finish(l, s, kSvdPathLds), "svd");
   } else {
-    // the sectors that fit run their sweeps on the second stream meanwhile
+    // beside the rounds of the big sectors (or else the register path), the
+    // other sectors on the second stream
     int dev = -1;
     check_hip(hipGetDevice(&dev), "device");
     if (P.aux && P.aux_dev != dev) P.release_aux();
@@ -401,9 +454,12 @@ bst_status bst_svd_execute(bst_svd* p, const void* M, void* ws, void* stream) {
     }
     check_hip(hipEventRecord(P.ev[0], s), "svd event");
     check_hip(hipStreamWaitEvent(P.aux, P.ev[0], 0), "svd event");
-    check_hip(launch_svd_finish(l, P.aux, 1), "svd");
+    if (l.nbig > 0) check_hip(launch_svd_reg(l, P.aux), "svd");
+    if (l.nlds > 0) check_hip(launch_svd_finish(l, P.aux, kSvdPathLds), "svd");
     check_hip(hipEventRecord(P.ev[1], P.aux), "svd event");
-    {
+    if (l.nbig == 0) {
+      check_hip(launch_svd_reg(l, s), "svd");
+    } else {
       // sweeps of the big sectors until each has had one without a rotation
       // (at most kSvdMaxSweeps): the host reads the flags after every sweep
       std::vector<int32_t> fl(2 * (size_t)l.nbig);
@@ -418,7 +474,7 @@ bst_status bst_svd_execute(bst_svd* p, const void* M, void* ws, void* stream) {
       }
     }
     check_hip(hipStreamWaitEvent(s, P.ev[1], 0), "svd event");
-    check_hip(launch_svd_finish(l, s, 2), "svd");
+    if (l.nbig > 0) check_hip(launch_svd_finish(l, s, kSvdPathRounds), "svd");
   }
   BST_CATCH
 }
@@ -537,7 +593,7 @@ bst_status bst_svd_write(bst_svd* p, const int64_t* kept, int32_t absorb, void* 
   l.nwork = (int64_t)work.size();
   l.secs = at<const SvdSec>(ws, P.ws_secs);
   l.X = at<const double>(ws, P.ws_x);
-  l.V = at<const double>(ws, P.ws_v);
+  l.rowpos = at<const int32_t>(ws, P.ws_rowpos);
   l.sorted = at<const double>(ws, P.ws_sorted);
   l.perm = at<const int32_t>(ws, P.ws_perm);
   l.absorb = absorb;
