@@ -352,9 +352,16 @@ hipError_t launch_svd_finish(const SvdLaunch& l, hipStream_t s, int path) {
 // Truncation across sectors (one workgroup).  Every sector first keeps its
 // min_blockdim largest values; the other values not below err are the
 // candidates, ordered by value (descending), then sector, then position; the
-// first keepdim - (forced) of them are kept.  The cut is found by bisection
-// on the bit pattern of the values (non-negative doubles order like their
-// bits), then on the flat position among values equal to the cut.
+// first keepdim - (forced) of them are kept.  The cut is found on the bit
+// pattern of the values (non-negative doubles order like their bits), four
+// bits at a time: each wave counts the candidates not below one of the 16
+// next digits, and a sector's count is a binary search, since its values are
+// sorted.  It is found when exactly the wanted number lie at or above it;
+// where equal values leave no such cut, the last of them go by sector.
+//
+// Bound: latency, a round is one search in LDS and a barrier.  A two-site
+// state at chi = 256 (15 sectors, 510 values): 292 us with a scan of all values
+// for each bit, now 12 us.
 // ------------------------------------------------------------------------
 constexpr int kSelectMaxSectors = 4096;
 constexpr int kSelectLdsValues = 8192;   // values staged in LDS when they all fit
@@ -364,116 +371,136 @@ __global__ __launch_bounds__(1024) void svd_select_kernel(const SvdSec* __restri
                                                          const int64_t* __restrict__ min_blockdim,
                                                          int64_t keepdim, double err, int64_t* __restrict__ kept,
                                                          double* __restrict__ s_err) {
-  __shared__ unsigned long long red[16];
-  __shared__ int cnt[kSelectMaxSectors];
-  __shared__ long long forced_total, total;
+  constexpr unsigned long long kInf = 0x7FF0000000000000ull;
   __shared__ double vals[kSelectLdsValues];
-  // per sector: value offset (below 2^31: the plan refuses more values),
-  // rank and forced count, staged once, since every counting pass of the
-  // bisections below walks all sectors
-  __shared__ int soff[kSelectMaxSectors], srank[kSelectMaxSectors], sforced[kSelectMaxSectors];
+  // per sector: value offset (below 2^31: the plan refuses more values), the
+  // candidates' range of positions, forced count, values equal to the cut
+  __shared__ int soff[kSelectMaxSectors], base[kSelectMaxSectors], cap[kSelectMaxSectors], cnt[kSelectMaxSectors];
+  __shared__ long long red[17];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int q = tid; q < nsec; q += 1024) {
-    const SvdSec S = secs[q];
-    const int r = S.m < S.n ? S.m : S.n;
+  auto rank_of = [&](int q) {
+    const SvdSec& S = secs[q];
+    return S.m < S.n ? S.m : S.n;
+  };
+  auto forced = [&](int q, int r) -> int {
     const int64_t f = min_blockdim ? min_blockdim[q] : 0;
-    soff[q] = (int)S.s_off;
-    srank[q] = r;
-    sforced[q] = (int)(f < 0 ? 0 : (f < r ? f : r));
-  }
-  __syncthreads();
-  auto rsec = [&](int q) { return srank[q]; };
-  // the sorted values of all sectors (flat, s_off + i) in LDS when they fit:
-  // every bisection step below scans them all
-  if (tid == 0) {
-    long long t = 0;
-    for (int q = 0; q < nsec; ++q) t = (long long)soff[q] + rsec(q) > t ? (long long)soff[q] + rsec(q) : t;
-    total = t;
-  }
-  __syncthreads();
+    return (int)(f < 0 ? 0 : (f < r ? f : r));
+  };
+  const long long total = secs[nsec - 1].s_off + rank_of(nsec - 1);
   const bool staged = total <= kSelectLdsValues;
   if (staged)
-    for (long long e = tid; e < total; e += 1024) vals[e] = sorted[e];
-  const double* src = staged ? (const double*)vals : sorted;
-  auto forced = [&](int q) -> int { return sforced[q]; };
-  // block-wide sum of per-thread counts
-  auto block_sum = [&](unsigned long long v) -> unsigned long long {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    for (int e = tid; e < total; e += 1024) vals[e] = sorted[e];
+  for (int q = tid; q < nsec; q += 1024) {
+    soff[q] = (int)secs[q].s_off;
+    cap[q] = rank_of(q);
+  }
+  __syncthreads();
+  // entries of sector q in [lo, hi) whose bits are t or more: a prefix
+  auto search = [](const auto* v, int lo, int hi, unsigned long long t) {
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      const double x = v[mid];
+      if (((unsigned long long)__double_as_longlong(x) & 0x7FFFFFFFFFFFFFFFull) >= t) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  auto prefix = [&](int q, int lo, int hi, unsigned long long t) {
+    return staged ? search((const BST_LDS double*)vals + soff[q], lo, hi, t) : search(sorted + soff[q], lo, hi, t);
+  };
+  // sum over the wave (the values' count is below 2^31)
+  auto wave_total = [&](int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);   // rotations by 8, 4, 2, 1 within 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true);
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
+           __builtin_amdgcn_readlane(v, 48);
+  };
+  // sums over all threads
+  auto block_total = [&](int n) {
+    const long long v = wave_total(n);
     __syncthreads();
     if (lane == 0) red[wave] = v;
     __syncthreads();
-    unsigned long long t = 0;
+    long long t = 0;
     for (int w = 0; w < 16; ++w) t += red[w];
     return t;
   };
-  // candidates with bits >= lo (mode 0), or with bits == lo and flat < lim (mode 1)
-  auto count = [&](int mode, unsigned long long lo, long long lim) -> unsigned long long {
-    unsigned long long c = 0;
-    for (int q = 0; q < nsec; ++q) {
-      const int r = rsec(q), f = forced(q);
-      for (int i = f + tid; i < r; i += 1024) {
-        const double v = src[(long long)soff[q] + i];
-        if (!(v >= err)) continue;
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-        if (mode == 0) c += b >= lo ? 1 : 0;
-        else c += (b == lo && (long long)soff[q] + i < lim) ? 1 : 0;
+  // candidates: after the forced values (and any NaN, sorted first), down to err
+  int f_mine = 0, c_mine = 0;
+  const unsigned long long ebits = (unsigned long long)__double_as_longlong(err + 0.0) & 0x7FFFFFFFFFFFFFFFull;
+  for (int q = tid; q < nsec; q += 1024) {
+    const int r = cap[q], f = forced(q, r);
+    const int b = max(f, prefix(q, 0, r, kInf + 1));
+    const int c = max(b, prefix(q, b, r, ebits));
+    base[q] = b;
+    cap[q] = c;
+    cnt[q] = 0;
+    f_mine += f;
+    c_mine += c - b;
+  }
+  const long long room = keepdim - block_total(f_mine);
+  const long long ncand = block_total(c_mine);
+  const bool all = room >= ncand, none = room <= 0;
+  // the room-th largest candidate: the largest t with count(t) >= room
+  auto count = [&](unsigned long long t) {   // by one wave
+    int c = 0;
+    for (int q = lane; q < nsec; q += 64) c += prefix(q, base[q], cap[q], t) - base[q];
+    return wave_total(c);
+  };
+  unsigned long long cut = 0ull;
+  bool exact = false;   // count(cut) == room
+  if (!all && !none) {
+    for (int shift = 60; shift >= 0 && !exact; shift -= 4) {
+      const long long c = count(cut | ((unsigned long long)wave << shift));
+      __syncthreads();
+      if (lane == 0) red[wave] = c;
+      __syncthreads();
+      int d = 0;   // the counts fall with the digit; that of 0 is room or more
+      for (int w = 1; w < 16; ++w) d = red[w] >= room ? w : d;
+      cut |= (unsigned long long)d << shift;
+      exact = red[d] == room;
+    }
+    __syncthreads();
+  }
+  if (!all && !none && !exact) {
+    if (wave == 0) {
+      const long long c = count(cut + 1);
+      if (lane == 0) red[16] = room - c;
+    }
+    __syncthreads();
+    for (int q = tid; q < nsec; q += 1024) {
+      const int gt = prefix(q, base[q], cap[q], cut + 1), ge = prefix(q, base[q], cap[q], cut);
+      cnt[q] = ge - gt;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      long long need = red[16];   // of the values equal to the cut
+      for (int q = 0; q < nsec; ++q) {
+        cnt[q] = (int)(cnt[q] < need ? cnt[q] : need);
+        need -= cnt[q];
       }
     }
-    return block_sum(c);
-  };
-  for (int q = tid; q < nsec; q += 1024) cnt[q] = 0;
-  if (tid == 0) {
-    long long ft = 0;
-    for (int q = 0; q < nsec; ++q) ft += forced(q);
-    forced_total = ft;
+    __syncthreads();
   }
+  double e = 0.0;
+  for (int q = tid; q < nsec; q += 1024) {
+    const int r = rank_of(q), f = forced(q, r);
+    int k = f;
+    if (all) k = f + cap[q] - base[q];
+    else if (!none) k = f + prefix(q, base[q], cap[q], exact ? cut : cut + 1) - base[q] + cnt[q];
+    kept[q] = k;
+    if (k < r) e = fmax(e, sorted[soff[q] + k]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) e = fmax(e, __shfl_xor(e, off, 64));
   __syncthreads();
-  const long long room = keepdim - forced_total;
-  const unsigned long long ncand = count(0, 0ull, 0);
-  unsigned long long cut = 0ull;
-  long long lim = 0;
-  bool all = room >= (long long)ncand, none = room <= 0;
-  if (!all && !none) {
-    // the room-th largest candidate value: the largest bit pattern T with
-    // count(>= T) >= room
-    unsigned long long lo = 0ull, hi = 0x7FF0000000000000ull;
-    while (lo < hi) {
-      const unsigned long long mid = lo + (hi - lo + 1) / 2;
-      if (count(0, mid, 0) >= (unsigned long long)room) lo = mid;
-      else hi = mid - 1;
-    }
-    cut = lo;
-    const long long need = room - (long long)count(0, cut + 1, 0);
-    // the smallest flat bound with need equal values before it
-    long long a = 0, b = 0;
-    for (int q = 0; q < nsec; ++q) b = (long long)soff[q] + rsec(q) > b ? (long long)soff[q] + rsec(q) : b;
-    while (a < b) {
-      const long long mid = a + (b - a) / 2;
-      if ((long long)count(1, cut, mid) >= need) b = mid;
-      else a = mid + 1;
-    }
-    lim = a;
-  }
-  for (int q = 0; q < nsec; ++q) {
-    const int r = rsec(q), f = forced(q);
-    int c = 0;
-    for (int i = f + tid; i < r; i += 1024) {
-      const double v = src[(long long)soff[q] + i];
-      if (!(v >= err) || none) continue;
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
-      c += (all || bits > cut || (bits == cut && (long long)soff[q] + i < lim)) ? 1 : 0;
-    }
-    if (c) atomicAdd(&cnt[q], c);
-  }
+  double* const re = reinterpret_cast<double*>(red);
+  if (lane == 0) re[wave] = e;
   __syncthreads();
   if (tid == 0) {
-    double e = 0.0;
-    for (int q = 0; q < nsec; ++q) {
-      const int k = forced(q) + cnt[q];
-      kept[q] = k;
-      if (k < rsec(q)) e = fmax(e, sorted[(long long)soff[q] + k]);
-    }
+    for (int w = 1; w < 16; ++w) e = fmax(e, re[w]);
     *s_err = e;
   }
 }
