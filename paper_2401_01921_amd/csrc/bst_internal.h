@@ -22,6 +22,14 @@ namespace bst {
 // loads (a flat access also holds up every wait for a scalar load).
 #define BST_G __attribute__((address_space(1)))
 
+// Every kernel with MFMAs asks for two waves per SIMD, that is, for at most 256
+// registers.  With one, a workgroup of four waves may have 512, half of them
+// accumulation registers; the compiler then puts the accumulators there but
+// keeps them in ordinary ones across a loop, copying all of them in and out
+// around every k-step (a bare loop of float64 MFMAs ran at 140 instead of 64
+// cycles each, 49 instead of 78 TFLOP/s).
+constexpr int kMfmaWaves = 2;
+
 // ------------------------------------------------------------------------
 // Errors
 // ------------------------------------------------------------------------

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void calib_read_kernel(const dbl2v* __restrict
 
 // iters rounds of 8 independent MFMAs per wave; the accumulators are summed
 // and written so that nothing is optimised away.
-__global__ __launch_bounds__(256) void calib_mfma_f64_kernel(int64_t iters, double* __restrict__ out) {
+__global__ __launch_bounds__(256, kMfmaWaves) void calib_mfma_f64_kernel(int64_t iters, double* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   double a = 1.0 + 1e-3 * lane, b = 1.0 - 1e-3 * lane;
   dbl4 acc[8];
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void calib_mfma_f64_kernel(int64_t iters, doub
   out[(int64_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void calib_mfma_bf16_kernel(int64_t iters, double* __restrict__ out) {
+__global__ __launch_bounds__(256, kMfmaWaves) void calib_mfma_bf16_kernel(int64_t iters, double* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   bf16x8 a, b;
 #pragma unroll

@@ -18,7 +18,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
 template <int FORM, typename TA, typename TC, bool TRANSB, int BM, int BN>
-__global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmTile* __restrict__ tiles,
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_direct_kernel(const GemmTile* __restrict__ tiles,
                                                           const GemmProb* __restrict__ probs,
                                                           const GemmSeg* __restrict__ segs,
                                                           void* const* __restrict__ ptrs) {

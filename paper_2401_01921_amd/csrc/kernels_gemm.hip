@@ -20,11 +20,12 @@
 namespace bst {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
+typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
-// Direct (LDS-free) variants first: index 0 is the default.
+// Direct (LDS-free) variants first.
 static const std::vector<TileShape> kShapesF64 = {{64, 64, 1}, {128, 64, 1}, {64, 128, 1}, {32, 32, 1},
                                                   {32, 32, 0}, {64, 64, 0}, {64, 32, 0}, {32, 64, 0}};
 static const std::vector<TileShape> kShapesF32 = {{64, 64, 1}, {128, 64, 1}, {64, 128, 1}, {32, 32, 1},
@@ -76,8 +77,6 @@ __device__ __forceinline__ void split_bf16(float a, unsigned short* h) {
 }
 
 template <int FORM> struct FormTraits;
-template <> struct FormTraits<BST_FP64> { static constexpr int BK = 16; static constexpr int NP = 0; };
-template <> struct FormTraits<BST_FP32> { static constexpr int BK = 16; static constexpr int NP = 0; };
 template <> struct FormTraits<BST_BF16X3> { static constexpr int BK = 32; static constexpr int NP = 2; };
 template <> struct FormTraits<BST_BF16X6> { static constexpr int BK = 32; static constexpr int NP = 3; };
 
@@ -88,30 +87,22 @@ __device__ __forceinline__ int acc_row(int lane, int r) {
   return F64ACC ? (4 * r + lane / 16) : (4 * (lane / 16) + r);
 }
 
+// Split forms.
 template <int FORM, typename TA, typename TC, bool TRANSB, int BM, int BN>
-__global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmTile* __restrict__ tiles,
-                                                           const GemmProb* __restrict__ probs,
-                                                           const GemmSeg* __restrict__ segs,
-                                                           void* const* __restrict__ ptrs) {
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_grouped_kernel(const GemmTile* __restrict__ tiles,
+                                                                       const GemmProb* __restrict__ probs,
+                                                                       const GemmSeg* __restrict__ segs,
+                                                                       void* const* __restrict__ ptrs) {
   constexpr int BK = FormTraits<FORM>::BK;
   constexpr int NP = FormTraits<FORM>::NP;
-  constexpr bool F64 = (FORM == BST_FP64);
-  constexpr bool BF = (NP > 0);
   constexpr int WM = BM / 2, WN = BN / 2;
   constexpr int SM = WM / 16, SN = WN / 16;
-  using CT = typename std::conditional<F64, double, float>::type;      // MFMA operand (non-bf16)
-  using ACC = typename std::conditional<F64, dbl4, flt4>::type;
-  constexpr int PADF = 2;   // float/double LDS row pad (elements)
-  constexpr int PADH = 8;   // bf16 LDS row pad (elements): keeps 16-byte alignment
+  constexpr int PADH = 8;   // LDS row pad (elements): keeps 16-byte alignment
   constexpr int EA = BM * BK / 256, EB = BN * BK / 256;   // tile elements per thread
 
-  // LDS, double buffered: plain forms store [BK][BM+PADF] (k-major), bf16
-  // forms store planes [NP][BM][BK+PADH] (k contiguous, 16-byte lane reads).
-  constexpr int A_ELEMS = BF ? NP * BM * (BK + PADH) : BK * (BM + PADF);
-  constexpr int B_ELEMS = BF ? NP * BN * (BK + PADH) : BK * (BN + PADF);
-  using LT = typename std::conditional<BF, unsigned short, CT>::type;
-  __shared__ __attribute__((aligned(16))) LT As[2][A_ELEMS];
-  __shared__ __attribute__((aligned(16))) LT Bs[2][B_ELEMS];
+  // LDS, double buffered: planes [NP][BM][BK+PADH], k contiguous, 16-byte lane reads
+  __shared__ __attribute__((aligned(16))) unsigned short As[2][NP * BM * (BK + PADH)];
+  __shared__ __attribute__((aligned(16))) unsigned short Bs[2][NP * BN * (BK + PADH)];
 
   const GemmTile t = tiles[blockIdx.x];
   if (t.prob < 0) return;   // padding of the per-XCD tile lists
@@ -121,11 +112,11 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmTile* __res
   const int wm = wave >> 1, wn = wave & 1;
   const int m0 = t.m0, n0 = t.n0;
 
-  ACC acc[SM][SN];
+  flt4 acc[SM][SN];
 #pragma unroll
   for (int i = 0; i < SM; ++i)
 #pragma unroll
-    for (int j = 0; j < SN; ++j) acc[i][j] = ACC{0, 0, 0, 0};
+    for (int j = 0; j < SN; ++j) acc[i][j] = flt4{0, 0, 0, 0};
 
   // next k-step to fetch: segment ls, offset lk; values staged in registers
   int ls = 0, lk = 0;
@@ -164,14 +155,10 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmTile* __res
     for (int e = 0; e < EA; ++e) {
       const int idx = tid + e * 256;
       const int r = idx / BK, k = idx % BK;
-      if constexpr (BF) {
-        unsigned short h[3];
-        split_bf16<NP>(ra[e], h);
+      unsigned short h[3];
+      split_bf16<NP>(ra[e], h);
 #pragma unroll
-        for (int q = 0; q < NP; ++q) As[buf][(q * BM + r) * (BK + PADH) + k] = h[q];
-      } else {
-        As[buf][k * (BM + PADF) + r] = (CT)ra[e];
-      }
+      for (int q = 0; q < NP; ++q) As[buf][(q * BM + r) * (BK + PADH) + k] = h[q];
     }
 #pragma unroll
     for (int e = 0; e < EB; ++e) {
@@ -179,68 +166,43 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmTile* __res
       int n, k;
       if constexpr (TRANSB) { n = idx / BK; k = idx % BK; }
       else { k = idx / BN; n = idx % BN; }
-      if constexpr (BF) {
-        unsigned short h[3];
-        split_bf16<NP>(rb[e], h);
+      unsigned short h[3];
+      split_bf16<NP>(rb[e], h);
 #pragma unroll
-        for (int q = 0; q < NP; ++q) Bs[buf][(q * BN + n) * (BK + PADH) + k] = h[q];
-      } else {
-        Bs[buf][k * (BN + PADF) + n] = (CT)rb[e];
-      }
+      for (int q = 0; q < NP; ++q) Bs[buf][(q * BN + n) * (BK + PADH) + k] = h[q];
     }
   };
   auto compute = [&](int buf) {
-    if constexpr (BF) {
-      bf16x8 a[NP][SM], b[NP][SN];
-      const int kl = 8 * (lane >> 4);
+    bf16x8 a[NP][SM], b[NP][SN];
+    const int kl = 8 * (lane >> 4);
 #pragma unroll
-      for (int q = 0; q < NP; ++q) {
+    for (int q = 0; q < NP; ++q) {
 #pragma unroll
-        for (int i = 0; i < SM; ++i) {
-          const int r = wm * WM + i * 16 + (lane & 15);
-          us8 raw = *reinterpret_cast<const us8*>(&As[buf][(q * BM + r) * (BK + PADH) + kl]);
-          a[q][i] = __builtin_bit_cast(bf16x8, raw);
-        }
-#pragma unroll
-        for (int j = 0; j < SN; ++j) {
-          const int c = wn * WN + j * 16 + (lane & 15);
-          us8 raw = *reinterpret_cast<const us8*>(&Bs[buf][(q * BN + c) * (BK + PADH) + kl]);
-          b[q][j] = __builtin_bit_cast(bf16x8, raw);
-        }
+      for (int i = 0; i < SM; ++i) {
+        const int r = wm * WM + i * 16 + (lane & 15);
+        us8 raw = *reinterpret_cast<const us8*>(&As[buf][(q * BM + r) * (BK + PADH) + kl]);
+        a[q][i] = __builtin_bit_cast(bf16x8, raw);
       }
 #pragma unroll
-      for (int i = 0; i < SM; ++i)
-#pragma unroll
-        for (int j = 0; j < SN; ++j) {
-          if constexpr (NP == 3) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2][i], b[0][j], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[1][j], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[2][j], acc[i][j], 0, 0, 0);
-          }
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[0][j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[1][j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[0][j], acc[i][j], 0, 0, 0);
-        }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 4) {
-        const int k = kk + (lane >> 4);
-        CT a[SM], b[SN];
-#pragma unroll
-        for (int i = 0; i < SM; ++i) a[i] = As[buf][k * (BM + PADF) + wm * WM + i * 16 + (lane & 15)];
-#pragma unroll
-        for (int j = 0; j < SN; ++j) b[j] = Bs[buf][k * (BN + PADF) + wn * WN + j * 16 + (lane & 15)];
-#pragma unroll
-        for (int i = 0; i < SM; ++i)
-#pragma unroll
-          for (int j = 0; j < SN; ++j) {
-            if constexpr (F64)
-              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-          }
+      for (int j = 0; j < SN; ++j) {
+        const int c = wn * WN + j * 16 + (lane & 15);
+        us8 raw = *reinterpret_cast<const us8*>(&Bs[buf][(q * BN + c) * (BK + PADH) + kl]);
+        b[q][j] = __builtin_bit_cast(bf16x8, raw);
       }
     }
+#pragma unroll
+    for (int i = 0; i < SM; ++i)
+#pragma unroll
+      for (int j = 0; j < SN; ++j) {
+        if constexpr (NP == 3) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2][i], b[0][j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[1][j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[2][j], acc[i][j], 0, 0, 0);
+        }
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[0][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[1][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[0][j], acc[i][j], 0, 0, 0);
+      }
   };
 
   // pipeline: the next k-step's global loads are in flight while the
@@ -268,20 +230,279 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GemmTile* __res
     for (int j = 0; j < SN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
+        const int row = m0 + wm * WM + i * 16 + acc_row<false>(lane, r);
+        const int col = n0 + wn * WN + j * 16 + (lane & 15);
+        if (row < p.M && col < p.N) C[(int64_t)row * p.ldc + col] = (TC)acc[i][j][r];
+      }
+}
+
+// float64 / float32 forms.
+//
+// The sectors of a block-sparse operand are small and odd (a chi = 2048 spin-1/2
+// H_eff has 372 block pairs of some 3 to 200 rows and K of 3 to 110).  Without
+// its MFMAs this kernel takes nearly as long as with them, so what counts are
+// the instructions that move operands, the L1's above all (it was busy nine
+// cycles of ten with 8-byte loads):
+//   - two neighbouring elements per load where the step and the tile lie inside
+//     the segment and the block;
+//   - a wave runs the MFMAs of its 16 x 16 sub-tiles that hold elements of the
+//     block, and of a segment's last k-step those that reach into it;
+//   - loads run D k-steps ahead, in registers, across segments; the record of
+//     the next segment is read one segment ahead.
+// Rows and columns past the block read its last one (their results are not
+// stored); k past the segment reads its last and is replaced by zero.
+//
+// LDS holds a row of A (and of a transposed B) as its 16 k in the order in which
+// the four lane groups read them, each group its operands of the step's four
+// MFMAs as one run.  float64: group g and MFMA q take k = 8 (q / 2) + 2 g + q % 2,
+// so that a loaded pair stays one 16-byte store.  float32: k = 4 q + g, the plain
+// order of the sum.  Rows are 18 doubles or 20 floats apart, so that the 16 rows
+// of a read lie in different banks; k-rows of a plain B likewise.
+//
+// L.psi / T3.R, with one-element loads, a zero for each element outside, every
+// MFMA run and one register stage, then now: float64, spin-1/2 chi = 2048 (32 x 32)
+// 28.5 / 32.8 -> 26.6 / 29.1 us, spin-1 chi = 4096 (64 x 32) 201 / 198 -> 174 / 161
+// us; float32, chi = 4096 (64 x 64) 136 / 132 -> 109 / 102 us.  The MFMAs of the
+// chi = 4096 steps alone take 104 (float64).
+template <int FORM, typename TA, typename TC, bool TRANSB, int BM, int BN, int D>
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmTile* __restrict__ tiles,
+                                                                     const GemmProb* __restrict__ probs,
+                                                                     const GemmSeg* __restrict__ segs,
+                                                                     void* const* __restrict__ ptrs) {
+  constexpr bool F64 = (FORM == BST_FP64);
+  constexpr int BK = 16, WM = BM / 2, WN = BN / 2, SM = WM / 16, SN = WN / 16;
+  constexpr int EA = BM / 32, EB = BN / 32;               // pairs per lane and k-step
+  constexpr int KB = 512 / BN;                            // k rows of B per load (not transposed)
+  constexpr int LDK = F64 ? 18 : 20;                      // LDS row of A (and B if transposed)
+  constexpr int LDN = F64 ? BN + 8 : BN + 16;             // LDS k-row of B if not
+  using CT = typename std::conditional<F64, double, float>::type;
+  using ACC = typename std::conditional<F64, dbl4, flt4>::type;
+  typedef CT CT2 __attribute__((ext_vector_type(2)));
+  typedef TA TA2 __attribute__((ext_vector_type(2)));
+  typedef TA TA2u __attribute__((ext_vector_type(2), aligned(sizeof(TA))));
+  typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+  __shared__ __attribute__((aligned(16))) CT As[2][BM * LDK];
+  __shared__ __attribute__((aligned(16))) CT Bs[2][TRANSB ? BN * LDK : BK * LDN];
+
+  const GemmTile t = tiles[blockIdx.x];
+  if (t.prob < 0) return;   // padding of the per-XCD tile lists
+  const GemmProb p = probs[t.prob];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int m0 = t.m0, n0 = t.n0;
+  // sub-tiles of this wave that hold elements of the block
+  const int mi = min(max((p.M - m0 - wm * WM + 15) / 16, 0), SM);
+  const int nj = min(max((p.N - n0 - wn * WN + 15) / 16, 0), SN);
+  const bool inner_n = TRANSB || n0 + BN <= p.N;   // pairs of columns lie inside the block
+
+  ACC acc[SM][SN];
+#pragma unroll
+  for (int i = 0; i < SM; ++i)
+#pragma unroll
+    for (int j = 0; j < SN; ++j) acc[i][j] = ACC{0, 0, 0, 0};
+
+  // load cursor: segment ls at k = lk
+  int ls = 0, lk = 0, lK = 0;
+  int64_t ldb = 0;
+  const BST_G TA* pa[EA];
+  const BST_G double* pb[EB];
+  GemmSeg nxt{};
+  int a_buf = -1, b_buf = -1;
+  const BST_G TA* A = nullptr;
+  const BST_G double* B = nullptr;
+  const int ak = 2 * (tid & 7), ar = tid >> 3;                           // A: first k of the pair, row
+  const int bk = TRANSB ? ak : tid / (BN / 2), bn = TRANSB ? ar : 2 * (tid % (BN / 2));
+  auto begin = [&]() {   // the segment in nxt becomes current
+    const GemmSeg g = nxt;
+    if (g.a_buf != a_buf) A = (const BST_G TA*)(ptrs[a_buf = g.a_buf]);
+    if (g.b_buf != b_buf) B = (const BST_G double*)(ptrs[b_buf = g.b_buf]);
+    if (ls + 1 < p.seg_count) nxt = segs[p.seg_begin + ls + 1];
+    lk = 0;
+    lK = g.K;
+    ldb = g.ldb;
+#pragma unroll
+    for (int e = 0; e < EA; ++e) pa[e] = A + g.a_off + (int64_t)min(m0 + ar + 32 * e, p.M - 1) * g.lda + ak;
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      if constexpr (TRANSB)
+        pb[e] = B + g.b_off + (int64_t)min(n0 + bn + 32 * e, p.N - 1) * g.ldb + bk;
+      else
+        pb[e] = B + g.b_off + (int64_t)(bk + KB * e) * g.ldb + min(n0 + bn, p.N - 1);
+    }
+  };
+  TA2 ra[D][EA];
+  dbl2 rb[D][EB];
+  int kv[D];   // k of a step inside its segment
+  auto fetch = [&](TA2 (&a)[EA], dbl2 (&b)[EB], int& k) {
+    k = min(BK, lK - lk);
+    if (k == BK) {
+#pragma unroll
+      for (int e = 0; e < EA; ++e) a[e] = *reinterpret_cast<const BST_G TA2u*>(pa[e]);
+    } else {
+      const int o0 = min(k - 1 - ak, 0), o1 = min(k - 1 - ak, 1);   // element k or the last
+#pragma unroll
+      for (int e = 0; e < EA; ++e) a[e] = TA2{pa[e][o0], pa[e][o1]};
+    }
+    if (k == BK && inner_n) {
+#pragma unroll
+      for (int e = 0; e < EB; ++e) b[e] = *reinterpret_cast<const BST_G dbl2u*>(pb[e]);
+    } else if constexpr (TRANSB) {
+      const int o0 = min(k - 1 - bk, 0), o1 = min(k - 1 - bk, 1);
+#pragma unroll
+      for (int e = 0; e < EB; ++e) b[e] = dbl2{pb[e][o0], pb[e][o1]};
+    } else {
+      const int c1 = n0 + bn + 1 < p.N ? 1 : 0;   // the column's neighbour or itself
+#pragma unroll
+      for (int e = 0; e < EB; ++e) {
+        const BST_G double* const q = pb[e] + min(k - 1 - bk - KB * e, 0) * ldb;
+        b[e] = dbl2{q[0], q[c1]};
+      }
+    }
+    lk += BK;
+    if (lk < lK) {
+#pragma unroll
+      for (int e = 0; e < EA; ++e) pa[e] += BK;
+#pragma unroll
+      for (int e = 0; e < EB; ++e) pb[e] += TRANSB ? BK : BK * ldb;
+    } else if (++ls < p.seg_count) {
+      begin();
+    }
+  };
+  // a pair's place in its row
+  auto put = [&](CT* row, CT x, CT y) {
+    if constexpr (F64) {
+      *reinterpret_cast<CT2*>(row + 2 * (ak & 6) + 2 * (ak >> 3)) = CT2{x, y};
+    } else {
+      row[4 * (ak & 3) + (ak >> 2)] = x;
+      row[4 * (ak & 3) + (ak >> 2) + 4] = y;
+    }
+  };
+  // (k past the segment is replaced here and not after the load, which would wait for it)
+  auto stage = [&](int buf, TA2 (&a)[EA], dbl2 (&b)[EB], int k) {
+    if (k < BK) {
+#pragma unroll
+      for (int e = 0; e < EA; ++e) a[e] = TA2{ak < k ? a[e].x : (TA)0, ak + 1 < k ? a[e].y : (TA)0};
+#pragma unroll
+      for (int e = 0; e < EB; ++e) {
+        if constexpr (TRANSB) b[e] = dbl2{bk < k ? b[e].x : 0.0, bk + 1 < k ? b[e].y : 0.0};
+        else b[e] = bk + KB * e < k ? b[e] : dbl2{0.0, 0.0};
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < EA; ++e) put(As[buf] + (ar + 32 * e) * LDK, (CT)a[e].x, (CT)a[e].y);
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      if constexpr (TRANSB) put(Bs[buf] + (bn + 32 * e) * LDK, (CT)b[e].x, (CT)b[e].y);
+      else *reinterpret_cast<CT2*>(Bs[buf] + (bk + KB * e) * LDN + bn) = CT2{(CT)b[e].x, (CT)b[e].y};
+    }
+  };
+  auto mfma = [&](CT a, CT b, ACC c) -> ACC {
+    if constexpr (F64) return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  };
+  const bool full = mi == SM && nj == SN;
+  const int l16 = lane & 15, lg = lane >> 4;
+  auto compute = [&](int buf, int k) {
+    const CT* const as = As[buf] + (wm * WM + l16) * LDK;
+    const CT* const bs = Bs[buf] + (TRANSB ? (wn * WN + l16) * LDK : wn * WN + l16);
+    // a lane's operands of MFMA q: element q of its run
+    auto run = [&](const CT* row, CT (&v)[4]) {
+      if constexpr (F64) {
+        const dbl2 lo = *reinterpret_cast<const dbl2*>(row), hi = *reinterpret_cast<const dbl2*>(row + 2);
+        v[0] = lo.x;
+        v[1] = lo.y;
+        v[2] = hi.x;
+        v[3] = hi.y;
+      } else {
+        const flt4 w = *reinterpret_cast<const flt4*>(row);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = w[q];
+      }
+    };
+    CT a[SM][4], b[SN][4];
+#pragma unroll
+    for (int i = 0; i < SM; ++i) run(as + 16 * i * LDK + 4 * lg, a[i]);
+#pragma unroll
+    for (int j = 0; j < SN; ++j) {
+      if constexpr (TRANSB) {
+        run(bs + 16 * j * LDK + 4 * lg, b[j]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          b[j][q] = bs[(F64 ? 8 * (q >> 1) + 2 * lg + (q & 1) : 4 * q + lg) * LDN + 16 * j];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if ((F64 ? 8 * (q >> 1) + (q & 1) : 4 * q) >= k) break;
+#pragma unroll
+      for (int i = 0; i < SM; ++i)
+#pragma unroll
+        for (int j = 0; j < SN; ++j)
+          if (full || (i < mi && j < nj)) acc[i][j] = mfma(a[i][q], b[j][q], acc[i][j]);
+    }
+  };
+
+  // k-steps of the tile
+  int steps = 0;
+  for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
+  if (steps > 0) {
+    nxt = segs[p.seg_begin];
+    begin();
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (d < steps) fetch(ra[d], rb[d], kv[d]);
+    stage(0, ra[0], rb[0], kv[0]);
+    __syncthreads();
+    // step u computes from LDS, step u + 1 is staged, step u + D is loaded
+    for (int u0 = 0; u0 < steps; u0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int u = u0 + d;
+        if (u >= steps) break;
+        const int k = kv[d];
+        if (u + D < steps) fetch(ra[d], rb[d], kv[d]);
+        if (mi > 0 && nj > 0) compute(D % 2 ? u & 1 : d & 1, k);
+        const int e = (d + 1) % D;
+        if (u + 1 < steps) stage(D % 2 ? (u + 1) & 1 : (d + 1) & 1, ra[e], rb[e], kv[e]);
+        __syncthreads();
+      }
+    }
+  }
+  // ---- epilogue: each element written exactly once ----
+  BST_G TC* __restrict__ C = (BST_G TC*)(ptrs[p.c_buf]) + p.c_off;
+#pragma unroll
+  for (int i = 0; i < SM; ++i)
+#pragma unroll
+    for (int j = 0; j < SN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
         const int row = m0 + wm * WM + i * 16 + acc_row<F64>(lane, r);
         const int col = n0 + wn * WN + j * 16 + (lane & 15);
         if (row < p.M && col < p.N) C[(int64_t)row * p.ldc + col] = (TC)acc[i][j][r];
       }
 }
 
+// k-steps that loads run ahead.  32 x 32 float64 at 1, 2, 3, 4: T3.R of chi =
+// 512 14.3, 13.7, 13.3, 13.1 us, of chi = 2048 31.6, 28.4, 29.5, 29.4 us, L.psi of
+// chi = 2048 26.1, 25.4, 27.7, 27.8 us: more depth costs registers, that is waves,
+// which hide as much.  64 x 64 float32 (chi = 4096 L.psi) 120, 130, 131, 146 us.
+template <int FORM, int BM, int BN>
+constexpr int kBlockDepth = FORM == BST_FP64 || BM * BN <= 1024 ? 2 : 1;
+
 template <int FORM, typename TA, typename TC, bool TRANSB>
 static hipError_t launch_shape(int bm, int bn, const GemmLaunch& g, hipStream_t s) {
   dim3 grid((unsigned)g.ntiles), block(256);
-#define BST_SHAPE(BM_, BN_)                                                                  \
-  if (bm == BM_ && bn == BN_) {                                                              \
-    hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, TRANSB, BM_, BN_>), grid, block, 0, \
-                       s, g.tiles, g.probs, g.segs, g.ptrs);                                 \
-    return hipGetLastError();                                                                \
+#define BST_SHAPE(BM_, BN_)                                                                      \
+  if (bm == BM_ && bn == BN_) {                                                                  \
+    if constexpr (FORM == BST_FP64 || FORM == BST_FP32)                                          \
+      hipLaunchKernelGGL((gemm_block_kernel<FORM, TA, TC, TRANSB, BM_, BN_, kBlockDepth<FORM, BM_, BN_>>), grid, block, 0, s, \
+                         g.tiles, g.probs, g.segs, g.ptrs);                                      \
+    else                                                                                         \
+      hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, TRANSB, BM_, BN_>), grid, block, 0,   \
+                         s, g.tiles, g.probs, g.segs, g.ptrs);                                   \
+    return hipGetLastError();                                                                    \
   }
   if constexpr (FORM == BST_FP64) {
     BST_SHAPE(32, 32) BST_SHAPE(64, 64) BST_SHAPE(64, 32) BST_SHAPE(32, 64)

@@ -201,7 +201,7 @@ const std::vector<TileShape>& gemm_planes_shapes(int np) {
 }
 
 template <int NP, typename TC, int BM, int BN, int BK>
-__global__ __launch_bounds__(256) void gemm_planes_kernel(const GemmTile* __restrict__ tiles,
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_planes_kernel(const GemmTile* __restrict__ tiles,
                                                           const GemmProb* __restrict__ probs,
                                                           const GemmSeg* __restrict__ segs,
                                                           void* const* __restrict__ ptrs,

@@ -132,11 +132,11 @@ __device__ __attribute__((aligned(1024))) unsigned int g_stream_zero[64 * 4] = {
 constexpr int kSinkWgs = 4 * kStreamCUs;
 __device__ __attribute__((aligned(256))) double g_stream_sink[kSinkWgs * 8 * 16];
 
+// (a SIMD can hold two waves only where LDS has room for eight per CU)
 template <int NP, typename TC, int BM, int BN, int S, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_planes_stream_kernel(const KStep* __restrict__ steps,
-                                                                 const int64_t* __restrict__ wg_begin,
-                                                                 void* const* __restrict__ ptrs,
-                                                                 const int64_t* __restrict__ rowtab) {
+__global__ __launch_bounds__(64 * WGM * WGN, stream_wgs_per_cu(NP, BM, BN, S) * WGM * WGN < 8 ? 1 : kMfmaWaves)
+void gemm_planes_stream_kernel(const KStep* __restrict__ steps, const int64_t* __restrict__ wg_begin,
+                               void* const* __restrict__ ptrs, const int64_t* __restrict__ rowtab) {
   constexpr int NW = WGM * WGN, NT = 64 * NW;             // waves, lanes
   constexpr int WM = BM / WGM, WN = BN / WGN, SM = WM / 16, SN = WN / 16;
   constexpr int NC = 4 * NP;                            // 16-byte pieces per operand row
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_planes_stream_kernel(cons
 // 16-byte LDS reads) for the step's four MFMAs.  The sum over the step is the
 // same set of products in a fixed order, so results are bitwise repeatable.
 template <int BM, int BN, int S, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_f64_stream_kernel(const KStep* __restrict__ steps,
+__global__ __launch_bounds__(64 * WGM * WGN, kMfmaWaves) void gemm_f64_stream_kernel(const KStep* __restrict__ steps,
                                                                      const int64_t* __restrict__ wg_begin,
                                                                      void* const* __restrict__ ptrs,
                                                                      const int64_t* __restrict__ rowtab) {
@@ -605,7 +605,7 @@ hipError_t launch_gemm_planes_stream(const StreamLaunch& g, hipStream_t s) {
 // ring slot beside the operand stages.
 // ------------------------------------------------------------------------
 template <int NMAX>
-__global__ __launch_bounds__(512) void lh_fused_kernel(const KStep* __restrict__ steps,
+__global__ __launch_bounds__(512, kMfmaWaves) void lh_fused_kernel(const KStep* __restrict__ steps,
                                                        const int64_t* __restrict__ wg_begin,
                                                        void* const* __restrict__ ptrs,
                                                        const float* __restrict__ coef,

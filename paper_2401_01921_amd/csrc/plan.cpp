@@ -604,8 +604,26 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
                          lab(W2.legs[3], "w3"), lab(psi.legs[3], "y")});
   P.t1_numel = T1->numel;
   P.t3_numel = T3->numel;
-  P.internals.push_back({6, (size_t)T1->numel * 8, 0});
-  P.internals.push_back({7, (size_t)T3->numel * 8, 0});
+  // Both are the plan's own, so their rows are padded to 16 elements: a row's
+  // 16 k of a GEMM step (and a row of 16 results) is then one 128-byte line of
+  // float64 instead of parts of two, and the number of lines requested is what
+  // bounds those steps.  Block b starts at off[b], its rows are ld[b] apart.
+  struct Rows {
+    std::vector<int64_t> off, ld;
+    int64_t total = 0;
+    Rows(const TensorDesc& T, int split) {
+      for (int64_t b = 0; b < T.nblocks; ++b) {
+        int64_t rows = 1, cols = 1;
+        for (int i = 0; i < T.rank(); ++i) (i < split ? rows : cols) *= T.block_shape(b)[i];
+        off.push_back(total);
+        ld.push_back((cols + 15) / 16 * 16);
+        total += rows * ld.back();
+      }
+    }
+  };
+  const Rows T1r(*T1, 2), T3r(*T3, 3);
+  P.internals.push_back({6, (size_t)T1r.total * 8, 0});
+  P.internals.push_back({7, (size_t)T3r.total * 8, 0});
   // bfloat16 planes for the split forms: L [(a w) x a'], R [b x (w b')],
   // psi transposed to [(t1 t2 b') x a'], T3 [(a s1 s2) x (w3 b')]
   P.has_planes = true;
@@ -681,11 +699,11 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
       const int64_t* sh = T1->block_shape(cb);
       GemmProb p{};
       const int64_t M = sh[0] * sh[1], N = sh[2] * sh[3] * sh[4];
-      p.c_off = T1->offset[cb];
+      p.c_off = T1r.off[cb];
       p.c_buf = 6;
       p.M = (int32_t)M;
       p.N = (int32_t)N;
-      p.ldc = (int32_t)N;
+      p.ldc = (int32_t)T1r.ld[cb];
       p.seg_begin = (int32_t)s1.segs.size();
       for (int kap = 0; kap < nA; ++kap) {
         lt[0] = t[0]; lt[1] = t[1]; lt[2] = kap;
@@ -765,7 +783,7 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
       p.seg_begin = (int32_t)s1.segs_alt.size();
       p.seg_count = 0;
       s1.probs_alt.push_back(p);
-      cum += T1->block_size(cb);
+      cum += (int64_t)p.M * p.ldc;
     }
     // the T1 buffer holds the float64 block layout or this merged one (float32
     // for the split forms, float64 for the float64 panels)
@@ -828,10 +846,10 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
               for (int64_t c = 0; c < gw; ++c)
                 for (int64_t e1 = 0; e1 < g1; ++e1)
                   for (int64_t e2 = 0; e2 < g2; ++e2) {
-                    const int64_t in_blk = ((c * g1 + e1) * g2 + e2) * gy;
-                    ins.push_back({T1->offset[b] + in_blk, gw * g1 * g2 * gy});
+                    const int64_t in_blk = c * T1r.ld[b] + (e1 * g2 + e2) * gy;
+                    ins.push_back({T1r.off[b] + in_blk, gw * T1r.ld[b]});
                     if (t1zero[b] >= 0) {
-                      ins_alt.push_back({t1zero[b] + in_blk, gw * g1 * g2 * gy});
+                      ins_alt.push_back({t1zero[b] + in_blk, gw * T1r.ld[b]});
                       fin.push_back({0, 0, 0, 0, 0, 0});
                     } else {
                       const int64_t ld = t1m_ld[kx];
@@ -872,7 +890,7 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
               for (int64_t e1 = 0; e1 < g1; ++e1)
                 for (int64_t e2 = 0; e2 < g2; ++e2)
                   for (int64_t c = 0; c < gw; ++c) {
-                    outs.push_back({T3->offset[b] + ((e1 * g2 + e2) * gw + c) * gy, g1 * g2 * gw * gy});
+                    outs.push_back({T3r.off[b] + (e1 * g2 + e2) * T3r.ld[b] + c * gy, g1 * g2 * T3r.ld[b]});
                     if (read)
                       outs_alt.push_back({t3g[kb3] + (prow[pb3] + e1 * g2 + e2) * t3w[kb3] +
                                               rseg[rb3] + c * gy,
@@ -1003,12 +1021,12 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
           if (ab < 0 || bb < 0) continue;
           const int64_t K = W2.legs[3].g[kw] * psi.legs[3].g[ky];
           GemmSeg g{};
-          g.a_off = T3->offset[ab];
+          g.a_off = T3r.off[ab];
           g.a_buf = 7;
           g.b_off = R.offset[bb];
           g.b_buf = 3;
           g.K = (int32_t)K;
-          g.lda = (int32_t)K;
+          g.lda = (int32_t)T3r.ld[ab];
           g.ldb = (int32_t)K;
           s4.segs.push_back(g);
           s4.flops += 2.0 * (double)M * (double)N * (double)K;
@@ -1509,8 +1527,18 @@ static Step::StreamList make_fused(std::vector<uint8_t>& blob, const Step& st, i
 int default_tile(const Step& st, bst_precision form) {
   auto it = st.tile_choice.find((int)form);
   if (it != st.tile_choice.end()) return it->second;
-  // float64 / float32: the LDS-staged 64x64 kernel
-  if (form == BST_FP64 || form == BST_FP32) return 5;
+  // float64 / float32: a larger tile of the staged kernel once it gives every
+  // CU four workgroups, else 32 x 32.  A larger tile reads its operands less
+  // often, a smaller one spreads few blocks over more CUs and pads less.  Steps
+  // of H_eff, us, 32 x 32 against the larger tile, at the larger one's count:
+  //   float64, 64 x 32: 92 tiles 13.5 / 15.6, 520 29.1 / 31.4, 2280 26.6 / 26.2,
+  //                     3162 171 / 161, 14512 191 / 174
+  //   float32, 64 x 64: 248 tiles 7.6 / 8.2, 304 25.7 / 29.3, 1312 22.7 / 20.1,
+  //                     1749 139 / 102, 7993 152 / 109
+  if (form == BST_FP64 || form == BST_FP32) {
+    const int64_t tiles = form == BST_FP64 ? st.tiles64x32 : st.tiles64x64;
+    return tiles < 4 * kStreamCUs ? 4 : form == BST_FP64 ? 6 : 5;
+  }
   // on-the-fly split forms: 64x64 unless most problems are small
   const auto& shapes = gemm_tile_shapes(form);
   double avg = 0;
@@ -1533,6 +1561,12 @@ void finalize(PlanData& P) {
         st.off1 = put(P.blob, st.segs);
         st.tile_lists.clear();
         st.tile_lists_alt.clear();
+        st.tiles64x32 = st.tiles64x64 = 0;
+        for (const auto& p : st.probs) {
+          const int64_t rows = (p.M + 63) / 64;
+          st.tiles64x32 += rows * ((p.N + 31) / 32);
+          st.tiles64x64 += rows * ((p.N + 63) / 64);
+        }
         for (int f = 0; f < 4; ++f)
           for (const auto& sh : gemm_tile_shapes((bst_precision)f)) {
             auto key = std::make_pair(sh.bm, sh.bn);

@@ -51,6 +51,7 @@ struct Step {
   std::vector<GemmProb> probs;
   std::vector<GemmSeg> segs;
   std::map<int, int> tile_choice;   // form -> index into gemm_tile_shapes(form)
+  int64_t tiles64x32 = 0, tiles64x64 = 0;   // tiles of that size over all problems
   // Permute
   std::vector<PermJob> jobs;
   std::vector<PermWork> pwork;

@@ -1,0 +1,49 @@
+"""The staged float64 / float32 sector GEMM at the edges of its tiles: rows and
+columns just below, at and above 16, 32 and 64, segments whose K ends inside, at
+or after a k-step, odd strides and offsets, B read along k and across it.  Every
+tile shape gives the same bits (the k order is one and the same) and the oracle's
+result within the form's tolerance."""
+import numpy as np
+import pytest
+
+from tests.gpu_common import DEV, check, dev, host, require_gpu, torch
+from oracle import oracle as orc
+from paper_2401_01921_amd import bst
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("b_order", [("k", "l", "j"), ("j", "k", "l")], ids=["B plain", "B along k"])
+@pytest.mark.parametrize("rows, cols", [((1, 17, 33), (1, 16, 65)), ((64, 65, 31), (32, 33, 63)),
+                                        ((15, 129, 2), (130, 7, 64))])
+def test_tile_edges(prec, b_order, rows, cols):
+    i = (1, list(enumerate(rows)))
+    j = (-1, list(enumerate(cols)))
+    k, l = (-1, [(0, 1), (1, 3), (2, 15)]), (-1, [(-1, 5), (0, 1), (1, 16)])   # K of 1 to 240
+    A = orc.BlockTensor(["i", "k", "l"], [i, k, l])
+    flip = {"j": j, "k": (1, k[1]), "l": (1, l[1])}
+    B = orc.BlockTensor(list(b_order), [flip[x] for x in b_order])
+    rng = np.random.default_rng(11)
+    A.data[:] = rng.standard_normal(A.numel)
+    B.data[:] = rng.standard_normal(B.numel)
+    C = orc.contract(A, B)
+    tC, plan = bst.contract_plan(bst.Tensor(A.labels, A.legs), bst.Tensor(B.labels, B.legs), prec)
+    ws = bst.workspace(plan.workspace_bytes)
+    first = None
+    for tile in range(plan.tile_count(prec)):
+        plan.set_tile(prec, tile)
+        if "l;" not in plan.tiles():
+            continue
+        out = torch.full((tC.numel,), np.nan, dtype=torch.float64, device=DEV)
+        plan.execute([dev(A.data), dev(B.data)], [out], ws)
+        got = host(out)
+        check(got, C.data, prec, f"{plan.tiles()}")
+        first = got if first is None else first
+        assert np.array_equal(got, first), plan.tiles()
+    assert first is not None
