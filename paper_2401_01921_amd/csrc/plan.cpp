@@ -1550,6 +1550,59 @@ int default_tile(const Step& st, bst_precision form) {
   return 0;
 }
 
+// Shape of a plane GEMM without a tuned choice.  All of them give the same
+// bits; what decides is whether the tiles fill the chip.  us on steps of H_eff,
+// chosen shape against the next best and against 256 x 128 or 128 x 256 (two
+// planes) or 128 x 128 (three), the former choice at every size:
+//   two planes   up to 127 tiles of 128 x 64, 32 x 32 staged (no schedule to
+//                read, many workgroups): 24 tiles 12.2 / 13.7 / 22.5, 64 tiles
+//                15.7 / 16.9 / 28.6; 134 tiles 22.6 / 20.9, 511 15.5 / 11.7;
+//                above, 128 x 64 (64 x 128 where most work is in wide problems):
+//                134 tiles 20.9 / 20.6 / 35.4, 726 43.5 / 48.5 / 53.5, 3162
+//                40.2 / 42.1 / 44.8; two stages, so that more than one workgroup
+//                fits a CU
+//   three planes 64 x 64 up to 1023 tiles of 128 x 128: 24 tiles 14.4 / 21.8,
+//                470 90.8 / 93.5; 1616 84.8 / 68.2
+//   float64      64 x 64 up to 511 tiles of 128 x 64, then 128 x 64: 134 tiles
+//                41.1 / 60.1, 511 25.2 / 27.9; 726 198 / 190, 3162 162 / 155
+// The first of the list whose schedule exists (its layout rules hold) is taken.
+static int planes_auto_tile(const Step& st, int np) {
+  double wm = 0, wn = 0;
+  int64_t t128x64 = 0, t128 = 0;
+  for (const auto& p : st.probs_alt) {
+    int64_t k = 0;
+    for (int q = 0; q < p.seg_count; ++q) k += st.segs_alt[p.seg_begin + q].K;
+    const double w = (double)p.M * (double)p.N * (double)std::max<int64_t>(k, 1);
+    wm += w * p.M;
+    wn += w * p.N;
+    const int64_t rows = (p.M + 127) / 128;
+    t128x64 += rows * ((p.N + 63) / 64);
+    t128 += rows * ((p.N + 127) / 128);
+  }
+  const TileShape staged32{32, 32, 0}, tall{128, 64, 3, 2, 4}, wide{64, 128, 3, 2, 4};
+  std::vector<TileShape> want;
+  if (np == 2) {
+    if (t128x64 < kStreamCUs / 2) want = {staged32};
+    else want = {wn >= wm ? wide : tall};
+  } else if (np == 3) {
+    if (t128 >= 4 * kStreamCUs) want = {{128, 128, 3, 3, 8}};
+    want.push_back({64, 64, 3, 3, 4});
+  } else {
+    if (t128x64 >= 2 * kStreamCUs) want = {tall};
+    want.push_back({64, 64, 3, 2, 4});
+  }
+  const auto& shapes = gemm_planes_shapes(np);
+  for (const auto& w : want)
+    for (size_t i = 0; i < shapes.size(); ++i) {
+      const TileShape& sh = shapes[i];
+      if (sh.bm != w.bm || sh.bn != w.bn || sh.direct != w.direct || sh.stages != w.stages || sh.waves != w.waves)
+        continue;
+      auto it = st.streams_alt.find(np * 64 + (int)i);
+      if (sh.direct != 3 || (it != st.streams_alt.end() && it->second.ok)) return (int)i;
+    }
+  return kPlanesDefaultTile;
+}
+
 void finalize(PlanData& P) {
   P.blob.clear();
   P.coef_entries = 0;
@@ -1592,6 +1645,7 @@ void finalize(PlanData& P) {
               auto tl = make_tiles(st.probs_alt, st.segs_alt, sh.bm, sh.bn);
               st.tile_lists_alt[key] = {put(P.blob, tl), (int64_t)tl.size()};
             }
+            st.planes_default[np - 1] = planes_auto_tile(st, np);
           }
         }
         break;

@@ -87,6 +87,7 @@ struct Step {
   std::vector<GemmProb> probs_alt;   // problems of the plane variant (may merge blocks)
   std::vector<int64_t> rowmap;       // C row offsets of probs_alt with rowmap1 > 0
   std::vector<GemmSeg> segs_alt;     // indexed by probs_alt[].seg_begin
+  int planes_default[3] = {0, 0, 0}; // shape without a tuned choice, by plane count - 1
   std::vector<HTask> tasks_alt;
   std::vector<HPlane> planes_alt;
   // Split (float64 -> bfloat16 planes), run only by the split forms
@@ -191,6 +192,9 @@ bool step_runs(const PlanData& p, const Step& st, bst_precision prec, bool skip_
 bool fused_active(const PlanData& p, bst_precision prec);
 int planes_tile(const Step& st, bst_precision prec);
 int default_tile(const Step& st, bst_precision form);
+// LDS-staged 64x64: the fallback of the pipelined plane shapes (problems
+// outside their layout rules)
+constexpr int kPlanesDefaultTile = 0;
 void run_steps_impl(PlanData& p, void* ws, void* const* dptrs, bst_precision prec, hipStream_t s,
                     bool skip_const, int only_step,
                     std::vector<std::pair<hipEvent_t, hipEvent_t>>* ev);
