@@ -20,7 +20,7 @@ ARCH = "gfx950"
 SOURCES = ["structure.cpp", "plan.cpp", "exec.cpp", "lanczos.cpp", "kernels_gemm.hip", "kernels_aux.hip", "kernels_planes.hip",
            "kernels_direct.hip", "kernels_stream.hip", "network.cpp", "kernels_calib.hip",
            "svd.cpp", "kernels_svd.hip", "kernels_svd_reg.hip"]
-HEADERS = ["bst_internal.h", "plan.h", "svd.h", os.path.join("..", "..", "include", "bst.h")]
+HEADERS = ["bst_internal.h", "hcoef.h", "plan.h", "svd.h", os.path.join("..", "..", "include", "bst.h")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-function",
           "-Wno-unused-variable"]

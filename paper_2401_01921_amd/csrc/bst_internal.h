@@ -214,6 +214,20 @@ struct TileShape {
 // Tile shapes compiled for each arithmetic form.
 const std::vector<TileShape>& gemm_tile_shapes(bst_precision form);
 
+struct HCoefLaunch {
+  const HTerm* terms;
+  const int32_t* entry_begin;  // nentries + 1
+  int64_t nentries = 0;        // ncls * nmax * nmax
+  int nmax;
+  void* const* ptrs;
+  double* coef64;
+  float* coef32;
+  // compacted rows: cnt[ncls*nmax], idx / val[ncls*nmax*nmax]
+  int32_t* cnt;
+  int32_t* idx;
+  double* val64;
+  float* val32;
+};
 struct GemmLaunch {
   bst_precision form;
   ElemType ta, tb, tc;
@@ -224,6 +238,7 @@ struct GemmLaunch {
   const GemmSeg* segs;
   void* const* ptrs;
   int64_t ntiles;
+  HCoefLaunch coef{};          // float64 / float32 staged tiles: computed beside the GEMM
 };
 hipError_t launch_gemm(const GemmLaunch& g, hipStream_t s);
 hipError_t launch_gemm_direct(const GemmLaunch& g, int bm, int bn, hipStream_t s);
@@ -256,30 +271,18 @@ struct PermLaunch {
 };
 hipError_t launch_permute(const PermLaunch& p, hipStream_t s);
 
-struct HCoefLaunch {
-  const HTerm* terms;
-  const int32_t* entry_begin;  // nentries + 1
-  int64_t nentries;            // ncls * nmax * nmax
-  int nmax;
+// What an apply prepares before its first GEMM, in one launch: the splits of
+// its operands and the MPO coefficients.
+struct PrepLaunch {
+  int np = 0;
+  bool in_f32 = false;         // the blocks to split are float32 (a float32 Krylov row)
+  int nlists = 0;
+  const SplitItem* items[3];
+  int64_t count[3];
+  HCoefLaunch coef{};          // nentries = 0: none
   void* const* ptrs;
-  double* coef64;
-  float* coef32;
-  // compacted rows: cnt[ncls*nmax], idx / val[ncls*nmax*nmax]
-  int32_t* cnt;
-  int32_t* idx;
-  double* val64;
-  float* val32;
 };
-hipError_t launch_hcoef(const HCoefLaunch& c, hipStream_t s);
-
-struct SplitLaunch {
-  int np;
-  bool in_f32 = false;         // the input blocks are float32 (a float32 Krylov row)
-  const SplitItem* items;
-  void* const* ptrs;
-  int64_t nwork;
-};
-hipError_t launch_split(const SplitLaunch& l, hipStream_t s);
+hipError_t launch_prep(const PrepLaunch& l, hipStream_t s);
 
 // Grouped GEMM on pre-split bfloat16 planes (layout: plane_at): A [M x K]
 // and B [N x K], both with K contiguous, float32 accumulate.

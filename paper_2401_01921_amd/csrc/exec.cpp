@@ -115,21 +115,45 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
   const ElemType inter = (prec == BST_FP64) ? ElemType::F64 : ElemType::F32;
   const bool planes = uses_planes(P, prec);
   const int np = plane_count(prec);
+  // Splits and MPO coefficients read nothing but the inputs: they are collected
+  // and run as one launch, the coefficients alone beside the GEMM that follows.
+  // Steps that are timed one by one run one by one.
+  PrepLaunch prep;
+  prep.np = np;
+  prep.ptrs = dptrs;
+  auto flush = [&]() -> hipError_t {
+    const hipError_t e = launch_prep(prep, s);
+    prep.nlists = 0;
+    prep.in_f32 = false;
+    prep.coef = HCoefLaunch{};
+    return e;
+  };
+  const bool merge = !ev && only_step < 0;
   for (size_t k = 0; k < P.steps.size(); ++k) {
     if (only_step >= 0 && (int)k != only_step) continue;
     Step& st = P.steps[k];
     if (!step_runs(P, st, prec, skip_const)) continue;
     if (ev) check_hip(hipEventRecord((*ev)[k].first, s), "event");
     hipError_t e = hipSuccess;
+    if (st.kind != StepKind::Split && st.kind != StepKind::HCoef) {
+      bool beside = false;   // the coefficients go with this step's launch
+      if (prep.nlists == 0 && st.kind == StepKind::Gemm && !(planes && st.has_alt)) {
+        const bst_precision form = st.fixed_fp64 ? BST_FP64 : prec;
+        const TileShape& sh = gemm_tile_shapes(form)[default_tile(st, form)];
+        auto it = st.tile_lists.find({sh.bm, sh.bn});
+        beside = (form == BST_FP64 || form == BST_FP32) && sh.direct == 0 && it != st.tile_lists.end() &&
+                 it->second.second > 0;
+      }
+      if (!beside) check_hip(flush(), "preparation");
+    }
     switch (st.kind) {
       case StepKind::Split: {
-        SplitLaunch l{};
-        l.np = np;
-        l.in_f32 = st.reads_psi && P.psi_f32;
-        l.items = reinterpret_cast<const SplitItem*>(blob + st.off0);
-        l.ptrs = dptrs;
-        l.nwork = st.n0;
-        e = launch_split(l, s);
+        const bool f32 = st.reads_psi && P.psi_f32;
+        if (prep.nlists == 3 || (prep.nlists > 0 && f32 != prep.in_f32)) e = flush();
+        prep.in_f32 = f32;
+        prep.items[prep.nlists] = reinterpret_cast<const SplitItem*>(blob + st.off0);
+        prep.count[prep.nlists++] = st.n0;
+        if (!merge && e == hipSuccess) e = flush();
         break;
       }
       case StepKind::Gemm: {
@@ -187,6 +211,8 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.probs = reinterpret_cast<const GemmProb*>(blob + st.off0);
         g.segs = reinterpret_cast<const GemmSeg*>(blob + st.off1);
         g.ptrs = dptrs;
+        g.coef = prep.coef;
+        prep.coef = HCoefLaunch{};
         e = launch_gemm(g, s);
         break;
       }
@@ -203,7 +229,8 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         break;
       }
       case StepKind::HCoef: {
-        HCoefLaunch c{};
+        if (prep.coef.nentries > 0) e = flush();
+        HCoefLaunch& c = prep.coef;
         c.terms = reinterpret_cast<const HTerm*>(blob + st.off0);
         c.entry_begin = reinterpret_cast<const int32_t*>(blob + st.off1);
         c.nentries = st.n0;
@@ -215,7 +242,7 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         c.idx = reinterpret_cast<int32_t*>(wsb + P.ws_idx_off);
         c.val64 = reinterpret_cast<double*>(wsb + P.ws_val64_off);
         c.val32 = reinterpret_cast<float*>(wsb + P.ws_val32_off);
-        e = launch_hcoef(c, s);
+        if (!merge && e == hipSuccess) e = flush();
         break;
       }
       case StepKind::HApply: {
@@ -266,6 +293,7 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
     check_hip(e, st.name.c_str());
     if (ev) check_hip(hipEventRecord((*ev)[k].second, s), "event");
   }
+  check_hip(flush(), "preparation");
 }
 
 void run_steps(PlanData& P, void* ws, void* const* dptrs, bst_precision prec, hipStream_t s,

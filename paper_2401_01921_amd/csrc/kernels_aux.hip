@@ -170,64 +170,6 @@ hipError_t launch_permute(const PermLaunch& p, hipStream_t s) {
 // matrix h[o][i] = sum_w2 W1[w1,s1,t1,w2] W2[w2,s2,t2,w3] (Sec. "Benchmarks",
 // Fig. Hpsi_fig: the two W's form the two-site operator h).
 // ------------------------------------------------------------------------
-// Every entry of a coefficient row (class, output o) is the sum of its W1*W2
-// terms in a fixed order; the row is written dense (coef64/coef32) and
-// compacted to its nonzero entries in increasing input order (cnt, idx,
-// val64, val32) for the sparse apply.
-__global__ __launch_bounds__(256) void hcoef_kernel(const HTerm* __restrict__ terms,
-                                                    const int32_t* __restrict__ entry_begin,
-                                                    int64_t nentries, int nmax,
-                                                    void* const* __restrict__ ptrs,
-                                                    double* __restrict__ c64,
-                                                    float* __restrict__ c32,
-                                                    int32_t* __restrict__ cnt,
-                                                    int32_t* __restrict__ idx,
-                                                    double* __restrict__ v64,
-                                                    float* __restrict__ v32) {
-  // one lane per entry, then one lane per row compacts the row (nmax
-  // divides 256, so a workgroup holds whole rows)
-  __shared__ double cs[256];
-  const int tid = threadIdx.x;
-  const int64_t e = (int64_t)blockIdx.x * 256 + tid;
-  double sum = 0.0;
-  if (e < nentries) {
-    for (int32_t k = entry_begin[e]; k < entry_begin[e + 1]; ++k) {
-      const HTerm t = terms[k];
-      const double w1 = ((const BST_G double*)(ptrs[t.w1_buf]))[t.w1_off];
-      const double w2 = ((const BST_G double*)(ptrs[t.w2_buf]))[t.w2_off];
-      sum += w1 * w2;
-    }
-    c64[e] = sum;
-    c32[e] = (float)sum;
-  }
-  cs[tid] = sum;
-  __syncthreads();
-  const int rpb = 256 / nmax;
-  if (tid >= rpb) return;
-  const int64_t row = (int64_t)blockIdx.x * rpb + tid;
-  if (row * nmax >= nentries) return;
-  int32_t n = 0;
-  for (int i = 0; i < nmax; ++i) {
-    const double v = cs[tid * nmax + i];
-    if (v != 0.0) {
-      idx[row * nmax + n] = i;
-      v64[row * nmax + n] = v;
-      v32[row * nmax + n] = (float)v;
-      ++n;
-    }
-  }
-  cnt[row] = n;
-}
-
-hipError_t launch_hcoef(const HCoefLaunch& c, hipStream_t s) {
-  if (c.nentries <= 0) return hipSuccess;
-  if (c.nmax <= 0 || 256 % c.nmax != 0 || c.nentries % c.nmax != 0) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)((c.nentries + 255) / 256);
-  hipLaunchKernelGGL(hcoef_kernel, dim3(blocks), dim3(256), 0, s, c.terms, c.entry_begin, c.nentries,
-                     c.nmax, c.ptrs, c.coef64, c.coef32, c.cnt, c.idx, c.val64, c.val32);
-  return hipGetLastError();
-}
-
 // Sparse two-site MPO apply: each lane stages its site's nin inputs in LDS
 // (one column per lane, no bank conflicts) and runs only the nonzero terms
 // of its class.  The terms of an output are added in increasing input order,

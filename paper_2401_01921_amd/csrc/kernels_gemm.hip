@@ -15,7 +15,7 @@
 //   BF16X6  same with a2: a0b0+a0b1+a1b0+a0b2+a1b1+a2b0
 // Tiles: 4 waves (wave64) in a 2 x 2 arrangement, each wave a
 // (BM/2) x (BN/2) patch of 16 x 16 MFMA sub-tiles.
-#include "bst_internal.h"
+#include "hcoef.h"
 
 namespace bst {
 
@@ -268,7 +268,8 @@ template <int FORM, typename TA, typename TC, bool TRANSB, int BM, int BN, int D
 __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmTile* __restrict__ tiles,
                                                                      const GemmProb* __restrict__ probs,
                                                                      const GemmSeg* __restrict__ segs,
-                                                                     void* const* __restrict__ ptrs) {
+                                                                     void* const* __restrict__ ptrs, int hb,
+                                                                     HCoefLaunch coef) {
   constexpr bool F64 = (FORM == BST_FP64);
   constexpr int BK = 16, WM = BM / 2, WN = BN / 2, SM = WM / 16, SN = WN / 16;
   constexpr int EA = BM / 32, EB = BN / 32;               // pairs per lane and k-step
@@ -284,7 +285,13 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
   __shared__ __attribute__((aligned(16))) CT As[2][BM * LDK];
   __shared__ __attribute__((aligned(16))) CT Bs[2][TRANSB ? BN * LDK : BK * LDN];
 
-  const GemmTile t = tiles[blockIdx.x];
+  static_assert(sizeof(As) >= 256 * sizeof(double), "coefficient rows");
+  if ((int)blockIdx.x < hb) {   // the first hb workgroups: MPO coefficients
+    if ((int64_t)blockIdx.x * 256 < coef.nentries)
+      hcoef_block(coef, blockIdx.x, reinterpret_cast<double*>(&As[0][0]));
+    return;
+  }
+  const GemmTile t = tiles[blockIdx.x - hb];
   if (t.prob < 0) return;   // padding of the per-XCD tile lists
   const GemmProb p = probs[t.prob];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -493,12 +500,16 @@ constexpr int kBlockDepth = FORM == BST_FP64 || BM * BN <= 1024 ? 2 : 1;
 
 template <int FORM, typename TA, typename TC, bool TRANSB>
 static hipError_t launch_shape(int bm, int bn, const GemmLaunch& g, hipStream_t s) {
-  dim3 grid((unsigned)g.ntiles), block(256);
+  // (a multiple of the XCD count, which keeps the tiles' place on the XCDs)
+  const int64_t hb = (hcoef_blocks(g.coef) + 7) / 8 * 8;
+  if (!hcoef_valid(g.coef) || g.ntiles + hb > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (hb > 0 && FORM != BST_FP64 && FORM != BST_FP32) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(g.ntiles + hb)), block(256);
 #define BST_SHAPE(BM_, BN_)                                                                      \
   if (bm == BM_ && bn == BN_) {                                                                  \
     if constexpr (FORM == BST_FP64 || FORM == BST_FP32)                                          \
       hipLaunchKernelGGL((gemm_block_kernel<FORM, TA, TC, TRANSB, BM_, BN_, kBlockDepth<FORM, BM_, BN_>>), grid, block, 0, s, \
-                         g.tiles, g.probs, g.segs, g.ptrs);                                      \
+                         g.tiles, g.probs, g.segs, g.ptrs, (int)hb, g.coef);                     \
     else                                                                                         \
       hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, TRANSB, BM_, BN_>), grid, block, 0,   \
                          s, g.tiles, g.probs, g.segs, g.ptrs);                                   \
@@ -521,7 +532,7 @@ static hipError_t launch_form(const GemmLaunch& g, hipStream_t s) {
   const auto& shapes = gemm_tile_shapes((bst_precision)FORM);
   if (g.tile < 0 || g.tile >= (int)shapes.size()) return hipErrorInvalidValue;
   const int bm = shapes[g.tile].bm, bn = shapes[g.tile].bn;
-  if (shapes[g.tile].direct) return launch_gemm_direct(g, bm, bn, s);
+  if (shapes[g.tile].direct) return g.coef.nentries > 0 ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
   const bool a64 = g.ta == ElemType::F64, c64 = g.tc == ElemType::F64;
   if (g.tb != ElemType::F64) return hipErrorInvalidValue;
   if (a64 && c64) {
