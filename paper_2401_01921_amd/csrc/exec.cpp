@@ -95,6 +95,7 @@ bool step_runs(const PlanData& P, const Step& st, bst_precision prec, bool skip_
   if (skip_const && st.constant) return false;
   if (st.fusable && fused_active(P, prec)) return false;   // formed inside the fused MPO step
   if (st.kind == StepKind::Split && !uses_planes(P, prec)) return false;
+  if (st.kind == StepKind::Expand && reads_complex(P.steps.back(), prec)) return false;   // (its GEMM is the last)
   return true;
 }
 
@@ -209,7 +210,8 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.tiles = reinterpret_cast<const GemmTile*>(blob + it->second.first);
         g.ntiles = it->second.second;
         g.probs = reinterpret_cast<const GemmProb*>(blob + st.off0);
-        g.segs = reinterpret_cast<const GemmSeg*>(blob + st.off1);
+        g.b_complex = reads_complex(st, prec);
+        g.segs = reinterpret_cast<const GemmSeg*>(blob + (g.b_complex ? st.off4 : st.off1));
         g.ptrs = dptrs;
         g.coef = prep.coef;
         prep.coef = HCoefLaunch{};
@@ -610,6 +612,8 @@ bst_status bst_plan_autotune(bst_plan* p, const void* const* in, void* const* ou
       double best = 1e30;
       int best_i = pl ? planes_tile(st, form) : default_tile(st, f);
       for (size_t i = 0; i < shapes.size(); ++i) {
+        // a complex B is expanded only for the direct kernels, which costs as much as the GEMM
+        if (shapes[i].direct && !st.segs_cplx.empty()) continue;
         st.tile_choice[key] = (int)i;
         run_steps_impl(P, ws, table, P.prec, s, false, (int)k, nullptr);
         const double ms = time_runs((int)k);

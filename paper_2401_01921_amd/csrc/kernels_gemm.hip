@@ -236,6 +236,8 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_grouped_kernel(const Gem
       }
 }
 
+enum BLayout { kBPlain, kBTrans, kBComplex };   // [k][n], [n][k], complex [k / 2][n / 2]
+
 // float64 / float32 forms.
 //
 // The sectors of a block-sparse operand are small and odd (a chi = 2048 spin-1/2
@@ -259,18 +261,22 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_grouped_kernel(const Gem
 // order of the sum.  Rows are 18 doubles or 20 floats apart, so that the 16 rows
 // of a read lie in different banks; k-rows of a plain B likewise.
 //
+// A complex B needs no copy: rows 2 k and 2 k + 1 of the real form of its row k
+// are (re, im) pairs and (-im, re) pairs of the same elements (a chi = 1500
+// contraction: 20.3 us with the expanded copy made first, now 11.4).
+//
 // L.psi / T3.R, with one-element loads, a zero for each element outside, every
 // MFMA run and one register stage, then now: float64, spin-1/2 chi = 2048 (32 x 32)
 // 28.5 / 32.8 -> 26.6 / 29.1 us, spin-1 chi = 4096 (64 x 32) 201 / 198 -> 174 / 161
 // us; float32, chi = 4096 (64 x 64) 136 / 132 -> 109 / 102 us.  The MFMAs of the
 // chi = 4096 steps alone take 104 (float64).
-template <int FORM, typename TA, typename TC, bool TRANSB, int BM, int BN, int D>
+template <int FORM, typename TA, typename TC, int BL, int BM, int BN, int D>
 __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmTile* __restrict__ tiles,
                                                                      const GemmProb* __restrict__ probs,
                                                                      const GemmSeg* __restrict__ segs,
                                                                      void* const* __restrict__ ptrs, int hb,
                                                                      HCoefLaunch coef) {
-  constexpr bool F64 = (FORM == BST_FP64);
+  constexpr bool F64 = (FORM == BST_FP64), TRANSB = (BL == kBTrans), CPLX = (BL == kBComplex);
   constexpr int BK = 16, WM = BM / 2, WN = BN / 2, SM = WM / 16, SN = WN / 16;
   constexpr int EA = BM / 32, EB = BN / 32;               // pairs per lane and k-step
   constexpr int KB = 512 / BN;                            // k rows of B per load (not transposed)
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
       if constexpr (TRANSB)
         pb[e] = B + g.b_off + (int64_t)min(n0 + bn + 32 * e, p.N - 1) * g.ldb + bk;
       else
-        pb[e] = B + g.b_off + (int64_t)(bk + KB * e) * g.ldb + min(n0 + bn, p.N - 1);
+        pb[e] = B + g.b_off + (int64_t)((bk + KB * e) >> CPLX) * g.ldb + min(n0 + bn, p.N - 1);
     }
   };
   TA2 ra[D][EA];
@@ -362,7 +368,8 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
       const int c1 = n0 + bn + 1 < p.N ? 1 : 0;   // the column's neighbour or itself
 #pragma unroll
       for (int e = 0; e < EB; ++e) {
-        const BST_G double* const q = pb[e] + min(k - 1 - bk - KB * e, 0) * ldb;
+        const int kk = bk + KB * e;
+        const BST_G double* const q = pb[e] + ((min(k - 1, kk) >> CPLX) - (kk >> CPLX)) * ldb;
         b[e] = dbl2{q[0], q[c1]};
       }
     }
@@ -371,7 +378,7 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
 #pragma unroll
       for (int e = 0; e < EA; ++e) pa[e] += BK;
 #pragma unroll
-      for (int e = 0; e < EB; ++e) pb[e] += TRANSB ? BK : BK * ldb;
+      for (int e = 0; e < EB; ++e) pb[e] += TRANSB ? BK : (BK >> CPLX) * ldb;
     } else if (++ls < p.seg_count) {
       begin();
     }
@@ -387,6 +394,10 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
   };
   // (k past the segment is replaced here and not after the load, which would wait for it)
   auto stage = [&](int buf, TA2 (&a)[EA], dbl2 (&b)[EB], int k) {
+    if constexpr (CPLX) {   // KB and BK are even, so a lane's k are all even or all odd
+#pragma unroll
+      for (int e = 0; e < EB; ++e) b[e] = bk & 1 ? dbl2{-b[e].y, b[e].x} : b[e];
+    }
     if (k < BK) {
 #pragma unroll
       for (int e = 0; e < EA; ++e) a[e] = TA2{ak < k ? a[e].x : (TA)0, ak + 1 < k ? a[e].y : (TA)0};
@@ -498,7 +509,7 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
 template <int FORM, int BM, int BN>
 constexpr int kBlockDepth = FORM == BST_FP64 || BM * BN <= 1024 ? 2 : 1;
 
-template <int FORM, typename TA, typename TC, bool TRANSB>
+template <int FORM, typename TA, typename TC, int BL>
 static hipError_t launch_shape(int bm, int bn, const GemmLaunch& g, hipStream_t s) {
   // (a multiple of the XCD count, which keeps the tiles' place on the XCDs)
   const int64_t hb = (hcoef_blocks(g.coef) + 7) / 8 * 8;
@@ -508,10 +519,10 @@ static hipError_t launch_shape(int bm, int bn, const GemmLaunch& g, hipStream_t 
 #define BST_SHAPE(BM_, BN_)                                                                      \
   if (bm == BM_ && bn == BN_) {                                                                  \
     if constexpr (FORM == BST_FP64 || FORM == BST_FP32)                                          \
-      hipLaunchKernelGGL((gemm_block_kernel<FORM, TA, TC, TRANSB, BM_, BN_, kBlockDepth<FORM, BM_, BN_>>), grid, block, 0, s, \
+      hipLaunchKernelGGL((gemm_block_kernel<FORM, TA, TC, BL, BM_, BN_, kBlockDepth<FORM, BM_, BN_>>), grid, block, 0, s, \
                          g.tiles, g.probs, g.segs, g.ptrs, (int)hb, g.coef);                     \
     else                                                                                         \
-      hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, TRANSB, BM_, BN_>), grid, block, 0,   \
+      hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, BL == kBTrans, BM_, BN_>), grid, block, 0,   \
                          s, g.tiles, g.probs, g.segs, g.ptrs);                                   \
     return hipGetLastError();                                                                    \
   }
@@ -532,16 +543,20 @@ static hipError_t launch_form(const GemmLaunch& g, hipStream_t s) {
   const auto& shapes = gemm_tile_shapes((bst_precision)FORM);
   if (g.tile < 0 || g.tile >= (int)shapes.size()) return hipErrorInvalidValue;
   const int bm = shapes[g.tile].bm, bn = shapes[g.tile].bn;
-  if (shapes[g.tile].direct) return g.coef.nentries > 0 ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
+  if (shapes[g.tile].direct)
+    return g.coef.nentries > 0 || g.b_complex ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
   const bool a64 = g.ta == ElemType::F64, c64 = g.tc == ElemType::F64;
   if (g.tb != ElemType::F64) return hipErrorInvalidValue;
   if (a64 && c64) {
-    return g.transb ? launch_shape<FORM, double, double, true>(bm, bn, g, s)
-                    : launch_shape<FORM, double, double, false>(bm, bn, g, s);
+    if constexpr (FORM == BST_FP64 || FORM == BST_FP32)
+      if (g.b_complex) return launch_shape<FORM, double, double, kBComplex>(bm, bn, g, s);
+    if (g.b_complex) return hipErrorInvalidValue;
+    return g.transb ? launch_shape<FORM, double, double, kBTrans>(bm, bn, g, s)
+                    : launch_shape<FORM, double, double, kBPlain>(bm, bn, g, s);
   }
   if constexpr (FORM != BST_FP64) {
-    if (a64 && !c64 && !g.transb) return launch_shape<FORM, double, float, false>(bm, bn, g, s);
-    if (!a64 && c64 && g.transb) return launch_shape<FORM, float, double, true>(bm, bn, g, s);
+    if (a64 && !c64 && !g.transb) return launch_shape<FORM, double, float, kBPlain>(bm, bn, g, s);
+    if (!a64 && c64 && g.transb) return launch_shape<FORM, float, double, kBTrans>(bm, bn, g, s);
   }
   return hipErrorInvalidValue;
 }

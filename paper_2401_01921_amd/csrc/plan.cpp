@@ -427,11 +427,21 @@ static void contract_c128_plan(const TensorDesc& A, const TensorDesc& B, PlanDat
     for (int64_t st0 = 0; st0 < K * N; st0 += 4096) ex.xwork.push_back({jid, (int32_t)st0});
   }
   ex.bytes = ex.bytes32 = 16.0 * (double)Bp->numel + 32.0 * (double)Bp->numel;
-  pre.push_back(std::move(ex));
-  // the contraction now reads B' from its internal slot
-  for (auto& st : P.steps)
+  // the contraction now reads B' from its internal slot, or B itself
+  std::map<int64_t, int64_t> at;   // expanded block -> the complex one
+  for (const auto& j : ex.xjobs) at[j.out_off] = j.in_off;
+  for (auto& st : P.steps) {
+    if (st.kind != StepKind::Gemm) continue;
+    st.segs_cplx = st.segs;
+    for (auto& g : st.segs_cplx)
+      if (g.b_buf == 1) {
+        g.b_off = at.at(g.b_off);
+        g.b_buf = src;
+      }
     for (auto& g : st.segs)
       if (g.b_buf == 1) g.b_buf = xslot;
+  }
+  pre.push_back(std::move(ex));
   P.steps.insert(P.steps.begin(), std::make_move_iterator(pre.begin()), std::make_move_iterator(pre.end()));
   P.in_numel = {Ar->numel, 2 * B.numel};
   std::vector<LegDesc> cl(Cr->legs.begin(), Cr->legs.end() - 1);
@@ -1550,6 +1560,11 @@ int default_tile(const Step& st, bst_precision form) {
   return 0;
 }
 
+bool reads_complex(const Step& st, bst_precision prec) {
+  if (st.segs_cplx.empty() || (prec != BST_FP64 && prec != BST_FP32)) return false;
+  return gemm_tile_shapes(prec)[default_tile(st, prec)].direct == 0;
+}
+
 // Shape of a plane GEMM without a tuned choice.  All of them give the same
 // bits; what decides is whether the tiles fill the chip.  us on steps of H_eff,
 // chosen shape against the next best and against 256 x 128 or 128 x 256 (two
@@ -1612,6 +1627,7 @@ void finalize(PlanData& P) {
       case StepKind::Gemm: {
         st.off0 = put(P.blob, st.probs);
         st.off1 = put(P.blob, st.segs);
+        if (!st.segs_cplx.empty()) st.off4 = put(P.blob, st.segs_cplx);
         st.tile_lists.clear();
         st.tile_lists_alt.clear();
         st.tiles64x32 = st.tiles64x64 = 0;

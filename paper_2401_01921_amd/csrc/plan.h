@@ -55,6 +55,9 @@ struct Step {
   // Permute
   std::vector<PermJob> jobs;
   std::vector<PermWork> pwork;
+  // complex contraction: the segments on B itself; the expanded copy is made
+  // only for GEMM kernels that cannot read them
+  std::vector<GemmSeg> segs_cplx;
   // Expand (complex contraction)
   std::vector<ExpandJob> xjobs;
   std::vector<ExpandWork> xwork;
@@ -192,6 +195,9 @@ bool step_runs(const PlanData& p, const Step& st, bst_precision prec, bool skip_
 bool fused_active(const PlanData& p, bst_precision prec);
 int planes_tile(const Step& st, bst_precision prec);
 int default_tile(const Step& st, bst_precision form);
+// The GEMM of a complex contraction reads B itself in this form (staged
+// float64 / float32 tiles).
+bool reads_complex(const Step& st, bst_precision prec);
 // LDS-staged 64x64: the fallback of the pipelined plane shapes (problems
 // outside their layout rules)
 constexpr int kPlanesDefaultTile = 0;

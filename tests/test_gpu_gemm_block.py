@@ -47,3 +47,34 @@ def test_tile_edges(prec, b_order, rows, cols):
         first = got if first is None else first
         assert np.array_equal(got, first), plan.tiles()
     assert first is not None
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("b_order", [("k", "l", "j"), ("j", "l", "k")], ids=["B in place", "B packed"])
+@pytest.mark.parametrize("rows, cols", [((1, 17, 33), (1, 8, 33)), ((64, 65, 31), (16, 17, 31)), ((15, 129, 2), (65, 3, 32))])
+def test_complex_tile_edges(prec, b_order, rows, cols):
+    """A complex B read in place by the staged tiles (real columns 2 x cols), and
+    its expanded copy by the direct ones."""
+    i, j = (1, list(enumerate(rows))), (-1, list(enumerate(cols)))
+    k, l = (-1, [(0, 1), (1, 3), (2, 15)]), (-1, [(-1, 5), (0, 1), (1, 8)])   # real K of 2 to 240
+    rng = np.random.default_rng(12)
+    flip = {"j": j, "k": (1, k[1]), "l": (1, l[1])}
+    A = orc.BlockTensor(["i", "k", "l"], [i, k, l])
+    B = orc.BlockTensor(list(b_order), [flip[x] for x in b_order])
+    for T in (A, B):
+        T.data = rng.standard_normal(T.numel) + 1j * rng.standard_normal(T.numel)
+    C = orc.contract(A, B)
+    tC, plan = bst.contract_plan(bst.Tensor(A.labels, A.legs), bst.Tensor(B.labels, B.legs), prec, dtype="c128")
+    ins = [torch.view_as_real(torch.from_numpy(T.data).to(DEV)).reshape(-1) for T in (A, B)]
+    ws = bst.workspace(plan.workspace_bytes)
+    first = None
+    for tile in range(plan.tile_count(prec)):
+        plan.set_tile(prec, tile)
+        ws.fill_(255)          # an expanded copy that is read must be made by this run
+        out = torch.full((2 * tC.numel,), np.nan, dtype=torch.float64, device=DEV)
+        plan.execute(ins, [out], ws)
+        got = host(torch.view_as_complex(out.reshape(-1, 2)))
+        check(got, C.data, prec, plan.tiles())
+        if "l;" in plan.tiles():
+            first = got if first is None else first
+            assert np.array_equal(got, first), plan.tiles()
