@@ -149,6 +149,7 @@ struct PermJob {
 // A work item of the permute kernels: a tile (transposing jobs) or a row
 // range (jobs that keep the fastest dim).
 constexpr int kPermRows = 1024;   // most rows in one row-copy work item
+constexpr int kPermElems = 4096;  // and most elements, unless it is one longer row
 struct PermWork {
   int32_t job;
   int32_t kind;       // 0: rows; 1, 2, 3: a 64 x 64, 128 x 32 or 256 x 16 tile

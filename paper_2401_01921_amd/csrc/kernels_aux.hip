@@ -11,14 +11,18 @@ namespace bst {
 // ------------------------------------------------------------------------
 static_assert(kPermRows <= 256 * 17, "row offsets share the transpose tile's LDS");
 
-// Streaming 16-byte access when the address is 16-byte aligned, else two
-// 8-byte accesses (block offsets and strides may be odd).
+// Pairs move as one 16-byte access whatever the address: blocks and rows start at
+// odd elements, and two 8-byte accesses touch every line twice.
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 typedef double dbl2v __attribute__((ext_vector_type(2)));
 
 // One transposing tile of TY x TX elements (TY = 4096 / TX) over (pdim,
 // last): read as pairs of consecutive input columns, written as pairs of
 // consecutive output positions (input rows) through LDS rows padded by one
-// element.  Odd addresses fall back to 8-byte accesses.
+// element.  Bound by memory; 701 x 451 x 613 in seven sectors per leg, cab: 56.9
+// us with 8-byte accesses at odd addresses and a bounds check around each load,
+// 42.2 with 16-byte ones, 32.3 (5.3 TB/s) with a lane's eight loads all in
+// flight; bac (row copies): 70.9 -> 37.4 us.
 template <int TX>
 __device__ __forceinline__ void permute_tile(const PermJob& j, const PermWork& w, const BST_G double* __restrict__ in,
                                              BST_G double* __restrict__ out, double* lds) {
@@ -36,41 +40,38 @@ __device__ __forceinline__ void permute_tile(const PermJob& j, const PermWork& w
   }
   const int np = j.shape[p], nl = j.shape[r - 1];
   const int64_t isp = j.istride[p], osl = j.ostride[r - 1];
+  // all loads of a lane in flight before the first LDS store: rows and columns
+  // past the block read its last pair (no dim here has fewer than 2)
+  constexpr int G = 2048 / 256;
+  dbl2v v[G];
 #pragma unroll
-  for (int k = 0; k < 2048 / 256; ++k) {
+  for (int k = 0; k < G; ++k) {
+    const int e = tid + 256 * k;
+    const int gy = min(w.t0 + e / (TX / 2), np - 1), gx = min(w.t1 + 2 * (e % (TX / 2)), nl - 2);
+    v[k] = __builtin_nontemporal_load(reinterpret_cast<const BST_G dbl2u*>(in + ib + gy * isp + gx));
+  }
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
     const int e = tid + 256 * k;
     const int y = e / (TX / 2), x = 2 * (e % (TX / 2));
-    const int gy = w.t0 + y, gx = w.t1 + x;
-    if (gy < np && gx < nl) {
-      const BST_G double* src = in + ib + gy * isp + gx;
-      if (gx + 1 < nl && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-        const dbl2v v = __builtin_nontemporal_load(reinterpret_cast<const BST_G dbl2v*>(src));
-        lds[y * LD + x] = v.x;
-        lds[y * LD + x + 1] = v.y;
-      } else {
-        lds[y * LD + x] = src[0];
-        if (gx + 1 < nl) lds[y * LD + x + 1] = src[1];
-      }
-    }
+    lds[y * LD + x] = w.t1 + x == nl - 1 ? v[k].y : v[k].x;   // (a last odd column)
+    lds[y * LD + x + 1] = v[k].y;
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 2048 / 256; ++k) {
+  for (int k = 0; k < G; ++k) {
     const int e = tid + 256 * k;
     const int x = e / (TY / 2), y = 2 * (e % (TY / 2));
-    const int gy = w.t0 + y, gx = w.t1 + x;
-    if (gy < np && gx < nl) {
-      BST_G double* dst = out + ob + gy + gx * osl;
-      if (gy + 1 < np && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-        dbl2v v;
-        v.x = lds[y * LD + x];
-        v.y = lds[(y + 1) * LD + x];
-        __builtin_nontemporal_store(v, reinterpret_cast<BST_G dbl2v*>(dst));
-      } else {
-        dst[0] = lds[y * LD + x];
-        if (gy + 1 < np) dst[1] = lds[(y + 1) * LD + x];
-      }
-    }
+    v[k] = dbl2v{lds[y * LD + x], lds[(y + 1) * LD + x]};
+  }
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    const int e = tid + 256 * k;
+    const int gy = w.t0 + 2 * (e % (TY / 2)), gx = w.t1 + e / (TY / 2);
+    if (gy >= np || gx >= nl) continue;
+    BST_G double* dst = out + ob + gy + gx * osl;
+    if (gy + 1 < np) __builtin_nontemporal_store((dbl2u)v[k], reinterpret_cast<BST_G dbl2u*>(dst));
+    else dst[0] = v[k].x;
   }
 }
 
@@ -102,17 +103,30 @@ __global__ __launch_bounds__(256) void permute_kernel(const PermJob* __restrict_
       orow[q] = ob;
     }
     __syncthreads();
-    const int64_t npair = (last + 1) / 2;
-    for (int64_t e = tid; e < (int64_t)nrow * npair; e += 256) {
-      const int64_t q = e / npair, c = 2 * (e - q * npair);
-      const BST_G double* src = in + (w.batch + q) * last + c;
-      BST_G double* dst = out + orow[q] + c;
-      if (c + 1 < last && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
-        __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const BST_G dbl2v*>(src)),
-                                    reinterpret_cast<BST_G dbl2v*>(dst));
-      } else {
-        dst[0] = src[0];
-        if (c + 1 < last) dst[1] = src[1];
+    // kPermElems elements or one longer row; a lane's loads are all in flight
+    // before its first store
+    const BST_G double* const src0 = in + w.batch * last;
+    constexpr int G = 8;
+    const uint32_t npair = (uint32_t)((last + 1) / 2), n = (uint32_t)nrow * npair;
+    for (uint32_t e0 = tid; e0 < n; e0 += 256 * G) {
+      dbl2v v[G];
+      BST_G double* dst[G];
+      bool two[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const uint32_t e = min(e0 + 256 * g, n - 1), q = e / npair;
+        const uint32_t c = 2 * (e - q * npair);
+        const BST_G double* src = src0 + (uint64_t)q * last + c;
+        two[g] = c + 1 < last;
+        dst[g] = out + orow[q] + c;
+        if (two[g]) v[g] = __builtin_nontemporal_load(reinterpret_cast<const BST_G dbl2u*>(src));
+        else v[g].x = src[0];
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (e0 + 256 * g >= n) break;
+        if (two[g]) __builtin_nontemporal_store((dbl2u)v[g], reinterpret_cast<BST_G dbl2u*>(dst[g]));
+        else dst[g][0] = v[g].x;
       }
     }
     return;

@@ -90,7 +90,7 @@ static void add_permute_jobs(Step& st, const TensorDesc& in, const TensorDesc& o
       j.pdim = rr - 1;
       st.jobs.push_back(j);
       const int64_t rows = numel / last;
-      int64_t per = std::max<int64_t>(1, 8192 / last);
+      int64_t per = std::max<int64_t>(1, kPermElems / last);
       per = std::min<int64_t>(per, kPermRows);
       for (int64_t r0 = 0; r0 < rows; r0 += per) {
         PermWork w{};
