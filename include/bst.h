@@ -120,6 +120,11 @@ bst_status bst_tensor_create(int32_t rank, const int32_t* dir, const int32_t* ns
 bst_status bst_tensor_create_sym(int32_t rank, const int32_t* dir, const int32_t* nsec,
                                  int32_t nsym, const int32_t* sym, const int32_t* qn,
                                  const int64_t* dim, const char* const* labels, bst_tensor** out);
+/* A copy of t's descriptor under new labels ([rank], unique), all directions
+ * reversed if reverse is non-zero (the conjugate's legs): the same blocks, order
+ * and layout.  Errors: BST_E_INVALID, BST_E_LABEL. */
+bst_status bst_tensor_relabel(const bst_tensor* t, const char* const* labels, int32_t reverse,
+                              bst_tensor** out);
 bst_status bst_tensor_destroy(bst_tensor* t);
 
 /* The symmetries of a tensor: their number, and (if moduli is non-null) the

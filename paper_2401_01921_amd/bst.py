@@ -36,7 +36,7 @@ EXPORTS = [
     "bst_network_order", "bst_plan_record_tiles", "bst_execute_static", "bst_calib_grid", "bst_calib_copy", "bst_calib_read", "bst_calib_mfma",
     "bst_svd_plan", "bst_svd_info", "bst_svd_sector", "bst_svd_execute", "bst_svd_truncate",
     "bst_svd_factors", "bst_svd_write", "bst_svd_sweeps", "bst_svd_forget_workspace", "bst_svd_destroy",
-    "bst_permute_plan_c128", "bst_contract_plan_c128",
+    "bst_permute_plan_c128", "bst_contract_plan_c128", "bst_tensor_relabel",
 ]
 
 
@@ -82,6 +82,7 @@ def _load():
         "bst_tensor_create_sym": [i32, P(i32), P(i32), i32, P(i32), P(i32), P(i64), P(C.c_char_p),
                                   P(vp)],
         "bst_tensor_symmetry": [vp, P(i32), P(i32), i32],
+        "bst_tensor_relabel": [vp, P(C.c_char_p), i32, P(vp)],
         "bst_tensor_leg_charges": [vp, i32, P(i32)],
         "bst_network_order": [i32, P(i32), P(i32), i32, P(i64), P(i32), P(C.c_double)],
         "bst_tensor_destroy": [vp],
@@ -231,6 +232,16 @@ class Tensor:
     def labels(self) -> List[str]:
         return self.legs()[0]
 
+    def relabeled(self, labels: Sequence[str] | None = None, reverse: bool = False) -> "Tensor":
+        """The same legs under new labels, all directions reversed if asked."""
+        labels = self.labels if labels is None else labels
+        if len(labels) != self.rank:
+            raise BstError(1, "one label per leg")
+        labs = (C.c_char_p * max(self.rank, 1))(*[l.encode() for l in labels])
+        h = C.c_void_p()
+        _check(_lib.bst_tensor_relabel(self._h, labs, int(reverse), C.byref(h)))
+        return Tensor(None, None, _handle=h)
+
     def symmetry(self) -> List[int]:
         """Moduli of the symmetries (0 = U(1))."""
         n = C.c_int32()
@@ -376,6 +387,31 @@ class Plan:
         return buf.value.decode()
 
     def _arrays(self, ins, outs):
+        a = self._pointers(ins, self.n_in, self.in_numel)
+        b = self._pointers(outs, self.n_out, self.out_numel)
+        return (a, b) if a is not None and b is not None else self._arrays_checked(ins, outs)
+
+    @staticmethod
+    def _pointers(bufs, n, numels):
+        """The buffers' addresses, None if one is not what the plan takes."""
+        import torch
+        if len(bufs) != n:
+            return None
+        out = (C.c_void_p * max(n, 1))()
+        for k, t in enumerate(bufs):
+            if not isinstance(t, torch.Tensor) or t.dtype is not torch.float64:
+                return None
+            m = t.numel()
+            if numels is not None and numels[k] is not None and numels[k] != m:
+                return None
+            if m:
+                if not t.is_cuda or not t.is_contiguous():
+                    return None
+                out[k] = t.data_ptr()
+        return out
+
+    def _arrays_checked(self, ins, outs):
+        """_arrays with a message for what is wrong."""
         if len(ins) != self.n_in or len(outs) != self.n_out:
             raise BstError(1, f"plan takes {self.n_in} inputs and {self.n_out} outputs")
         import torch

@@ -74,7 +74,6 @@ struct TensorDesc {
   std::vector<int32_t> qn;      // nblocks * rank sector indices
   std::vector<int64_t> shape;   // nblocks * rank
   std::vector<int64_t> offset;  // nblocks
-  std::unordered_map<std::string, int64_t> lookup;
 
   int rank() const { return (int)legs.size(); }
   // Enumerates the valid blocks in canonical order (called once by create).
@@ -92,6 +91,7 @@ struct TensorDesc {
 };
 
 std::unique_ptr<TensorDesc> make_tensor(std::vector<LegDesc> legs);
+void check_labels(const std::vector<LegDesc>& legs);
 
 // ------------------------------------------------------------------------
 // Device records

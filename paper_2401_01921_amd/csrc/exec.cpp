@@ -43,6 +43,50 @@ void* upload_table(PlanData& P, const std::vector<void*>& ptrs, void* ws, size_t
   return table;
 }
 
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  check_hip(hipStreamIsCapturing(s, &cap), "capture state");
+  return cap != hipStreamCaptureStatusNone;
+}
+
+void upload_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  if (bytes == 0) return;
+  check_hip(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s), "table upload");
+  check_hip(hipStreamSynchronize(s), "table upload");
+}
+
+void upload_blob(PlanData& P, void* ws, hipStream_t s) {
+  if (P.blob_uploaded >= P.blob.size()) return;
+  char* dst = static_cast<char*>(ws) + P.ws_blob_off + P.blob_uploaded;
+  const uint8_t* src = P.blob.data() + P.blob_uploaded;
+  const size_t bytes = P.blob.size() - P.blob_uploaded;
+  // a list first used under a capture (the form was changed since the last
+  // call) is written by the graph itself, through kernel arguments, and counts
+  // as absent outside it (outside captures these are no faster than a copy)
+  if (P.blob_uploaded > 0 && capturing(s)) {
+    std::vector<void*> words((bytes + 7) / 8, nullptr);
+    std::memcpy(words.data(), src, bytes);
+    check_hip(launch_set_ptrs(reinterpret_cast<void**>(dst), words.data(), (int)words.size(), s), "table upload");
+    return;
+  }
+  upload_bytes(dst, src, bytes, s);
+  P.blob_uploaded = P.blob.size();
+}
+
+// The shape whose tile list a GEMM step runs on, null if it runs on a k-step
+// schedule instead.
+static const TileShape* list_shape(const PlanData& P, const Step& st, bst_precision prec) {
+  if (uses_planes(P, prec) && st.has_alt) {
+    const int np = plane_count(prec), t = planes_tile(st, prec);
+    const auto& shapes = gemm_planes_shapes(np);
+    if (shapes[t].direct != 3) return &shapes[t];
+    auto it = st.streams_alt.find(np * 64 + t);
+    return it != st.streams_alt.end() && it->second.ok ? nullptr : &shapes[kPlanesDefaultTile];
+  }
+  const bst_precision form = st.fixed_fp64 ? BST_FP64 : prec;
+  return &gemm_tile_shapes(form)[default_tile(st, form)];
+}
+
 void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws, hipStream_t s) {
   if (!ws) fail(BST_E_INVALID, "null workspace");
   if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) fail(BST_E_INVALID, "workspace must be 256-byte aligned");
@@ -53,13 +97,15 @@ void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws,
     auto it = g_ws_owner.find(ws);
     need_blob = (it == g_ws_owner.end() || it->second != P.id || P.uploaded_ws != ws);
   }
+  // tile lists this run needs, so that one upload takes them all
+  for (auto& st : P.steps) {
+    if (st.kind != StepKind::Gemm || !step_runs(P, st, P.prec, false)) continue;
+    const TileShape* sh = list_shape(P, st, P.prec);
+    if (sh) tile_list(P, st, uses_planes(P, P.prec) && st.has_alt, sh->bm, sh->bn);
+  }
   if (need_blob) {
-    if (!P.blob.empty()) {
-      check_hip(hipMemcpyAsync(static_cast<char*>(ws) + P.ws_blob_off, P.blob.data(), P.blob.size(),
-                               hipMemcpyHostToDevice, s),
-                "plan table upload");
-      check_hip(hipStreamSynchronize(s), "plan table upload");
-    }
+    P.blob_uploaded = 0;
+    upload_blob(P, ws, s);
     std::lock_guard<std::mutex> lk(g_ws_mu);
     g_ws_owner[ws] = P.id;
     P.uploaded_ws = ws;
@@ -141,9 +187,7 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
       if (prep.nlists == 0 && st.kind == StepKind::Gemm && !(planes && st.has_alt)) {
         const bst_precision form = st.fixed_fp64 ? BST_FP64 : prec;
         const TileShape& sh = gemm_tile_shapes(form)[default_tile(st, form)];
-        auto it = st.tile_lists.find({sh.bm, sh.bn});
-        beside = (form == BST_FP64 || form == BST_FP32) && sh.direct == 0 && it != st.tile_lists.end() &&
-                 it->second.second > 0;
+        beside = (form == BST_FP64 || form == BST_FP32) && sh.direct == 0 && !st.probs.empty();
       }
       if (!beside) check_hip(flush(), "preparation");
     }
@@ -184,10 +228,10 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
             g.tile = kPlanesDefaultTile;   // problems outside the kernel's layout rules
           }
           const auto& sh = gemm_planes_shapes(np)[g.tile];
-          auto it = st.tile_lists_alt.find({sh.bm, sh.bn});
-          if (it == st.tile_lists_alt.end()) fail(BST_E_INVALID, "internal: missing tile list");
-          g.tiles = reinterpret_cast<const GemmTile*>(blob + it->second.first);
-          g.ntiles = it->second.second;
+          const auto list = tile_list(P, st, true, sh.bm, sh.bn);
+          upload_blob(P, ws, s);
+          g.tiles = reinterpret_cast<const GemmTile*>(blob + list.first);
+          g.ntiles = list.second;
           g.probs = reinterpret_cast<const GemmProb*>(blob + st.off3);
           g.segs = reinterpret_cast<const GemmSeg*>(blob + st.off2);
           g.rowmap = reinterpret_cast<const int64_t*>(blob + st.off5);
@@ -205,10 +249,10 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.transb = st.transb;
         g.tile = default_tile(st, form);
         const auto& sh = gemm_tile_shapes(form)[g.tile];
-        auto it = st.tile_lists.find({sh.bm, sh.bn});
-        if (it == st.tile_lists.end()) fail(BST_E_INVALID, "internal: missing tile list");
-        g.tiles = reinterpret_cast<const GemmTile*>(blob + it->second.first);
-        g.ntiles = it->second.second;
+        const auto list = tile_list(P, st, false, sh.bm, sh.bn);
+        upload_blob(P, ws, s);
+        g.tiles = reinterpret_cast<const GemmTile*>(blob + list.first);
+        g.ntiles = list.second;
         g.probs = reinterpret_cast<const GemmProb*>(blob + st.off0);
         g.b_complex = reads_complex(st, prec);
         g.segs = reinterpret_cast<const GemmSeg*>(blob + (g.b_complex ? st.off4 : st.off1));

@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <set>
 #include <numeric>
 
 namespace bst {
@@ -1233,49 +1234,81 @@ static int round_nmax(int n) {
 //
 // Workgroups go to the 8 XCDs round-robin by linear id, and each XCD has its
 // own L2.  The tiles of one problem share their A row panels and B column
-// panels, so whole problems are bin-packed onto XCDs (largest cost first,
-// each to the least loaded XCD), each XCD's tiles are ordered by cost with a
-// problem's tiles kept together, and the eight lists are interleaved so that
-// linear id 8*pos + x is tile pos of XCD x.  Short lists are padded with
-// empty tiles (prob = -1) that exit at once.
+// panels, so problems are bin-packed onto XCDs (largest cost first, each to the
+// least loaded XCD) and the eight lists are interleaved so that linear id
+// 8*pos + x is tile pos of XCD x.  A problem with more than 1/32 of all tiles
+// goes in runs of that many (a single block would otherwise stay on one XCD).
+// Short lists are padded with empty tiles (prob = -1) that exit at once; no list
+// is longer than 1.5 times an even share and one run, which bounds the space
+// (tile_list_cap) before a list is built.
 constexpr int kXcds = 8;
+
+static int64_t tile_total(const std::vector<GemmProb>& probs, int bm, int bn) {
+  int64_t n = 0;
+  for (const auto& p : probs) n += (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+  return n;
+}
+static int64_t tile_run(int64_t total) { return std::max<int64_t>(1, (total + 31) / 32); }
+static int64_t tile_list_cap(int64_t total) { return total * 3 / 2 / kXcds + tile_run(total) + 1; }
 
 static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
                                         const std::vector<GemmSeg>& segs, int bm, int bn) {
-  struct Prob {
+  const int64_t total = tile_total(probs, bm, bn), run = tile_run(total), cap = tile_list_cap(total);
+  struct Run {
     double cost;
-    int32_t idx;
+    int32_t prob;
+    int64_t first, count;
   };
-  std::vector<Prob> pr;
+  std::vector<Run> runs;
+  runs.reserve(probs.size() + 32);
   for (size_t pi = 0; pi < probs.size(); ++pi) {
     const auto& p = probs[pi];
     int64_t k = 0;
     for (int s = 0; s < p.seg_count; ++s) k += segs[p.seg_begin + s].K;
-    const double ntile = (double)((p.M + bm - 1) / bm) * (double)((p.N + bn - 1) / bn);
-    pr.push_back({ntile * (double)(k + 16), (int32_t)pi});
+    const int64_t nt = (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+    const int64_t parts = (nt + run - 1) / run;
+    for (int64_t q = 0; q < parts; ++q) {
+      const int64_t t0 = nt * q / parts, t1 = nt * (q + 1) / parts;
+      runs.push_back({(double)(t1 - t0) * (double)(k + 16), (int32_t)pi, t0, t1 - t0});
+    }
   }
-  std::stable_sort(pr.begin(), pr.end(), [](const Prob& a, const Prob& b) { return a.cost > b.cost; });
-  std::vector<std::vector<GemmTile>> bins(kXcds);
-  std::vector<double> load(kXcds, 0.0);
-  for (const auto& q : pr) {
-    int x = 0;
-    for (int i = 1; i < kXcds; ++i)
-      if (load[i] < load[x]) x = i;
-    load[x] += q.cost;
-    const auto& p = probs[q.idx];
-    for (int m0 = 0; m0 < p.M; m0 += bm)
-      for (int n0 = 0; n0 < p.N; n0 += bn) bins[x].push_back({q.idx, m0, n0, 0});
-  }
-  size_t longest = 0;
-  for (auto& b : bins) longest = std::max(longest, b.size());
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
+  int64_t count[kXcds] = {};
+  double load[kXcds] = {};
   std::vector<GemmTile> out;
-  out.reserve(longest * kXcds);
-  for (size_t pos = 0; pos < longest; ++pos)
-    for (int x = 0; x < kXcds; ++x)
-      out.push_back(pos < bins[x].size() ? bins[x][pos] : GemmTile{-1, 0, 0, 0});
-  // drop trailing empty tiles
-  while (!out.empty() && out.back().prob < 0) out.pop_back();
+  out.reserve((size_t)(total + total / 4));
+  for (const auto& q : runs) {
+    int x = -1;
+    for (int i = 0; i < kXcds; ++i)
+      if (count[i] + q.count <= cap && (x < 0 || load[i] < load[x])) x = i;
+    load[x] += q.cost;
+    const auto& p = probs[q.prob];
+    const int64_t nn = (p.N + bn - 1) / bn, last = kXcds * (count[x] + q.count - 1) + x;
+    if ((int64_t)out.size() <= last) out.resize((size_t)last + 1, GemmTile{-1, 0, 0, 0});
+    int64_t m = q.first / nn, n = q.first % nn;
+    for (int64_t e = 0; e < q.count; ++e) {
+      out[(size_t)(kXcds * (count[x] + e) + x)] = {q.prob, (int32_t)(m * bm), (int32_t)(n * bn), 0};
+      if (++n == nn) {
+        n = 0;
+        ++m;
+      }
+    }
+    count[x] += q.count;
+  }
   return out;
+}
+
+std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn) {
+  auto& lists = alt ? st.tile_lists_alt : st.tile_lists;
+  auto it = lists.find({bm, bn});
+  if (it == lists.end()) {
+    const auto tl = make_tiles(alt ? st.probs_alt : st.probs, alt ? st.segs_alt : st.segs, bm, bn);
+    const size_t off = put(P.blob, tl);
+    P.blob.resize(align256(P.blob.size()));
+    if (P.ws_blob_off + P.blob.size() > P.ws_coef64_off) fail(BST_E_INVALID, "internal: tile lists outgrow their space");
+    it = lists.emplace(std::make_pair(bm, bn), std::make_pair(off, (int64_t)tl.size())).first;
+  }
+  return it->second;
 }
 
 // k-step schedule of the pipelined plane kernel for one tile shape.  The
@@ -1620,6 +1653,10 @@ static int planes_auto_tile(const Step& st, int np) {
 
 void finalize(PlanData& P) {
   P.blob.clear();
+  size_t reserve = 0;
+  auto list_bytes = [](const std::vector<GemmProb>& probs, int bm, int bn) {
+    return align256((size_t)(kXcds * tile_list_cap(tile_total(probs, bm, bn))) * sizeof(GemmTile));
+  };
   P.coef_entries = 0;
   P.fused_ok = false;
   for (auto& st : P.steps) {
@@ -1636,18 +1673,21 @@ void finalize(PlanData& P) {
           st.tiles64x32 += rows * ((p.N + 31) / 32);
           st.tiles64x64 += rows * ((p.N + 63) / 64);
         }
-        for (int f = 0; f < 4; ++f)
-          for (const auto& sh : gemm_tile_shapes((bst_precision)f)) {
-            auto key = std::make_pair(sh.bm, sh.bn);
-            if (st.tile_lists.count(key)) continue;
-            auto tl = make_tiles(st.probs, st.segs, sh.bm, sh.bn);
-            st.tile_lists[key] = {put(P.blob, tl), (int64_t)tl.size()};
-          }
+        // space for every tile list; each is built on first use (an MPO
+        // contraction has thousands of tiles, six lists of them took longer to
+        // build and upload than everything else)
+        {
+          std::set<std::pair<int, int>> shapes;
+          for (int f = 0; f < 4; ++f)
+            for (const auto& sh : gemm_tile_shapes((bst_precision)f)) shapes.insert({sh.bm, sh.bn});
+          for (const auto& b : shapes) reserve += list_bytes(st.probs, b.first, b.second);
+        }
         if (st.has_alt) {
           st.off2 = put(P.blob, st.segs_alt);
           st.off3 = put(P.blob, st.probs_alt);
           st.off5 = put(P.blob, st.rowmap);
           st.streams_alt.clear();
+          std::set<std::pair<int, int>> shapes_alt;
           for (int np = 1; np <= 3; ++np) {
             const auto& shapes = gemm_planes_shapes(np);
             for (size_t i = 0; i < shapes.size(); ++i) {
@@ -1656,13 +1696,11 @@ void finalize(PlanData& P) {
                 st.streams_alt[np * 64 + (int)i] = make_stream(P.blob, st, np, sh);
                 continue;
               }
-              auto key = std::make_pair(sh.bm, sh.bn);
-              if (st.tile_lists_alt.count(key)) continue;
-              auto tl = make_tiles(st.probs_alt, st.segs_alt, sh.bm, sh.bn);
-              st.tile_lists_alt[key] = {put(P.blob, tl), (int64_t)tl.size()};
+              shapes_alt.insert({sh.bm, sh.bn});
             }
             st.planes_default[np - 1] = planes_auto_tile(st, np);
           }
+          for (const auto& b : shapes_alt) reserve += list_bytes(st.probs_alt, b.first, b.second);
         }
         break;
       }
@@ -1802,7 +1840,8 @@ void finalize(PlanData& P) {
   P.ws_ptr_off = off;
   off = align256(off + sizeof(void*) * (size_t)std::max(P.nslots, 1));
   P.ws_blob_off = off;
-  off = align256(off + P.blob.size());
+  P.blob.resize(align256(P.blob.size()));
+  off = align256(off + P.blob.size() + reserve);
   P.ws_coef64_off = off;
   off = align256(off + sizeof(double) * (size_t)std::max(P.coef_entries, 1));
   P.ws_coef32_off = off;
@@ -2018,8 +2057,7 @@ bst_status bst_plan_info(const bst_plan* p, bst_plan_stats* st) {
       st->gemm_problems += (int64_t)s.probs.size();
       const int t = default_tile(s, P.prec);
       const auto& sh = gemm_tile_shapes(P.prec)[t];
-      auto it = s.tile_lists.find({sh.bm, sh.bn});
-      if (it != s.tile_lists.end()) st->gemm_tiles += it->second.second;
+      st->gemm_tiles += (int64_t)make_tiles(s.probs, s.segs, sh.bm, sh.bn).size();
     }
   }
   st->launches = (int64_t)P.steps.size();
@@ -2041,8 +2079,7 @@ bst_status bst_plan_step_info(const bst_plan* p, int32_t step, bst_step_info* in
   if (s.kind == StepKind::Gemm) {
     const int t = default_tile(s, P.prec);
     const auto& sh = gemm_tile_shapes(P.prec)[t];
-    auto it = s.tile_lists.find({sh.bm, sh.bn});
-    info->items = it == s.tile_lists.end() ? 0 : it->second.second;
+    info->items = (int64_t)make_tiles(s.probs, s.segs, sh.bm, sh.bn).size();
   } else {
     info->items = s.n0;
   }

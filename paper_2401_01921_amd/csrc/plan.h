@@ -151,7 +151,8 @@ struct PlanData {
   bool fused_on = false;             // run it (autotuner choice, BST_FUSED_MPO overrides)
   bool sparse_mpo = true;       // MPO apply runs only the nonzero h entries
   // finalize
-  std::vector<uint8_t> blob;
+  std::vector<uint8_t> blob;     // tables; tile lists are appended when first used
+  size_t blob_uploaded = 0;      // bytes of it in uploaded_ws
   size_t ws_ptr_off = 0, ws_blob_off = 0, ws_coef64_off = 0, ws_coef32_off = 0, ws_bytes = 0;
   size_t ws_cnt_off = 0, ws_idx_off = 0, ws_val64_off = 0, ws_val32_off = 0;
   int32_t coef_entries = 0;
@@ -170,6 +171,13 @@ struct PlanData {
 };
 
 void finalize(PlanData& p);
+// A GEMM step's tile list for one shape (offset in the blob, entries), built on
+// first use; alt: of the plane variant.
+std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn);
+// Puts blob bytes that ws does not hold yet there.
+void upload_blob(PlanData& P, void* ws, hipStream_t s);
+// Host bytes to device memory by a copy that is waited for.
+void upload_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);
 // Uploads tables (if this plan's tables are not in ws yet) and the pointer
 // table built from in / out; returns the device address of the pointer table.
 void* prepare_ws(PlanData& p, const void* const* in, void* const* out, void* ws, hipStream_t s);

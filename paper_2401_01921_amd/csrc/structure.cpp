@@ -22,16 +22,11 @@ void check_hip(hipError_t e, const char* what) {
   if (e != hipSuccess) fail(BST_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-static std::string key_of(const int32_t* t, int rank) {
-  return std::string(reinterpret_cast<const char*>(t), sizeof(int32_t) * (size_t)rank);
-}
-
 void TensorDesc::build() {
   const int r = rank();
   qn.clear();
   shape.clear();
   offset.clear();
-  lookup.clear();
   // Per-suffix reachable flux range of the first charge component, to prune
   // the lexicographic walk (U(1) only; a Z_n flux wraps, so no pruning).
   const int nsym = r > 0 ? legs[0].nsym() : 1;
@@ -58,7 +53,6 @@ void TensorDesc::build() {
   int depth = 0;
   if (r == 0) {
     offset.push_back(0);
-    lookup[key_of(t.data(), 0)] = 0;
     nblocks = 1;
     numel = 1;
     return;
@@ -82,7 +76,6 @@ void TensorDesc::build() {
         ok = vanishes(fc, legs[0].modulus(c));
       }
       if (!ok) continue;
-      int64_t b = (int64_t)offset.size();
       int64_t n = 1;
       for (int i = 0; i < r; ++i) {
         qn.push_back(t[i]);
@@ -90,7 +83,6 @@ void TensorDesc::build() {
         n *= legs[i].g[t[i]];
       }
       offset.push_back(off);
-      lookup[key_of(t.data(), r)] = b;
       off += n;
       continue;
     }
@@ -103,14 +95,35 @@ void TensorDesc::build() {
 }
 
 int64_t TensorDesc::find(const int32_t* t) const {
-  auto it = lookup.find(key_of(t, rank()));
-  return it == lookup.end() ? -1 : it->second;
+  // the blocks are in lexicographic order of their tuples (a hash map from
+  // tuples took most of the time of building a descriptor)
+  const int r = rank();
+  int64_t lo = 0, n = nblocks;
+  while (n > 0) {
+    const int64_t half = n / 2;
+    const int32_t* m = block_qn(lo + half);
+    if (std::lexicographical_compare(m, m + r, t, t + r)) {
+      lo += half + 1;
+      n -= half + 1;
+    } else {
+      n = half;
+    }
+  }
+  return lo < nblocks && std::equal(t, t + r, block_qn(lo)) ? lo : -1;
 }
 
 int TensorDesc::label_index(const std::string& l) const {
   for (int i = 0; i < rank(); ++i)
     if (legs[i].label == l) return i;
   return -1;
+}
+
+void check_labels(const std::vector<LegDesc>& legs) {
+  for (size_t i = 0; i < legs.size(); ++i) {
+    if (legs[i].label.empty()) fail(BST_E_LABEL, "empty label");
+    for (size_t j = 0; j < i; ++j)
+      if (legs[j].label == legs[i].label) fail(BST_E_LABEL, "duplicate label '" + legs[i].label + "'");
+  }
 }
 
 std::unique_ptr<TensorDesc> make_tensor(std::vector<LegDesc> legs) {
@@ -133,10 +146,8 @@ std::unique_ptr<TensorDesc> make_tensor(std::vector<LegDesc> legs) {
     }
     for (auto g : L.g)
       if (g < 1 || g > (int64_t)1 << 30) fail(BST_E_INVALID, "sector dim must be in [1, 2^30]");
-    if (L.label.empty()) fail(BST_E_LABEL, "empty label");
-    for (size_t j = 0; j < i; ++j)
-      if (legs[j].label == L.label) fail(BST_E_LABEL, "duplicate label '" + L.label + "'");
   }
+  check_labels(legs);
   auto t = std::make_unique<TensorDesc>();
   t->legs = std::move(legs);
   t->build();
@@ -237,6 +248,21 @@ bst_status bst_tensor_leg_charges(const bst_tensor* t, int32_t leg, int32_t* qn)
   const int n = L.nsym();
   for (size_t s = 0; s < L.q.size(); ++s)
     for (int c = 0; c < n; ++c) qn[s * n + c] = L.charge((int)s, c);
+  BST_CATCH
+}
+
+bst_status bst_tensor_relabel(const bst_tensor* t, const char* const* labels, int32_t reverse, bst_tensor** out) {
+  BST_TRY
+  if (!t || !out) fail(BST_E_INVALID, "null argument");
+  auto d = std::make_unique<TensorDesc>(*t->d);
+  if (d->rank() > 0 && !labels) fail(BST_E_INVALID, "null argument");
+  for (int i = 0; i < d->rank(); ++i) {
+    if (!labels[i]) fail(BST_E_LABEL, "null label");
+    d->legs[i].label = labels[i];
+    if (reverse) d->legs[i].dir = -d->legs[i].dir;   // every flux changes sign: the same blocks
+  }
+  check_labels(d->legs);
+  *out = wrap_tensor(std::move(d));
   BST_CATCH
 }
 

@@ -321,8 +321,7 @@ void build(SvdPlanData& P) {
 void upload(SvdPlanData& P, void* ws, hipStream_t s) {
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255)) fail(BST_E_INVALID, "workspace must be non-null and 256-byte aligned");
   if (P.uploaded == ws) return;
-  check_hip(hipMemcpyAsync(ws, P.blob.data(), P.blob.size(), hipMemcpyHostToDevice, s), "svd tables");
-  check_hip(hipStreamSynchronize(s), "svd tables");
+  upload_bytes(ws, P.blob.data(), P.blob.size(), s);
   P.uploaded = ws;
 }
 
@@ -506,14 +505,16 @@ bst_status bst_svd_truncate(bst_svd* p, int64_t keepdim, double err, const int64
   l.kept = at<int64_t>(ws, P.ws_kept);
   l.s_err = at<double>(ws, P.ws_serr);
   if (ns > 0) check_hip(launch_svd_select(l, s), "svd truncation");
-  std::vector<int64_t> hk((size_t)ns);
+  // the counts and s_err lie side by side: one copy
+  const size_t gap = P.ws_serr - P.ws_kept;
+  std::vector<char> host(gap + sizeof(double));
   double he = 0.0;
-  if (ns > 0) {
-    check_hip(hipMemcpyAsync(hk.data(), l.kept, sizeof(int64_t) * (size_t)ns, hipMemcpyDeviceToHost, s), "kept");
-    check_hip(hipMemcpyAsync(&he, l.s_err, sizeof(double), hipMemcpyDeviceToHost, s), "s_err");
-  }
+  if (ns > 0) check_hip(hipMemcpyAsync(host.data(), l.kept, host.size(), hipMemcpyDeviceToHost, s), "kept");
   check_hip(hipStreamSynchronize(s), "svd truncation");
-  for (int k = 0; k < ns; ++k) kept[k] = hk[k];
+  if (ns > 0) {
+    std::memcpy(kept, host.data(), sizeof(int64_t) * (size_t)ns);
+    std::memcpy(&he, host.data() + gap, sizeof(double));
+  }
   if (s_err) *s_err = he;
   BST_CATCH
 }
@@ -585,8 +586,7 @@ bst_status bst_svd_write(bst_svd* p, const int64_t* kept, int32_t absorb, void* 
   std::vector<uint8_t> tab;
   const size_t jo = put(tab, jobs), wo = put(tab, work);
   if (tab.size() > P.wtab_cap) fail(BST_E_INVALID, "internal: write tables exceed their reserve");
-  check_hip(hipMemcpyAsync(at<uint8_t>(ws, P.ws_wtab), tab.data(), tab.size(), hipMemcpyHostToDevice, s),
-            "svd write tables");
+  upload_bytes(at<uint8_t>(ws, P.ws_wtab), tab.data(), tab.size(), s);
   SvdWriteLaunch l{};
   l.jobs = at<const SvdWrite>(ws, P.ws_wtab + jo);
   l.work = at<const SvdWriteWork>(ws, P.ws_wtab + wo);
@@ -601,7 +601,7 @@ bst_status bst_svd_write(bst_svd* p, const int64_t* kept, int32_t absorb, void* 
   l.Vd = static_cast<double*>(Vd);
   l.S = static_cast<double*>(S);
   check_hip(launch_svd_write(l, s), "svd write");
-  // the host copy of the tables must outlive the transfer
+  // (the call returns when the factors are written)
   check_hip(hipStreamSynchronize(s), "svd write");
   BST_CATCH
 }

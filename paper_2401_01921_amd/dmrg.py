@@ -51,15 +51,13 @@ def legs_full(T: bst.Tensor):
 
 def relabel(T: bst.Tensor, labels: Sequence[str]) -> bst.Tensor:
     """The same legs under new labels (descriptor only)."""
-    _, legs, sym = legs_full(T)
-    return bst.Tensor(list(labels), legs, sym=sym)
+    return T.relabeled(list(labels))
 
 
 def dagger(T: bst.Tensor, labels: Sequence[str] | None = None) -> bst.Tensor:
     """Every leg's direction reversed: the descriptor of the conjugate of a
     real tensor, whose data (valid blocks, order, layout) is unchanged."""
-    old, legs, sym = legs_full(T)
-    return bst.Tensor(list(labels or old), [(-d, s) for d, s in legs], sym=sym)
+    return T.relabeled(list(labels) if labels else None, reverse=True)
 
 
 def contract(A: DevTensor, a_labels, B: DevTensor, b_labels, prec="fp64") -> DevTensor:
