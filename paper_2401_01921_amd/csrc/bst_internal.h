@@ -208,6 +208,7 @@ enum class ElemType : int { F64 = 0, F32 = 1 };
 struct TileShape {
   int bm, bn;
   int direct = 0;   // 1: LDS-free kernel (fragments loaded straight from memory);
+                    // 4: four waves share the tile's k-steps (float64);
                     // 3: pipelined persistent kernel on a k-step schedule (padded layouts only)
   int stages = 0;   // kind 3: LDS stages (copies run stages - 1 k-steps ahead)
   int waves = 4;    // kind 3: waves per workgroup (4: 2 x 2, or 1 x 4 for 192 columns; 8: 2 x 4, or 4 x 2 when bm > bn)

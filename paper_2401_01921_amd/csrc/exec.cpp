@@ -100,8 +100,12 @@ void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws,
   // tile lists this run needs, so that one upload takes them all
   for (auto& st : P.steps) {
     if (st.kind != StepKind::Gemm || !step_runs(P, st, P.prec, false)) continue;
+    const bool planes = uses_planes(P, P.prec) && st.has_alt;
     const TileShape* sh = list_shape(P, st, P.prec);
-    if (sh) tile_list(P, st, uses_planes(P, P.prec) && st.has_alt, sh->bm, sh->bn);
+    if (!planes && shares_some(st, st.fixed_fp64 ? BST_FP64 : P.prec)) {
+      tile_list(P, st, false, 32, 32, kSharedProbs);
+      tile_list(P, st, false, sh->bm, sh->bn, kOtherProbs);
+    } else if (sh) tile_list(P, st, planes, sh->bm, sh->bn);
   }
   if (need_blob) {
     P.blob_uploaded = 0;
@@ -249,7 +253,9 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.transb = st.transb;
         g.tile = default_tile(st, form);
         const auto& sh = gemm_tile_shapes(form)[g.tile];
-        const auto list = tile_list(P, st, false, sh.bm, sh.bn);
+        const bool two = shares_some(st, form);
+        const auto first = two ? tile_list(P, st, false, 32, 32, kSharedProbs) : std::pair<size_t, int64_t>();
+        const auto list = tile_list(P, st, false, sh.bm, sh.bn, two ? kOtherProbs : kAllProbs);
         upload_blob(P, ws, s);
         g.tiles = reinterpret_cast<const GemmTile*>(blob + list.first);
         g.ntiles = list.second;
@@ -260,6 +266,13 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.coef = prep.coef;
         prep.coef = HCoefLaunch{};
         e = launch_gemm(g, s);
+        if (two && e == hipSuccess) {
+          g.coef = HCoefLaunch{};
+          g.tile = kShareShape;
+          g.tiles = reinterpret_cast<const GemmTile*>(blob + first.first);
+          g.ntiles = first.second;
+          e = launch_gemm(g, s);
+        }
         break;
       }
       case StepKind::Expand: {
@@ -657,7 +670,7 @@ bst_status bst_plan_autotune(bst_plan* p, const void* const* in, void* const* ou
       int best_i = pl ? planes_tile(st, form) : default_tile(st, f);
       for (size_t i = 0; i < shapes.size(); ++i) {
         // a complex B is expanded only for the direct kernels, which costs as much as the GEMM
-        if (shapes[i].direct && !st.segs_cplx.empty()) continue;
+        if (shapes[i].direct == 1 && !st.segs_cplx.empty()) continue;
         st.tile_choice[key] = (int)i;
         run_steps_impl(P, ws, table, P.prec, s, false, (int)k, nullptr);
         const double ms = time_runs((int)k);

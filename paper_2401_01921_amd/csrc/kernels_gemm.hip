@@ -27,7 +27,8 @@ typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
 // Direct (LDS-free) variants first.
 static const std::vector<TileShape> kShapesF64 = {{64, 64, 1}, {128, 64, 1}, {64, 128, 1}, {32, 32, 1},
-                                                  {32, 32, 0}, {64, 64, 0}, {64, 32, 0}, {32, 64, 0}};
+                                                  {32, 32, 0}, {64, 64, 0}, {64, 32, 0}, {32, 64, 0},
+                                                  {32, 32, 4}};
 static const std::vector<TileShape> kShapesF32 = {{64, 64, 1}, {128, 64, 1}, {64, 128, 1}, {32, 32, 1},
                                                   {32, 32, 0}, {64, 64, 0}, {128, 64, 0}, {64, 128, 0}};
 static const std::vector<TileShape> kShapesBF3 = {{32, 32}, {64, 64}, {128, 64}, {64, 128}};
@@ -502,6 +503,197 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
       }
 }
 
+// float64 tiles of 32 x 32 whose k-steps are shared by the workgroup's four
+// waves, a contiguous quarter each, and added at the end (waves 0 + 1, 2 + 3,
+// then both).  A tile's k-steps are a serial chain, 0.33 us each in the staged
+// kernel (stage, barrier, read, MFMA), and a step with few blocks of large K is
+// as long as its longest chain; here a chain is a quarter, and a step of it has
+// neither LDS nor barrier: a lane's loads are its MFMA operands, k = 4 g + q of
+// MFMA q in lane group g.  T3.R of H_eff: chi = 64 7.5 -> 6.3 us,
+// 256 10.8 -> 8.2, 512 13.4 -> 9.7, 1024 18.8 -> 15.1.  Loads two steps ahead; three
+// take registers, that is waves (chi = 1024 16.2 us).
+__device__ __forceinline__ int wave_scan(int v) {   // inclusive, all lanes active
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast 15 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast 31 to rows 2 and 3
+  return v;
+}
+
+template <int BL>
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_ksplit_kernel(const GemmTile* __restrict__ tiles,
+                                                                      const GemmProb* __restrict__ probs,
+                                                                      const GemmSeg* __restrict__ segs,
+                                                                      void* const* __restrict__ ptrs) {
+  constexpr int BK = 16, D = 2;
+  typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+  __shared__ double sum[4][32 * 33];
+  const GemmTile t = tiles[blockIdx.x];
+  if (t.prob < 0) return;   // padding of the per-XCD tile lists
+  const GemmProb p = probs[t.prob];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = t.m0, n0 = t.n0;
+  const bool m2 = m0 + 16 < p.M, n2 = n0 + 16 < p.N;   // the second 16 rows, columns hold elements
+
+  // this wave's k-steps [t0, t1) of the tile's, and the segment they start in
+  int total = 0, base = 0, scan = 0, own = 0;
+  for (base = 0; base < p.seg_count; base += 64) {
+    own = base + lane < p.seg_count ? (segs[p.seg_begin + base + lane].K + BK - 1) / BK : 0;
+    scan = wave_scan(own);
+    total += __builtin_amdgcn_readlane(scan, 63);
+  }
+  const int t0 = total * wave / 4, t1 = total * (wave + 1) / 4;
+  int ls = 0, before = 0;   // segment, steps before it
+  if (t0 < t1) {
+    for (base = 0; base < p.seg_count; base += 64) {
+      if (p.seg_count > 64) {
+        own = base + lane < p.seg_count ? (segs[p.seg_begin + base + lane].K + BK - 1) / BK : 0;
+        scan = wave_scan(own);
+      }
+      const int chunk = __builtin_amdgcn_readlane(scan, 63);
+      if (before + chunk > t0) break;
+      before += chunk;
+    }
+    const int l = __builtin_ctzll(__ballot(before + scan > t0));
+    ls = base + l;
+    before += __builtin_amdgcn_readlane(scan, l) - __builtin_amdgcn_readlane(own, l);
+  }
+
+  dbl4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = dbl4{0, 0, 0, 0};
+
+  int lk = 0, lK = 0;
+  int64_t ldb = 0;
+  const BST_G double* pa[2];
+  const BST_G double* pb[2];
+  GemmSeg nxt{};
+  auto begin = [&](int k0) {   // the segment in nxt becomes current, from k0 on
+    const GemmSeg g = nxt;
+    const BST_G double* A = (const BST_G double*)(ptrs[g.a_buf]) + g.a_off + k0 + 4 * lg;
+    const BST_G double* B = (const BST_G double*)(ptrs[g.b_buf]) + g.b_off;
+    if (ls + 1 < p.seg_count) nxt = segs[p.seg_begin + ls + 1];
+    lk = k0;
+    lK = g.K;
+    ldb = g.ldb;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      pa[i] = A + (int64_t)min(m0 + 16 * i + l16, p.M - 1) * g.lda;
+      const int n = min(n0 + 16 * i + l16, p.N - 1);
+      if constexpr (BL == kBTrans) pb[i] = B + (int64_t)n * g.ldb + k0 + 4 * lg;
+      else if constexpr (BL == kBComplex) pb[i] = B + (int64_t)((k0 + 4 * lg) >> 1) * g.ldb + (n & ~1);
+      else pb[i] = B + (int64_t)(k0 + 4 * lg) * g.ldb + n;
+    }
+  };
+  dbl2 ra[D][2][2], rb[D][2][2];
+  int kv[D];
+  auto fetch = [&](dbl2 (&a)[2][2], dbl2 (&b)[2][2], int& k) {
+    k = min(BK, lK - lk);
+    if (k == BK) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          a[i][h] = *reinterpret_cast<const BST_G dbl2u*>(pa[i] + 2 * h);
+          if constexpr (BL == kBTrans) b[i][h] = *reinterpret_cast<const BST_G dbl2u*>(pb[i] + 2 * h);
+          else if constexpr (BL == kBComplex) b[i][h] = *reinterpret_cast<const BST_G dbl2u*>(pb[i] + h * ldb);
+          else b[i][h] = dbl2{pb[i][2 * h * ldb], pb[i][(2 * h + 1) * ldb]};
+        }
+    } else {   // k past the segment reads its last
+      const int d = k - 1 - 4 * lg;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int o0 = min(d, 2 * h), o1 = min(d, 2 * h + 1);
+          a[i][h] = dbl2{pa[i][o0], pa[i][o1]};
+          if constexpr (BL == kBTrans) b[i][h] = dbl2{pb[i][o0], pb[i][o1]};
+          else if constexpr (BL == kBComplex)   // (K is even: a pair of k is one row)
+            b[i][h] = *reinterpret_cast<const BST_G dbl2u*>(pb[i] + (o1 >> 1) * ldb);
+          else b[i][h] = dbl2{pb[i][o0 * ldb], pb[i][o1 * ldb]};
+        }
+    }
+    lk += BK;
+    if (lk < lK) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        pa[i] += BK;
+        pb[i] += BL == kBTrans ? BK : BL == kBComplex ? (BK / 2) * ldb : BK * ldb;
+      }
+    } else if (++ls < p.seg_count) {
+      begin(0);
+    }
+  };
+  auto compute = [&](const dbl2 (&ar)[2][2], const dbl2 (&br)[2][2], int k) {
+    double a[2][4], b[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[i][q] = ar[i][q >> 1][q & 1];
+        if constexpr (BL == kBComplex) {
+          // (re, im) of one element: real columns (re, im) in row k even, (-im, re) in row k odd
+          const dbl2 e = br[i][q >> 1];
+          b[i][q] = q & 1 ? (l16 & 1 ? e.x : -e.y) : (l16 & 1 ? e.y : e.x);
+        } else {
+          b[i][q] = br[i][q >> 1][q & 1];
+        }
+      }
+    if (k < BK) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[i][q] = 4 * lg + q < k ? a[i][q] : 0.0;
+          b[i][q] = 4 * lg + q < k ? b[i][q] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][q], b[0][q], acc[0][0], 0, 0, 0);
+      if (n2) acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][q], b[1][q], acc[0][1], 0, 0, 0);
+      if (m2) acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][q], b[0][q], acc[1][0], 0, 0, 0);
+      if (m2 && n2) acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][q], b[1][q], acc[1][1], 0, 0, 0);
+    }
+  };
+  const int steps = t1 - t0;
+  if (steps > 0) {
+    nxt = segs[p.seg_begin + ls];
+    begin((t0 - before) * BK);
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (d < steps) fetch(ra[d], rb[d], kv[d]);
+    for (int u0 = 0; u0 < steps; u0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int u = u0 + d;
+        if (u >= steps) break;
+        compute(ra[d], rb[d], kv[d]);
+        if (u + D < steps) fetch(ra[d], rb[d], kv[d]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[wave][(16 * i + acc_row<true>(lane, r)) * 33 + 16 * j + l16] = acc[i][j][r];
+  __syncthreads();
+  BST_G double* __restrict__ C = (BST_G double*)(ptrs[p.c_buf]) + p.c_off;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = (threadIdx.x >> 5) + 8 * e, col = threadIdx.x & 31, at = row * 33 + col;
+    if (m0 + row < p.M && n0 + col < p.N)
+      C[(int64_t)(m0 + row) * p.ldc + n0 + col] = (sum[0][at] + sum[1][at]) + (sum[2][at] + sum[3][at]);
+  }
+}
+
 // k-steps that loads run ahead.  32 x 32 float64 at 1, 2, 3, 4: T3.R of chi =
 // 512 14.3, 13.7, 13.3, 13.1 us, of chi = 2048 31.6, 28.4, 29.5, 29.4 us, L.psi of
 // chi = 2048 26.1, 25.4, 27.7, 27.8 us: more depth costs registers, that is waves,
@@ -543,6 +735,20 @@ static hipError_t launch_form(const GemmLaunch& g, hipStream_t s) {
   const auto& shapes = gemm_tile_shapes((bst_precision)FORM);
   if (g.tile < 0 || g.tile >= (int)shapes.size()) return hipErrorInvalidValue;
   const int bm = shapes[g.tile].bm, bn = shapes[g.tile].bn;
+  if constexpr (FORM == BST_FP64) {
+    if (shapes[g.tile].direct == 4) {
+      if (g.coef.nentries > 0 || g.ta != ElemType::F64 || g.tb != ElemType::F64 || g.tc != ElemType::F64)
+        return hipErrorInvalidValue;
+      const dim3 grid((unsigned)g.ntiles), block(256);
+      if (g.b_complex)
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBComplex>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+      else if (g.transb)
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBTrans>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+      else
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBPlain>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+      return hipGetLastError();
+    }
+  }
   if (shapes[g.tile].direct)
     return g.coef.nentries > 0 || g.b_complex ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
   const bool a64 = g.ta == ElemType::F64, c64 = g.tc == ElemType::F64;

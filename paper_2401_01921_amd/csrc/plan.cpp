@@ -1139,6 +1139,13 @@ static void heff_batch(const std::vector<const PlanData*>& subs, PlanData& P) {
           p.seg_begin += sb;
           b.probs.push_back(p);
         }
+        // (empty for a member means none; all empty stays empty)
+        b.shared_set = true;
+        if (!a.shared.empty() || !b.shared.empty()) {
+          b.shared.resize(b.probs.size() - a.probs.size(), 0);
+          b.shared.insert(b.shared.end(), a.shared.begin(), a.shared.end());
+          b.shared.resize(b.probs.size(), 0);
+        }
         const int32_t sba = (int32_t)b.segs_alt.size();
         for (auto g : a.segs_alt) {
           g.a_buf += base;
@@ -1252,7 +1259,8 @@ static int64_t tile_run(int64_t total) { return std::max<int64_t>(1, (total + 31
 static int64_t tile_list_cap(int64_t total) { return total * 3 / 2 / kXcds + tile_run(total) + 1; }
 
 static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
-                                        const std::vector<GemmSeg>& segs, int bm, int bn) {
+                                        const std::vector<GemmSeg>& segs, int bm, int bn,
+                                        const std::vector<uint8_t>& shared = {}, int part = kAllProbs) {
   const int64_t total = tile_total(probs, bm, bn), run = tile_run(total), cap = tile_list_cap(total);
   struct Run {
     double cost;
@@ -1263,6 +1271,7 @@ static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
   runs.reserve(probs.size() + 32);
   for (size_t pi = 0; pi < probs.size(); ++pi) {
     const auto& p = probs[pi];
+    if (part != kAllProbs && (shared[pi] != 0) != (part == kSharedProbs)) continue;
     int64_t k = 0;
     for (int s = 0; s < p.seg_count; ++s) k += segs[p.seg_begin + s].K;
     const int64_t nt = (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
@@ -1298,15 +1307,16 @@ static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
   return out;
 }
 
-std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn) {
+std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn, int part) {
   auto& lists = alt ? st.tile_lists_alt : st.tile_lists;
-  auto it = lists.find({bm, bn});
+  const std::pair<int, int> key(bm + 4096 * part, bn);
+  auto it = lists.find(key);
   if (it == lists.end()) {
-    const auto tl = make_tiles(alt ? st.probs_alt : st.probs, alt ? st.segs_alt : st.segs, bm, bn);
+    const auto tl = make_tiles(alt ? st.probs_alt : st.probs, alt ? st.segs_alt : st.segs, bm, bn, st.shared, part);
     const size_t off = put(P.blob, tl);
     P.blob.resize(align256(P.blob.size()));
     if (P.ws_blob_off + P.blob.size() > P.ws_coef64_off) fail(BST_E_INVALID, "internal: tile lists outgrow their space");
-    it = lists.emplace(std::make_pair(bm, bn), std::make_pair(off, (int64_t)tl.size())).first;
+    it = lists.emplace(key, std::make_pair(off, (int64_t)tl.size())).first;
   }
   return it->second;
 }
@@ -1567,6 +1577,11 @@ static Step::StreamList make_fused(std::vector<uint8_t>& blob, const Step& st, i
   return L;
 }
 
+bool shares_some(const Step& st, bst_precision form) {
+  if (form != BST_FP64 || st.shared.empty() || st.tile_choice.count((int)form)) return false;
+  return std::find(st.shared.begin(), st.shared.end(), 0) != st.shared.end();
+}
+
 int default_tile(const Step& st, bst_precision form) {
   auto it = st.tile_choice.find((int)form);
   if (it != st.tile_choice.end()) return it->second;
@@ -1578,6 +1593,7 @@ int default_tile(const Step& st, bst_precision form) {
   //                     3162 171 / 161, 14512 191 / 174
   //   float32, 64 x 64: 248 tiles 7.6 / 8.2, 304 25.7 / 29.3, 1312 22.7 / 20.1,
   //                     1749 139 / 102, 7993 152 / 109
+  if (form == BST_FP64 && !st.shared.empty() && !shares_some(st, form)) return kShareShape;
   if (form == BST_FP64 || form == BST_FP32) {
     const int64_t tiles = form == BST_FP64 ? st.tiles64x32 : st.tiles64x64;
     return tiles < 4 * kStreamCUs ? 4 : form == BST_FP64 ? 6 : 5;
@@ -1595,7 +1611,8 @@ int default_tile(const Step& st, bst_precision form) {
 
 bool reads_complex(const Step& st, bst_precision prec) {
   if (st.segs_cplx.empty() || (prec != BST_FP64 && prec != BST_FP32)) return false;
-  return gemm_tile_shapes(prec)[default_tile(st, prec)].direct == 0;
+  const int kind = gemm_tile_shapes(prec)[default_tile(st, prec)].direct;
+  return kind == 0 || kind == 4;
 }
 
 // Shape of a plane GEMM without a tuned choice.  All of them give the same
@@ -1668,10 +1685,22 @@ void finalize(PlanData& P) {
         st.tile_lists.clear();
         st.tile_lists_alt.clear();
         st.tiles64x32 = st.tiles64x64 = 0;
+        int64_t tiles = 0, ksteps = 0;
         for (const auto& p : st.probs) {
-          const int64_t rows = (p.M + 63) / 64;
+          const int64_t rows = (p.M + 63) / 64, t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
           st.tiles64x32 += rows * ((p.N + 31) / 32);
           st.tiles64x64 += rows * ((p.N + 63) / 64);
+          tiles += t32;
+          for (int q = 0; q < p.seg_count; ++q) ksteps += t32 * ((st.segs[p.seg_begin + q].K + 15) / 16);
+        }
+        // float64 steps with few tiles of long chains share a tile's k-steps between
+        // its waves, up to two tiles per CU and from three steps a tile; T3.R of
+        // H_eff, 32 x 32 staged / shared: 32 tiles of 3.6 steps 7.5 / 6.3, 80 of 7.7 10.8
+        // / 8.2, 144 of 11 13.4 / 9.7, 368 of 17 18.8 / 15.1; 912 of 21 28.6 / 28.4, L.psi
+        // 304 of 1.9 6.5 / 6.7, 620 of 2.5 8.5 / 9.1.
+        if (!st.shared_set) {
+          st.shared.clear();
+          if (tiles < 2 * kStreamCUs && ksteps >= 3 * tiles) st.shared.assign(st.probs.size(), 1);
         }
         // space for every tile list; each is built on first use (an MPO
         // contraction has thousands of tiles, six lists of them took longer to
@@ -1681,6 +1710,9 @@ void finalize(PlanData& P) {
           for (int f = 0; f < 4; ++f)
             for (const auto& sh : gemm_tile_shapes((bst_precision)f)) shapes.insert({sh.bm, sh.bn});
           for (const auto& b : shapes) reserve += list_bytes(st.probs, b.first, b.second);
+          // a batch of both kinds: the shared tiles' list and the others' (default_tile's shapes)
+          if (std::find(st.shared.begin(), st.shared.end(), 0) != st.shared.end())
+            reserve += 2 * list_bytes(st.probs, 32, 32) + list_bytes(st.probs, 64, 32);
         }
         if (st.has_alt) {
           st.off2 = put(P.blob, st.segs_alt);
@@ -2115,6 +2147,7 @@ bst_status bst_plan_tiles(const bst_plan* p, char* buf, size_t cap) {
     const TileShape sh = pl ? gemm_planes_shapes(plane_count(P.prec))[planes_tile(st, P.prec)]
                             : gemm_tile_shapes(P.prec)[default_tile(st, P.prec)];
     const std::string kind = sh.direct == 1   ? "d"
+                             : sh.direct == 4 ? "k"
                              : sh.direct == 3 ? "s" + std::to_string(sh.stages) + "w" + std::to_string(sh.waves)
                                               : "l";
     s += st.name + ":" + std::to_string(sh.bm) + "x" + std::to_string(sh.bn) + kind + (pl ? "p" : "") + ";";

@@ -52,6 +52,11 @@ struct Step {
   std::vector<GemmSeg> segs;
   std::map<int, int> tile_choice;   // form -> index into gemm_tile_shapes(form)
   int64_t tiles64x32 = 0, tiles64x64 = 0;   // tiles of that size over all problems
+  // float64 without a tuned choice: problems whose tiles share their k-steps
+  // between waves (kShareShape); a batch takes over its members' choice, so that
+  // a member's result has the bits of its own plan
+  std::vector<uint8_t> shared;
+  bool shared_set = false;
   // Permute
   std::vector<PermJob> jobs;
   std::vector<PermWork> pwork;
@@ -172,8 +177,10 @@ struct PlanData {
 
 void finalize(PlanData& p);
 // A GEMM step's tile list for one shape (offset in the blob, entries), built on
-// first use; alt: of the plane variant.
-std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn);
+// first use; alt: of the plane variant; part: of all problems, or those of
+// Step::shared, or the others.
+enum ProbPart { kAllProbs, kSharedProbs, kOtherProbs };
+std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn, int part = kAllProbs);
 // Puts blob bytes that ws does not hold yet there.
 void upload_blob(PlanData& P, void* ws, hipStream_t s);
 // Host bytes to device memory by a copy that is waited for.
@@ -203,6 +210,10 @@ bool step_runs(const PlanData& p, const Step& st, bst_precision prec, bool skip_
 bool fused_active(const PlanData& p, bst_precision prec);
 int planes_tile(const Step& st, bst_precision prec);
 int default_tile(const Step& st, bst_precision form);
+constexpr int kShareShape = 8;   // float64: 32 x 32, k-steps shared
+// float64 runs as two launches, the problems of Step::shared on kShareShape and
+// the others on default_tile's shape.
+bool shares_some(const Step& st, bst_precision form);
 // The GEMM of a complex contraction reads B itself in this form (staged
 // float64 / float32 tiles).
 bool reads_complex(const Step& st, bst_precision prec);

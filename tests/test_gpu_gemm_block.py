@@ -6,7 +6,7 @@ result within the form's tolerance."""
 import numpy as np
 import pytest
 
-from tests.gpu_common import DEV, check, dev, host, require_gpu, torch
+from tests.gpu_common import DEV, check, dev, heff_operands, host, lib_heff, require_gpu, torch
 from oracle import oracle as orc
 from paper_2401_01921_amd import bst
 
@@ -78,3 +78,55 @@ def test_complex_tile_edges(prec, b_order, rows, cols):
         if "l;" in plan.tiles():
             first = got if first is None else first
             assert np.array_equal(got, first), plan.tiles()
+
+
+@pytest.mark.parametrize("segs", [1, 2, 5, 63, 64, 65, 150])
+@pytest.mark.parametrize("kind", ["plain", "along k", "complex"])
+def test_shared_k_steps(segs, kind):
+    """float64 tiles whose waves share the k-steps: fewer steps than waves, a wave
+    that starts inside a segment, more segments than lanes, uneven K."""
+    rng = np.random.default_rng(segs)
+    i, j = (1, [(0, 33)]), (-1, [(0, 21)])
+    q = list(range(-(segs // 2), segs - segs // 2))
+    k = [(c, int(rng.integers(1, 40))) for c in q]
+    l = [(-c, 1 + (c % 2)) for c in q][::-1]
+    flip = {"k": (1, k), "l": (1, l), "j": j}
+    order = ["j", "k", "l"] if kind == "along k" else ["k", "l", "j"]
+    A = orc.BlockTensor(["i", "k", "l"], [i, (-1, k), (-1, l)])
+    B = orc.BlockTensor(order, [flip[x] for x in order])
+    cplx = kind == "complex"
+    for T in (A, B):
+        T.data = rng.standard_normal(T.numel) + (1j * rng.standard_normal(T.numel) if cplx else 0)
+    C = orc.contract(A, B)
+    tC, plan = bst.contract_plan(bst.Tensor(A.labels, A.legs), bst.Tensor(B.labels, B.legs), "fp64",
+                                 dtype="c128" if cplx else "f64")
+    plan.set_tile("fp64", 8)
+    assert "32x32k" in plan.tiles()
+    w = 2 if cplx else 1
+    ins = [torch.view_as_real(torch.from_numpy(T.data).to(DEV)).reshape(-1) if cplx else dev(T.data) for T in (A, B)]
+    out = torch.full((w * tC.numel,), np.nan, dtype=torch.float64, device=DEV)
+    plan.execute(ins, [out], bst.workspace(plan.workspace_bytes))
+    got = host(torch.view_as_complex(out.reshape(-1, 2))) if cplx else host(out)
+    check(got, C.data, "fp64", f"{kind} {segs} {plan.tiles()}")
+
+
+def test_batch_of_shared_and_other_members():
+    """A float64 batch whose members differ in whether their tiles share k-steps:
+    each member has the bits of its own plan."""
+    parts, plans, ins = [], [], []
+    for chi, qmax in ((256, 6), (1800, 3), (64, 4)):
+        specs, O = heff_operands(2, chi=chi, qmax=qmax)
+        parts.append(O)
+        plans.append(lib_heff(specs, "fp64")[1])
+        ins.append([dev(O[n].data) for n in ("L", "W1", "W2", "R", "psi")])
+    assert ["32x32k" in p.tiles() for p in plans] == [True, False, True]
+    single, outs = [], [torch.full((O["psi"].numel,), np.nan, dtype=torch.float64, device=DEV) for O in parts]
+    for p, x, O in zip(plans, ins, parts):
+        o = torch.empty(O["psi"].numel, dtype=torch.float64, device=DEV)
+        p.execute(x, [o], bst.workspace(p.workspace_bytes))
+        single.append(host(o))
+    batch = bst.heff_batch_plan(plans)
+    batch.set_precision("fp64")
+    batch.execute([t for x in ins for t in x], outs, bst.workspace(batch.workspace_bytes))
+    for a, b in zip(outs, single):
+        assert np.array_equal(host(a), b)
