@@ -223,9 +223,9 @@ static const std::vector<TileShape> kPlaneShapes2 = {
     {128, 64, 3, 3, 4},  {64, 128, 3, 3, 4},  {128, 128, 3, 3, 8}, {128, 256, 3, 3, 8},
     {256, 128, 3, 3, 8}, {256, 64, 3, 3, 8},  {64, 192, 3, 3, 4}, {64, 192, 3, 2, 4},
     {128, 192, 3, 3, 8}, {128, 128, 3, 2, 8}, {128, 64, 3, 2, 4}, {64, 128, 3, 2, 4},
-    {32, 192, 3, 2, 4}};
+    {32, 192, 3, 2, 4},  {32, 32, 4}};
 static const std::vector<TileShape> kPlaneShapes3 = {{64, 64, 0}, {32, 32, 0}, {64, 64, 3, 3, 4},
-                                                     {128, 128, 3, 3, 8}};
+                                                     {128, 128, 3, 3, 8}, {32, 32, 4}};
 // float64 operands in the padded layouts: the pipelined kernel only
 static const std::vector<TileShape> kPlaneShapes1 = {{64, 64, 3, 3, 4},   {128, 64, 3, 3, 4},
                                                      {64, 128, 3, 3, 4},  {128, 128, 3, 3, 8},
@@ -234,6 +234,120 @@ static const std::vector<TileShape> kPlaneShapes1 = {{64, 64, 3, 3, 4},   {128, 
                                                      {64, 128, 3, 2, 4},  {128, 128, 3, 2, 8}};
 const std::vector<TileShape>& gemm_planes_shapes(int np) {
   return np == 1 ? kPlaneShapes1 : np == 3 ? kPlaneShapes3 : kPlaneShapes2;
+}
+
+// Tiles of 32 x 32 for steps with few of them: a wave takes 16 x 16 and loads its
+// MFMA operands straight from the planes (lane group g's chunk of a row, all
+// planes, is one run of 16 NP bytes), D k-steps ahead.  Such a step is as long as
+// its longest chain of k-steps; through LDS (load, stage, barrier, read, MFMA, and
+// two dependent reads per segment) one took 0.6 us.  The products and their order
+// are those of the other kernels.  T3.R of H_eff in the two-plane form: chi = 64
+// 7.5 -> 6.6 us, 256 9.5 -> 8.3, 512 12.2 -> 9.8.  A row is read by two waves and 16
+// bytes at a time, so that with several tiles per CU the L1 bounds it (L.psi at
+// chi = 1024, five tiles per CU: 8.6 us staged, 13.8 here).
+template <int NP, typename TC>
+__global__ __launch_bounds__(256, kMfmaWaves) void gemm_planes_wave_kernel(const GemmTile* __restrict__ tiles,
+                                                                           const GemmProb* __restrict__ probs,
+                                                                           const GemmSeg* __restrict__ segs,
+                                                                           void* const* __restrict__ ptrs,
+                                                                           const int64_t* __restrict__ rowmap) {
+  constexpr int BK = 32, D = NP == 2 ? 4 : 3;
+  const GemmTile t = tiles[blockIdx.x];
+  if (t.prob < 0) return;   // padding of the per-XCD tile lists
+  const GemmProb p = probs[t.prob];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = t.m0 + 16 * (wave >> 1), n0 = t.n0 + 16 * (wave & 1);
+  if (m0 >= p.M || n0 >= p.N) return;   // (no barriers below)
+
+  flt4 acc = flt4{0, 0, 0, 0};
+  // load cursor: segment ls at k = lk; rows past the block read its last one
+  int ls = 0, lk = 0, lK = 0, a_buf = -1, b_buf = -1;
+  GemmSeg nxt{};
+  const BST_G unsigned short *A = nullptr, *B = nullptr, *pa = nullptr, *pb = nullptr;
+  const int64_t ar = min(m0 + l16, p.M - 1), br = min(n0 + l16, p.N - 1);
+  auto begin = [&]() {   // the segment in nxt becomes current
+    const GemmSeg g = nxt;
+    if (g.a_buf != a_buf) A = (const BST_G unsigned short*)(ptrs[a_buf = g.a_buf]);
+    if (g.b_buf != b_buf) B = (const BST_G unsigned short*)(ptrs[b_buf = g.b_buf]);
+    if (ls + 1 < p.seg_count) nxt = segs[p.seg_begin + ls + 1];
+    lk = 0;
+    lK = g.K;
+    pa = A + (g.a_off + ar * g.lda + 8 * lg) * NP;
+    pb = B + (g.b_off + br * g.ldb + 8 * lg) * NP;
+  };
+  us8 ra[D][NP], rb[D][NP];
+  int kv[D];   // k of a step inside its segment, 0: no such step
+  auto fetch = [&](us8 (&a)[NP], us8 (&b)[NP], int& k) {
+    k = min(BK, lK - lk);
+    const int back = k < BK ? min((k - 1) / 8 - lg, 0) * 8 * NP : 0;   // a chunk past k reads the last
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      a[q] = *reinterpret_cast<const BST_G us8*>(pa + back + 8 * q);
+      b[q] = *reinterpret_cast<const BST_G us8*>(pb + back + 8 * q);
+    }
+    lk += BK;
+    if (lk < lK) {
+      pa += BK * NP;
+      pb += BK * NP;
+    } else if (++ls < p.seg_count) {
+      begin();
+    }
+  };
+  auto compute = [&](us8 (&ua)[NP], us8 (&ub)[NP], int k) {
+    if (k < BK) {
+      const int n = k - 8 * lg;
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (e >= n) ua[q][e] = 0;
+          if (e >= n) ub[q][e] = 0;
+        }
+    }
+    bf16x8 a[NP], b[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      a[q] = __builtin_bit_cast(bf16x8, ua[q]);
+      b[q] = __builtin_bit_cast(bf16x8, ub[q]);
+    }
+    if constexpr (NP == 3) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
+    }
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
+  };
+  int steps = 0;
+  for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
+  if (steps > 0) {
+    nxt = segs[p.seg_begin];
+    begin();
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (d < steps) fetch(ra[d], rb[d], kv[d]);
+    for (int u0 = 0; u0 < steps; u0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int u = u0 + d;
+        if (u >= steps) break;
+        compute(ra[d], rb[d], kv[d]);
+        if (u + D < steps) fetch(ra[d], rb[d], kv[d]);
+      }
+    }
+  }
+  BST_G TC* __restrict__ C = (BST_G TC*)(ptrs[p.c_buf]);
+  int64_t rbase[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = min(m0 + 4 * lg + r, p.M - 1);
+    rbase[r] = p.rowmap1 > 0 ? rowmap[p.rowmap1 - 1 + row] : p.c_off + (int64_t)row * p.ldc;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (m0 + 4 * lg + r < p.M && n0 + l16 < p.N) C[rbase[r] + n0 + l16] = (TC)acc[r];
 }
 
 template <int NP, typename TC, int BM, int BN, int BK>
@@ -441,6 +555,19 @@ hipError_t launch_gemm_planes(const PlanesLaunch& g, hipStream_t s) {
   const auto& sh = gemm_planes_shapes(g.np);
   if (g.tile < 0 || g.tile >= (int)sh.size()) return hipErrorInvalidValue;
   const int bm = sh[g.tile].bm, bn = sh[g.tile].bn;
+  if (sh[g.tile].direct == 4) {
+    const dim3 grid((unsigned)g.ntiles), block(256);
+#define BST_WAVE(NP_, TC_)                                                                                  \
+  hipLaunchKernelGGL((gemm_planes_wave_kernel<NP_, TC_>), grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs, \
+                     g.rowmap)
+    if (g.np == 2 && g.tc == ElemType::F64) BST_WAVE(2, double);
+    else if (g.np == 2) BST_WAVE(2, float);
+    else if (g.np == 3 && g.tc == ElemType::F64) BST_WAVE(3, double);
+    else if (g.np == 3) BST_WAVE(3, float);
+    else return hipErrorInvalidValue;
+#undef BST_WAVE
+    return hipGetLastError();
+  }
   if (sh[g.tile].direct != 0) return hipErrorInvalidValue;   // kind 3: launch_gemm_planes_stream
   const int bk = 32;   // 64-deep k steps (1 or 2 workgroups per CU) measured slower
   if (g.np == 2)

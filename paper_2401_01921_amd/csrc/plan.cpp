@@ -1619,13 +1619,16 @@ bool reads_complex(const Step& st, bst_precision prec) {
 // bits; what decides is whether the tiles fill the chip.  us on steps of H_eff,
 // chosen shape against the next best and against 256 x 128 or 128 x 256 (two
 // planes) or 128 x 128 (three), the former choice at every size:
-//   two planes   up to 127 tiles of 128 x 64, 32 x 32 staged (no schedule to
-//                read, many workgroups): 24 tiles 12.2 / 13.7 / 22.5, 64 tiles
-//                15.7 / 16.9 / 28.6; 134 tiles 22.6 / 20.9, 511 15.5 / 11.7;
-//                above, 128 x 64 (64 x 128 where most work is in wide problems):
-//                134 tiles 20.9 / 20.6 / 35.4, 726 43.5 / 48.5 / 53.5, 3162
-//                40.2 / 42.1 / 44.8; two stages, so that more than one workgroup
-//                fits a CU
+//   both         up to 256 tiles of 32 x 32 (one per CU), those without LDS: two
+//                planes, 12 tiles 6.6 / 7.5 / 14.1, 48 8.3 / 9.5 / 18.1, 114 9.8 /
+//                12.2 / 22.5, 319 16.6 / 15.7, L.psi 440 7.2 / 6.4; three, 48 9.2 /
+//                11.5 / 17.3, 114 11.9 / 14.4 / 21.7, L.psi 440 8.4 / 7.4
+//   two planes   then up to 127 tiles of 128 x 64, 32 x 32 staged (no schedule to
+//                read, many workgroups): 64 tiles 15.7 / 16.9 / 28.6; 134 tiles 22.6
+//                / 20.9, 511 15.5 / 11.7; above, 128 x 64 (64 x 128 where most work
+//                is in wide problems): 134 tiles 20.9 / 20.6 / 35.4, 726 43.5 / 48.5
+//                / 53.5, 3162 40.2 / 42.1 / 44.8; two stages, so that more than one
+//                workgroup fits a CU
 //   three planes 64 x 64 up to 1023 tiles of 128 x 128: 24 tiles 14.4 / 21.8,
 //                470 90.8 / 93.5; 1616 84.8 / 68.2
 //   float64      64 x 64 up to 511 tiles of 128 x 64, then 128 x 64: 134 tiles
@@ -1633,7 +1636,7 @@ bool reads_complex(const Step& st, bst_precision prec) {
 // The first of the list whose schedule exists (its layout rules hold) is taken.
 static int planes_auto_tile(const Step& st, int np) {
   double wm = 0, wn = 0;
-  int64_t t128x64 = 0, t128 = 0;
+  int64_t t32 = 0, t128x64 = 0, t128 = 0;
   for (const auto& p : st.probs_alt) {
     int64_t k = 0;
     for (int q = 0; q < p.seg_count; ++q) k += st.segs_alt[p.seg_begin + q].K;
@@ -1641,16 +1644,19 @@ static int planes_auto_tile(const Step& st, int np) {
     wm += w * p.M;
     wn += w * p.N;
     const int64_t rows = (p.M + 127) / 128;
+    t32 += (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
     t128x64 += rows * ((p.N + 63) / 64);
     t128 += rows * ((p.N + 127) / 128);
   }
-  const TileShape staged32{32, 32, 0}, tall{128, 64, 3, 2, 4}, wide{64, 128, 3, 2, 4};
+  const TileShape wave32{32, 32, 4}, staged32{32, 32, 0}, tall{128, 64, 3, 2, 4}, wide{64, 128, 3, 2, 4};
   std::vector<TileShape> want;
   if (np == 2) {
-    if (t128x64 < kStreamCUs / 2) want = {staged32};
+    if (t32 <= kStreamCUs) want = {wave32};
+    else if (t128x64 < kStreamCUs / 2) want = {staged32};
     else want = {wn >= wm ? wide : tall};
   } else if (np == 3) {
-    if (t128 >= 4 * kStreamCUs) want = {{128, 128, 3, 3, 8}};
+    if (t32 <= kStreamCUs) want = {wave32};
+    else if (t128 >= 4 * kStreamCUs) want = {{128, 128, 3, 3, 8}};
     want.push_back({64, 64, 3, 3, 4});
   } else {
     if (t128x64 >= 2 * kStreamCUs) want = {tall};

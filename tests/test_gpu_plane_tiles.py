@@ -20,10 +20,12 @@ def _gemms(plan):
 
 
 @pytest.mark.parametrize("prec, chi, qmax, spin, want", [
-    ("bf16x3", 40, 3, "1/2", ["32x32lp", "32x32lp"]),
+    ("bf16x3", 40, 3, "1/2", ["32x32kp", "32x32kp"]),
+    ("bf16x3", 512, 8, "1/2", ["32x32lp", "32x32kp"]),
     ("bf16x3", 1024, 10, "1/2", ["128x64s2w4p", "32x32lp"]),
     ("bf16x3", 2048, 16, "1/2", ["128x64s2w4p", "128x64s2w4p"]),
     ("bf16x3", 1500, 2, "1", ["64x128s2w4p", "128x64s2w4p"]),
+    ("bf16x6", 512, 8, "1/2", ["64x64s3w4p", "32x32kp"]),
     ("bf16x6", 1024, 10, "1/2", ["64x64s3w4p", "64x64s3w4p"]),
     ("bf16x6", 1800, 2, "1", ["128x128s3w8p", "64x64s3w4p"]),
     ("fp64", 512, 8, "1/2", ["64x64s2w4p", "64x64s2w4p"]),
