@@ -15,8 +15,8 @@
 //
 // Measured, kernels only: a two-site spin-1/2 state at chi = 256 (15 sectors
 // to 52 x 52), 1.62 ms in the one-workgroup LDS kernel before, now 35 us (1) +
-// 170 us (2) + 31 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
-// round before, now 7 x (46 + 17) us (1) + 2.24 ms (2) + 0.16 ms (3).
+// 170 us (2) + 27 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
+// round before, now 7 x (46 + 17) us (1) + 2.24 ms (2) + 0.13 ms (3).
 //
 // Layout of a sector in the workspace: p + r rows of ld doubles, the rows of
 // X (sorted) and then those of V; ld is the padded column count N.
@@ -54,12 +54,6 @@ __device__ __forceinline__ int fresh_lane() {
 __device__ __forceinline__ double uniform(double v) {
   return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                           __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
-// Barrier of a workgroup that waits for LDS only: __syncthreads would also
-// wait for the log's stores to global memory, on the critical path of a step.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // 1 / sqrt(q) to rounding: the hardware's estimate (some 26 bits) and one
@@ -184,7 +178,7 @@ __device__ __forceinline__ void panel_rows(double* lds, double* ub, double* ubuf
     load_pairs<E>(x, lds, l16);
     form(x, lds[k0], 0);
   }
-  lds_barrier();
+  __syncthreads();
   for (int i = 0; i < nref; ++i) {
     double2 u[E], x[E];
     load_pairs<E>(u, ub + (i & 1) * LDL, l16);
@@ -202,7 +196,7 @@ __device__ __forceinline__ void panel_rows(double* lds, double* ub, double* ubuf
         if (q < rows) store_pairs<E>(x, lds + q * LDL, l16);
       }
     }
-    lds_barrier();
+    __syncthreads();
   }
 }
 }  // namespace
@@ -659,7 +653,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
                              dpp_zero<kWaveShl1>(st[1].e)};
           }
           sh.part[wave][2 + w][lane] = dot<RW>(v[0], v[1]);
-          lds_barrier();
+          __syncthreads();
           double g0 = 0.0, g1 = 0.0;
 #pragma unroll
           for (int i = 0; i < W; i += 2) {
@@ -692,7 +686,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
           const int la = fresh_lane();
           sh.part[wave][0][la] = g0;
           sh.part[wave][1][la] = g1;
-          lds_barrier();
+          __syncthreads();
           if (wave < U) {
             const int lb = fresh_lane();
             double2 c;
@@ -700,7 +694,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
             sh.cf[wave][lb] = c;
             lg[64 * ((s0 + w) * U + wave) + lb] = c;
           }
-          lds_barrier();
+          __syncthreads();
           const int lc = fresh_lane();
           lift<RW>(x0, y0, sh.cf[0][lc]);
           lift<RW>(x1, y1, sh.cf[1][lc]);
@@ -801,24 +795,26 @@ __global__ __launch_bounds__(64 * kSvdRegWaves) void svd_reg_kernel(const SvdSec
   }
 }
 
-// The logged rotations on the rows of V, four rows per wave.  Bound: latency
+constexpr int kSvdApplyRows = 2;
+// The logged rotations on the rows of V, two rows per wave.  Bound: latency
 // of a step (two dependent products and a move), hidden by the other waves of
-// the SIMD; the log is read once per four rows, from L2.
+// the SIMD; the log is read once per wave, from L2: with 4, 2 and 1 rows a wave
+// 160, 128 and 188 us at chi = 1024, 31, 27 and 26 us at chi = 256.
 __global__ __launch_bounds__(256) void svd_apply_kernel(const SvdSec* __restrict__ secs,
                                                         const int32_t* __restrict__ list, double* D,
                                                         const double* scratch, const int32_t* __restrict__ ctrl) {
   const SvdSec S = secs[list[blockIdx.y]];
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m;
-  const int lane = threadIdx.x & 63, q = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 4;
+  const int lane = threadIdx.x & 63, q = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kSvdApplyRows;
   if (q >= r) return;
   double* const V = D + S.x_off + (int64_t)p * S.ld;
   const double* const log = scratch + S.log_off;
   const int sweeps = ctrl[2 * blockIdx.y];
   const bool rev = ctrl[2 * blockIdx.y + 1] != 0;
   if (S.pairs == 1)
-    apply_log<1, 4>(V, q, r, S.ld, lane, log, sweeps, rev);
+    apply_log<1, kSvdApplyRows>(V, q, r, S.ld, lane, log, sweeps, rev);
   else
-    apply_log<2, 4>(V, q, r, S.ld, lane, log, sweeps, rev);
+    apply_log<2, kSvdApplyRows>(V, q, r, S.ld, lane, log, sweeps, rev);
 }
 
 hipError_t launch_svd_reg(const SvdLaunch& l, hipStream_t s) {
@@ -833,7 +829,7 @@ hipError_t launch_svd_reg(const SvdLaunch& l, hipStream_t s) {
   }
   hipLaunchKernelGGL(svd_reg_kernel, dim3(n), dim3(64 * kSvdRegWaves), 0, s, l.secs, l.reg, l.X, l.scratch, l.logcap,
                      l.ctrl, l.sweeps, l.sig, l.sorted, l.perm);
-  hipLaunchKernelGGL(svd_apply_kernel, dim3((unsigned)((l.reg_cols + 15) / 16), n), dim3(256), 0, s, l.secs, l.reg,
+  hipLaunchKernelGGL(svd_apply_kernel, dim3((unsigned)((l.reg_cols + 4 * kSvdApplyRows - 1) / (4 * kSvdApplyRows)), n), dim3(256), 0, s, l.secs, l.reg,
                      l.X, l.scratch, l.ctrl);
   return hipGetLastError();
 }
