@@ -570,10 +570,14 @@ static void add_split_jobs(Step& st, const TensorDesc& T, int split, bool transp
     j.transpose = transpose ? 1 : 0;
     const int32_t jid = (int32_t)st.sjobs.size();
     st.sjobs.push_back(j);
-    const int64_t rext = transpose ? Lay.ld[b] : rows;
-    const int64_t cext = transpose ? cols : Lay.ld[b];
-    for (int64_t r0 = 0; r0 < rext; r0 += 64)
-      for (int64_t c0 = 0; c0 < cext; c0 += 64) st.swork.push_back({jid, (int32_t)r0, (int32_t)c0, 0});
+    if (!transpose) {   // runs of 8-element output chunks, whatever the row length
+      const int64_t chunks = rows * (Lay.ld[b] / 8);
+      if (chunks > 0x7FFFFFFF - kSplitChunks) fail(BST_E_INVALID, "block too large for the bfloat16 split");
+      for (int64_t k = 0; k < chunks; k += kSplitChunks) st.swork.push_back({jid, (int32_t)k, 0, 0});
+      continue;
+    }
+    for (int64_t r0 = 0; r0 < Lay.ld[b]; r0 += 64)
+      for (int64_t c0 = 0; c0 < cols; c0 += 64) st.swork.push_back({jid, (int32_t)r0, (int32_t)c0, 0});
   }
   st.bytes += 8.0 * (double)T.numel + 4.0 * (double)Lay.total;
   st.bytes32 = st.bytes;

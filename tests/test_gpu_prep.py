@@ -4,7 +4,8 @@ with a GEMM that cannot carry the coefficients, and for a batch."""
 import numpy as np
 import pytest
 
-from tests.gpu_common import DEV, dev, heff_operands, host, lib_heff, require_gpu, torch
+from tests.gpu_common import DEV, check, dev, heff_operands, host, lib_heff, require_gpu, run_heff, torch
+from oracle import oracle as orc
 from paper_2401_01921_amd import bst
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +45,15 @@ def test_merged_equals_stepwise(prec, panels, tile, chis, monkeypatch):
     for a, b in zip(got, ref):
         assert np.isfinite(host(a)).all()
         assert np.array_equal(host(a), host(b))
+
+
+@pytest.mark.parametrize("chi, qmax", [(9, 1), (33, 2), (65, 1), (129, 1), (517, 3)])
+@pytest.mark.parametrize("prec", ["fp64", "bf16x3", "bf16x6"])
+def test_split_edges(chi, qmax, prec, monkeypatch):
+    """Operand splits at odd row lengths, chunks past the columns and runs of
+    chunks that end inside a row (float64: the copies into the padded layout)."""
+    monkeypatch.setenv("BST_FP64_PANELS", "1")
+    specs, O = heff_operands(2, chi=chi, qmax=qmax)
+    ref = orc.heff_apply(O["L"], O["W1"], O["W2"], O["R"], O["psi"]).data
+    T, plan = lib_heff(specs, prec)
+    check(run_heff(plan, O), ref, prec, f"chi {chi}")
