@@ -131,7 +131,8 @@ struct GemmProb {
   int32_t rowmap1, pad;
 };
 struct GemmTile {
-  int32_t prob, m0, n0, pad;
+  int32_t prob, m0, n0;
+  int32_t seg;   // the problem's first segment (0 if it has none)
 };
 
 // Block permute job: one block, row-major input shape and, per input dim,

@@ -251,7 +251,9 @@ enum BLayout { kBPlain, kBTrans, kBComplex };   // [k][n], [n][k], complex [k / 
 //   - a wave runs the MFMAs of its 16 x 16 sub-tiles that hold elements of the
 //     block, and of a segment's last k-step those that reach into it;
 //   - loads run D k-steps ahead, in registers, across segments; the record of
-//     the next segment is read one segment ahead.
+//     the next segment is read one segment ahead, the first with the problem's,
+//     and the steps are counted while the first loads run (T3.R of chi = 512
+//     13.4 -> 12.3 us).
 // Rows and columns past the block read its last one (their results are not
 // stored); k past the segment reads its last and is replaced by zero.
 //
@@ -300,6 +302,7 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
   }
   const GemmTile t = tiles[blockIdx.x - hb];
   if (t.prob < 0) return;   // padding of the per-XCD tile lists
+  GemmSeg nxt = segs[t.seg];   // the first one, read beside the problem
   const GemmProb p = probs[t.prob];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -321,7 +324,6 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
   int64_t ldb = 0;
   const BST_G TA* pa[EA];
   const BST_G double* pb[EB];
-  GemmSeg nxt{};
   int a_buf = -1, b_buf = -1;
   const BST_G TA* A = nullptr;
   const BST_G double* B = nullptr;
@@ -463,15 +465,14 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
     }
   };
 
-  // k-steps of the tile
-  int steps = 0;
-  for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
-  if (steps > 0) {
-    nxt = segs[p.seg_begin];
+  if (p.seg_count > 0) {
     begin();
 #pragma unroll
     for (int d = 0; d < D; ++d)
-      if (d < steps) fetch(ra[d], rb[d], kv[d]);
+      if (ls < p.seg_count) fetch(ra[d], rb[d], kv[d]);
+    // k-steps of the tile, counted while the first of them load
+    int steps = 0;
+    for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
     stage(0, ra[0], rb[0], kv[0]);
     __syncthreads();
     // step u computes from LDS, step u + 1 is staged, step u + D is loaded

@@ -281,6 +281,7 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_planes_wave_kernel(const
   constexpr int BK = 32, D = NP == 2 ? 4 : 3;
   const GemmTile t = tiles[blockIdx.x];
   if (t.prob < 0) return;   // padding of the per-XCD tile lists
+  GemmSeg nxt = segs[t.seg];   // the first one, read beside the problem
   const GemmProb p = probs[t.prob];
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -290,7 +291,6 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_planes_wave_kernel(const
   flt4 acc = flt4{0, 0, 0, 0};
   // load cursor: segment ls at k = lk; rows past the block read its last one
   int ls = 0, lk = 0, lK = 0, a_buf = -1, b_buf = -1;
-  GemmSeg nxt{};
   const BST_G unsigned short *A = nullptr, *B = nullptr, *pa = nullptr, *pb = nullptr;
   const int64_t ar = min(m0 + l16, p.M - 1), br = min(n0 + l16, p.N - 1);
   auto begin = [&]() {   // the segment in nxt becomes current
@@ -347,14 +347,14 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_planes_wave_kernel(const
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
   };
-  int steps = 0;
-  for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
-  if (steps > 0) {
-    nxt = segs[p.seg_begin];
+  if (p.seg_count > 0) {
     begin();
 #pragma unroll
     for (int d = 0; d < D; ++d)
-      if (d < steps) fetch(ra[d], rb[d], kv[d]);
+      if (ls < p.seg_count) fetch(ra[d], rb[d], kv[d]);
+    // counted while the first of them load
+    int steps = 0;
+    for (int q = 0; q < p.seg_count; ++q) steps += (segs[p.seg_begin + q].K + BK - 1) / BK;
     for (int u0 = 0; u0 < steps; u0 += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {

@@ -1296,11 +1296,12 @@ static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
       if (count[i] + q.count <= cap && (x < 0 || load[i] < load[x])) x = i;
     load[x] += q.cost;
     const auto& p = probs[q.prob];
+    const int32_t seg = p.seg_count > 0 ? p.seg_begin : 0;
     const int64_t nn = (p.N + bn - 1) / bn, last = kXcds * (count[x] + q.count - 1) + x;
     if ((int64_t)out.size() <= last) out.resize((size_t)last + 1, GemmTile{-1, 0, 0, 0});
     int64_t m = q.first / nn, n = q.first % nn;
     for (int64_t e = 0; e < q.count; ++e) {
-      out[(size_t)(kXcds * (count[x] + e) + x)] = {q.prob, (int32_t)(m * bm), (int32_t)(n * bn), 0};
+      out[(size_t)(kXcds * (count[x] + e) + x)] = {q.prob, (int32_t)(m * bm), (int32_t)(n * bn), seg};
       if (++n == nn) {
         n = 0;
         ++m;
@@ -1690,6 +1691,7 @@ void finalize(PlanData& P) {
     switch (st.kind) {
       case StepKind::Gemm: {
         st.off0 = put(P.blob, st.probs);
+        if (st.segs.empty()) st.segs.push_back(GemmSeg{});   // (kernels read a tile's first before its count)
         st.off1 = put(P.blob, st.segs);
         if (!st.segs_cplx.empty()) st.off4 = put(P.blob, st.segs_cplx);
         st.tile_lists.clear();
@@ -1725,6 +1727,7 @@ void finalize(PlanData& P) {
             reserve += 2 * list_bytes(st.probs, 32, 32) + list_bytes(st.probs, 64, 32);
         }
         if (st.has_alt) {
+          if (st.segs_alt.empty()) st.segs_alt.push_back(GemmSeg{});
           st.off2 = put(P.blob, st.segs_alt);
           st.off3 = put(P.blob, st.probs_alt);
           st.off5 = put(P.blob, st.rowmap);
