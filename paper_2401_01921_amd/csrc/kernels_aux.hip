@@ -21,8 +21,10 @@ typedef double dbl2v __attribute__((ext_vector_type(2)));
 // consecutive output positions (input rows) through LDS rows padded by one
 // element.  Bound by memory; 701 x 451 x 613 in seven sectors per leg, cab: 56.9
 // us with 8-byte accesses at odd addresses and a bounds check around each load,
-// 42.2 with 16-byte ones, 32.3 (5.3 TB/s) with a lane's eight loads all in
-// flight; bac (row copies): 70.9 -> 37.4 us.
+// 42.2 with 16-byte ones, 32.3 with a lane's eight loads all in flight, 30.5 (5.6
+// TB/s) with loads that stay in the caches, where the next tile finds the rest of
+// a line; bac (row copies): 70.9 -> 37.4 us.  1.23 GiB of 150^3 blocks, cab: 606,
+// 637 with non-temporal loads, 577 without.
 template <int TX>
 __device__ __forceinline__ void permute_tile(const PermJob& j, const PermWork& w, const BST_G double* __restrict__ in,
                                              BST_G double* __restrict__ out, double* lds) {
@@ -48,7 +50,7 @@ __device__ __forceinline__ void permute_tile(const PermJob& j, const PermWork& w
   for (int k = 0; k < G; ++k) {
     const int e = tid + 256 * k;
     const int gy = min(w.t0 + e / (TX / 2), np - 1), gx = min(w.t1 + 2 * (e % (TX / 2)), nl - 2);
-    v[k] = __builtin_nontemporal_load(reinterpret_cast<const BST_G dbl2u*>(in + ib + gy * isp + gx));
+    v[k] = *reinterpret_cast<const BST_G dbl2u*>(in + ib + gy * isp + gx);
   }
 #pragma unroll
   for (int k = 0; k < G; ++k) {
