@@ -87,6 +87,18 @@ static const TileShape* list_shape(const PlanData& P, const Step& st, bst_precis
   return &gemm_tile_shapes(form)[default_tile(st, form)];
 }
 
+void build_lists(PlanData& P) {
+  for (auto& st : P.steps) {
+    if (st.kind != StepKind::Gemm || !step_runs(P, st, P.prec, false)) continue;
+    const bool planes = uses_planes(P, P.prec) && st.has_alt;
+    const TileShape* sh = list_shape(P, st, P.prec);
+    if (!planes && shares_some(st, st.fixed_fp64 ? BST_FP64 : P.prec)) {
+      tile_list(P, st, false, 32, 32, kSharedProbs);
+      tile_list(P, st, false, sh->bm, sh->bn, kOtherProbs);
+    } else if (sh) tile_list(P, st, planes, sh->bm, sh->bn);
+  }
+}
+
 void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws, hipStream_t s) {
   if (!ws) fail(BST_E_INVALID, "null workspace");
   if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) fail(BST_E_INVALID, "workspace must be 256-byte aligned");
@@ -97,16 +109,7 @@ void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws,
     auto it = g_ws_owner.find(ws);
     need_blob = (it == g_ws_owner.end() || it->second != P.id || P.uploaded_ws != ws);
   }
-  // tile lists this run needs, so that one upload takes them all
-  for (auto& st : P.steps) {
-    if (st.kind != StepKind::Gemm || !step_runs(P, st, P.prec, false)) continue;
-    const bool planes = uses_planes(P, P.prec) && st.has_alt;
-    const TileShape* sh = list_shape(P, st, P.prec);
-    if (!planes && shares_some(st, st.fixed_fp64 ? BST_FP64 : P.prec)) {
-      tile_list(P, st, false, 32, 32, kSharedProbs);
-      tile_list(P, st, false, sh->bm, sh->bn, kOtherProbs);
-    } else if (sh) tile_list(P, st, planes, sh->bm, sh->bn);
-  }
+  build_lists(P);   // so that one upload takes them all
   if (need_blob) {
     P.blob_uploaded = 0;
     upload_blob(P, ws, s);

@@ -1915,6 +1915,7 @@ void finalize(PlanData& P) {
   P.uploaded_ws = nullptr;
   P.last_ptrs.clear();
   P.id = g_plan_id++;
+  build_lists(P);
 }
 
 }  // namespace bst
@@ -2136,6 +2137,7 @@ bst_status bst_plan_set_precision(bst_plan* p, bst_precision prec) {
   if (!p) fail(BST_E_INVALID, "null plan");
   if (prec < BST_FP64 || prec > BST_BF16X6) fail(BST_E_INVALID, "unknown precision");
   p->p.prec = prec;
+  if (p->p.finalized) build_lists(p->p);
   BST_CATCH
 }
 

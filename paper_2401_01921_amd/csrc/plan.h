@@ -181,6 +181,9 @@ void finalize(PlanData& p);
 // Step::shared, or the others.
 enum ProbPart { kAllProbs, kSharedProbs, kOtherProbs };
 std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, int bn, int part = kAllProbs);
+// The lists that a run in the plan's form needs: made with the plan and with a
+// change of its form, so that a first run does not build them.
+void build_lists(PlanData& P);
 // Puts blob bytes that ws does not hold yet there.
 void upload_blob(PlanData& P, void* ws, hipStream_t s);
 // Host bytes to device memory by a copy that is waited for.
