@@ -117,6 +117,8 @@ void* prepare_ws(PlanData& P, const void* const* in, void* const* out, void* ws,
     g_ws_owner[ws] = P.id;
     P.uploaded_ws = ws;
     P.last_ptrs.clear();
+  } else {
+    upload_blob(P, ws, s);   // lists made since
   }
   if (ptrs != P.last_ptrs) {
     upload_table(P, ptrs, ws, P.ws_ptr_off, s);

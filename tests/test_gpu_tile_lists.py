@@ -73,3 +73,25 @@ def test_form_first_used_under_a_capture():
     out.fill_(float("nan"))
     plan.execute(ins, [out], ws)
     assert np.array_equal(host(out), want)
+
+
+def test_form_changed_between_graph_replays():
+    """The plan's own graph: a form first used after the tables went up."""
+    specs, O = heff_operands(2, chi=96, qmax=4)
+    T, plan = lib_heff(specs, "fp64")
+    ins = [dev(O[n].data) for n in ("L", "W1", "W2", "R", "psi")]
+    ws = bst.workspace(plan.workspace_bytes)
+    out = torch.empty(O["psi"].numel, dtype=torch.float64, device=DEV)
+    for prec in ("fp64", "fp32", "bf16x3", "fp64"):
+        plan.use_graph(False)
+        plan.set_precision(prec)
+        fresh = lib_heff(specs, prec)[1]
+        fresh.execute(ins, [out], bst.workspace(fresh.workspace_bytes))
+        want = host(out)
+        plan.use_graph(True)
+        for rep in range(3):
+            out.fill_(float("nan"))
+            plan.execute(ins, [out], ws)
+            torch.cuda.synchronize()
+            assert torch.randn(1000, device=DEV).sum().isfinite().item()   # eager work between replays
+            assert np.array_equal(host(out), want), (prec, rep)
