@@ -3,11 +3,17 @@
 // A sector's tall matrix X (p x r, p >= r) goes through three kernels:
 //
 // 1. svd_panel_kernel / svd_trail_kernel: the rows of X, ordered by falling
-//    norm, are reduced to lower trapezoidal form by Householder reflections
-//    from the right, X <- X Q, and V <- I Q starts as that orthogonal factor.
-//    Jacobi on X Q needs about half the sweeps of Jacobi on X (Drmac and
-//    Veselic, SIAM J. Matrix Anal. Appl. 2008: the Gram matrix of the
-//    triangular factor is one LR step nearer to diagonal).
+//    norm, and its columns, by falling largest element (P), are reduced to lower trapezoidal form by
+//    Householder reflections from the right, X <- X P Q, and V <- P Q starts as
+//    that orthogonal factor.  Jacobi on X P Q needs about half the sweeps of
+//    Jacobi on X (Drmac and Veselic, SIAM J. Matrix Anal. Appl. 2008: the Gram
+//    matrix of the triangular factor is one LR step nearer to diagonal).  Both
+//    orders count for the small singular values: a reflection leaves an error of
+//    the rounding of its row's large elements in all of them, which a small
+//    column bears only if it comes after the large ones (Cox and Higham, on
+//    Householder QR of row-wise graded matrices, 1998).  24 x 20, columns of 1 to 1e-20 in any order, largest relative
+//    error of a singular value: rows ordered alone 100, both 5e-15, Jacobi on X
+//    itself 2e-15.
 // 2. svd_reg_kernel: one-sided Jacobi with X in registers, one workgroup per
 //    sector.  It logs its rotations.
 // 3. svd_apply_kernel: the logged rotations on the rows of V, which are
@@ -19,7 +25,8 @@
 // round before, now 7 x (46 + 17) us (1) + 2.24 ms (2) + 0.13 ms (3).
 //
 // Layout of a sector in the workspace: p + r rows of ld doubles, the rows of
-// X (sorted) and then those of V; ld is the padded column count N.
+// X (sorted) and then those of V; ld is the padded column count N.  Its part of
+// rowpos: the place of every row of X and the inverse, then of every column.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -85,7 +92,7 @@ __device__ __forceinline__ unsigned long long order_key(double v) {
 // the reflections of rows k0 .. k0 + nref - 1 on all later rows of the range.
 // A sector whose rows of X and V all fit is done in one launch; otherwise its
 // rows come nb at a time and svd_trail_kernel carries the reflections (kept in
-// ubuf) to the rest.  Panel 0 first orders the rows of X by norm.
+// ubuf) to the rest.  Panel 0 first orders the rows and columns of X.
 //
 // A row takes 16 lanes (E column pairs each), so that a sum along it is four
 // moves within them, and a wave four rows at a time.  Wave 0 takes the four
@@ -216,53 +223,87 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
   __shared__ __attribute__((aligned(16))) double lds[kSvdPanelLds / sizeof(double)];
   __shared__ __attribute__((aligned(16))) double ub[2 * kSvdRegMaxCols];
   __shared__ double nrm[kSvdRegMaxRows];
-  __shared__ int inv[kSvdRegMaxRows];
+  __shared__ unsigned long long cmax[kSvdRegMaxCols];
+  __shared__ int inv[kSvdRegMaxRows], cpos[kSvdRegMaxCols];
   double* const X = D + S.x_off;
   const double* const X0 = scratch + S.log_off;                  // as gathered
   double* const ubuf = scratch + S.log_off + (int64_t)p * ld;    // row i: the u of reflection i
   int32_t* const pos = rowpos + S.p_off;   // [0, p): sorted place of a row; [p, 2p): its inverse
+  int32_t* const pos_c = pos + 2 * p;      // the same of the r columns
+  const int l16 = tid & 15;
   if (panel == 0) {
+    // |row|^2 and the largest element of every column
+    constexpr int NC = kSvdRegRows2 / 16;   // columns of a lane, at most
+    static_assert(kSvdRegCols1 <= 16 * NC && kSvdRegMaxRows <= 256, "lanes of a row");
+    for (int c = tid; c < r; c += 1024) cmax[c] = 0ull;
+    __syncthreads();
+    double cm[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) cm[j] = 0.0;
     for (int q = tid >> 4; q < p; q += 64) {
       double a = 0.0;
-      for (int c = tid & 15; c < r; c += 16) {
-        const double v = X0[(int64_t)q * ld + c];
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        if (16 * j >= r) break;
+        const double v = l16 + 16 * j < r ? X0[(int64_t)q * ld + l16 + 16 * j] : 0.0;
         a = fma(v, v, a);
+        cm[j] = fmax(cm[j], fabs(v));
       }
       a = row_sum(a);
-      if ((tid & 15) == 0) nrm[q] = a;
+      if (l16 == 0) nrm[q] = a;
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      if (16 * j >= r) break;
+      if (l16 + 16 * j < r) atomicMax(&cmax[l16 + 16 * j], order_key(cm[j]));
     }
     __syncthreads();
-    // four lanes per row count the rows before it
-    for (int q = tid >> 2; q < p; q += 256) {
-      const unsigned long long k = order_key(nrm[q]);
-      int rank = 0;
-      for (int i = tid & 3; i < p; i += 4) {
-        const unsigned long long w = order_key(nrm[i]);
-        rank += (w > k || (w == k && i < q)) ? 1 : 0;
-      }
-      rank += __shfl_xor(rank, 1, 4);
-      rank += __shfl_xor(rank, 2, 4);
-      if ((tid & 3) == 0) {
-        inv[rank] = q;
-        pos[q] = rank;
-        pos[p + rank] = q;
-      }
+    // four lanes per row (column) count those before it
+    const int q = tid >> 2;
+    const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull, kc = q < r ? cmax[q] : 0ull;
+    int rank = 0, rank_c = 0;
+    for (int i = tid & 3; i < p; i += 4) {
+      const unsigned long long w = order_key(nrm[i]);
+      rank += (w > k || (w == k && i < q)) ? 1 : 0;
+    }
+    for (int i = tid & 3; i < r; i += 4) rank_c += (cmax[i] > kc || (cmax[i] == kc && i < q)) ? 1 : 0;
+    rank += __shfl_xor(rank, 1, 4);
+    rank += __shfl_xor(rank, 2, 4);
+    rank_c += __shfl_xor(rank_c, 1, 4);
+    rank_c += __shfl_xor(rank_c, 2, 4);
+    if ((tid & 3) == 0 && q < p) {
+      inv[rank] = q;
+      pos[q] = rank;
+      pos[p + rank] = q;
+    }
+    if ((tid & 3) == 0 && q < r) {
+      cpos[q] = rank_c;
+      pos_c[q] = rank_c;
+      pos_c[r + rank_c] = q;
     }
     __syncthreads();
   }
   // 16 lanes per row, all of a row's loads at once
   for (int q = tid >> 4; q < rows; q += 64) {
     const int g = k0 + q;
+    const bool unit = panel == 0 && g >= p;   // a row of P
     const double* const src = panel == 0 ? X0 + (int64_t)inv[min(g, p - 1)] * ld : X + (int64_t)g * ld;
+    const int one = unit ? cpos[g - p] : -1;
 #pragma unroll
     for (int j = 0; j < 7; ++j) {
-      const int c = 2 * (tid & 15) + 32 * j;
+      const int c = 2 * l16 + 32 * j;
       if (32 * j >= ldl) break;
       double2 v = *reinterpret_cast<const double2*>(src + min(c, ld - 2));
-      if (g >= p) v = double2{c == g - p ? 1.0 : 0.0, c + 1 == g - p ? 1.0 : 0.0};
+      if (unit) v = double2{c == one ? 1.0 : 0.0, c + 1 == one ? 1.0 : 0.0};
       if (c >= r) v.x = 0.0;
       if (c + 1 >= r) v.y = 0.0;
-      *reinterpret_cast<double2*>(lds + q * ldl + c) = v;
+      double* const row = lds + q * ldl;
+      if (panel == 0 && !unit) {   // each column to its place
+        row[c < r ? cpos[c] : c] = v.x;
+        row[c + 1 < r ? cpos[c + 1] : c + 1] = v.y;
+      } else {
+        *reinterpret_cast<double2*>(row + c) = v;
+      }
     }
   }
   __syncthreads();
@@ -279,28 +320,39 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
 
 // The reflections of one panel on the rows after it (those of X and all of
 // V's), 16 lanes per row as above, two rows per lane group in registers and
-// the panel's u in LDS.  Panel 0 takes the rows of X from the gathered copy in
-// sorted order and starts V from the identity.  Bound: latency of the sum
+// the panel's u in LDS.  Panel 0 takes X from the gathered copy in sorted order
+// (pos: that order, as in the panel kernel) and starts V from P.  Bound: latency of the sum
 // along a row, hidden by the second row and the other waves.
 namespace {
 template <int E>
-__device__ __forceinline__ void trail_rows(const SvdSec& S, double* X, const double* X0, const int32_t* inv,
+__device__ __forceinline__ void trail_rows(const SvdSec& S, double* X, const double* X0, const int32_t* pos,
                                            const double* ul, int panel, int nref, int q0) {
   constexpr int LDL = 32 * E;
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m, ld = S.ld;
   const int l16 = threadIdx.x & 15;
+  const int32_t *const inv = pos + p, *const pos_c = pos + 2 * p;
   double2 x[2][E];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int g = min(q0 + t, p + r - 1);
-    const bool unit = panel == 0 && g >= p;
-    const double* const src = panel > 0 ? X + (int64_t)g * ld : X0 + (int64_t)inv[min(g, p - 1)] * ld;
+    if (panel > 0) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int c = 2 * l16 + 32 * j;
-      const double2 v = *reinterpret_cast<const double2*>(src + min(c, ld - 2));
-      x[t][j].x = unit ? (c == g - p ? 1.0 : 0.0) : c < r ? v.x : 0.0;
-      x[t][j].y = unit ? (c + 1 == g - p ? 1.0 : 0.0) : c + 1 < r ? v.y : 0.0;
+      for (int j = 0; j < E; ++j) {
+        const int c = 2 * l16 + 32 * j;
+        const double2 v = *reinterpret_cast<const double2*>(X + (int64_t)g * ld + min(c, ld - 2));
+        x[t][j] = double2{c < r ? v.x : 0.0, c + 1 < r ? v.y : 0.0};
+      }
+    } else {
+      const bool unit = g >= p;
+      const int one = unit ? pos_c[g - p] : -1;
+      const double* const src = X0 + (int64_t)inv[min(g, p - 1)] * ld;
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        const int c = 2 * l16 + 32 * j;
+        const double v0 = src[pos_c[r + min(c, r - 1)]], v1 = src[pos_c[r + min(c + 1, r - 1)]];
+        x[t][j].x = unit ? (c == one ? 1.0 : 0.0) : c < r ? v0 : 0.0;
+        x[t][j].y = unit ? (c + 1 == one ? 1.0 : 0.0) : c + 1 < r ? v1 : 0.0;
+      }
     }
   }
   for (int i = 0; i < nref; ++i) {
@@ -334,7 +386,7 @@ __global__ __launch_bounds__(256) void svd_trail_kernel(const SvdSec* __restrict
   double* const X = D + S.x_off;
   const double* const X0 = scratch + S.log_off;
   const double* const ubuf = scratch + S.log_off + (int64_t)p * ld;
-  const int32_t* const inv = rowpos + S.p_off + p;
+  const int32_t* const pos = rowpos + S.p_off;
   const int ldl = svd_panel_ld(ld);
   for (int i = threadIdx.x >> 4; i < nref; i += 16) {
     const double* const src = ubuf + (int64_t)(k0 + i) * ld;
@@ -349,10 +401,10 @@ __global__ __launch_bounds__(256) void svd_trail_kernel(const SvdSec* __restrict
   }
   __syncthreads();
   const int q0 = b0 + 2 * (threadIdx.x >> 4);
-  if (ldl == 32) trail_rows<1>(S, X, X0, inv, ul, panel, nref, q0);
-  else if (ldl == 64) trail_rows<2>(S, X, X0, inv, ul, panel, nref, q0);
-  else if (ldl == 128) trail_rows<4>(S, X, X0, inv, ul, panel, nref, q0);
-  else trail_rows<7>(S, X, X0, inv, ul, panel, nref, q0);
+  if (ldl == 32) trail_rows<1>(S, X, X0, pos, ul, panel, nref, q0);
+  else if (ldl == 64) trail_rows<2>(S, X, X0, pos, ul, panel, nref, q0);
+  else if (ldl == 128) trail_rows<4>(S, X, X0, pos, ul, panel, nref, q0);
+  else trail_rows<7>(S, X, X0, pos, ul, panel, nref, q0);
 }
 
 // ---- Jacobi in registers ---------------------------------------------------

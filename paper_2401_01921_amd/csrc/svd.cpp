@@ -215,7 +215,7 @@ void build(SvdPlanData& P) {
       d.log_off = lo;
       lo += (std::max((p + rr) * ld, P.logcap * svd_log_sweep(ld, d.pairs)) + 31) / 32 * 32;
       d.p_off = po;
-      po += 2 * p;
+      po += 2 * (p + rr);
       P.reg.push_back((int32_t)k);
     } else {
       d.x_rs = d.v_rs = 1;

@@ -39,7 +39,7 @@ struct SvdSec {
   int64_t x_off, v_off;
   int64_t s_off;    // r values in the sigma / sorted / perm regions
   int64_t log_off;  // register path: gathered X and reflections, then the rotation log
-  int64_t p_off;    // register path: row order (p places, then their inverse)
+  int64_t p_off;    // register path: row order (p places, then their inverse), then column order (r)
   int32_t m, n;
   int32_t x_rs, x_cs, v_rs, v_cs;
   int32_t path;     // SvdPath
@@ -95,7 +95,7 @@ struct SvdLaunch {
   const double* in;
   double* X;          // X and Vh of every sector
   double* scratch;    // register path: gathered X and reflections, rotation logs
-  int32_t* rowpos;    // register path: row orders
+  int32_t* rowpos;    // register path: row and column orders
   // register path: its sectors, most panels and rows left after a panel (0:
   // every sector in one launch), most columns, logged sweeps, and per sector
   // [sweeps in the log, order reversed since]
