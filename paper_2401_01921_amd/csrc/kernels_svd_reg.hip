@@ -20,9 +20,15 @@
 //    independent of each other and spread over the device.
 //
 // Measured, kernels only: a two-site spin-1/2 state at chi = 256 (15 sectors
-// to 52 x 52), 1.62 ms in the one-workgroup LDS kernel before, now 35 us (1) +
-// 170 us (2) + 27 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
-// round before, now 7 x (46 + 17) us (1) + 2.24 ms (2) + 0.13 ms (3).
+// to 52 x 52), 1.62 ms in the one-workgroup LDS kernel before, now 36 us (1) +
+// 175 us (2) + 27 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
+// round before, now 7 x (45 + 13) us (1) + 2.24 ms (2) + 0.13 ms (3).
+//
+// The squares of a row or column have to stay inside float64's range: below it a
+// reflection is not orthogonal, and V with it (entries of 1e-160: |V V^T - 1| =
+// 1e-3).  A sector whose largest element is outside 2^-128 .. 2^128 is worked on
+// times a power of two (exact), and so is the reflection of a row that is tiny
+// even then.
 //
 // Layout of a sector in the workspace: p + r rows of ld doubles, the rows of
 // X (sorted) and then those of V; ld is the padded column count N.  Its part of
@@ -129,7 +135,8 @@ __device__ __forceinline__ void reflect(double2 (&x)[E], const double2 (&u)[E]) 
   }
 }
 // The reflection H = I - u u^T, |u|^2 = 2, that takes row x from column c0 on
-// to a multiple of e_c0: u, and x as it leaves it.  A zero row gives u = 0.
+// to a multiple of e_c0: u, and x as it leaves it.  A zero row gives u = 0; u of
+// one whose square would lose digits comes from the row times 2^800.
 template <int E>
 __device__ __forceinline__ void reflector(double2 (&x)[E], double2 (&u)[E], double x0, int c0, int l16) {
   double q0 = 0.0, q1 = 0.0;
@@ -145,8 +152,26 @@ __device__ __forceinline__ void reflector(double2 (&x)[E], double2 (&u)[E], doub
   const bool zero = q == 0.0;
   const double nrm = q * rsqrt_step(q);
   const double s = copysign(nrm, x0);
-  const double sc = zero ? 0.0 : rsqrt_step(nrm * (nrm + fabs(x0)));
-  const double diag = zero ? x0 : -s, head = zero ? 0.0 : (x0 + s) * sc;
+  double sc = zero ? 0.0 : rsqrt_step(nrm * (nrm + fabs(x0)));
+  double diag = zero ? 0.0 : -s, head = zero ? 0.0 : (x0 + s) * sc;
+  // (decided on last, off the chain; 16 lanes agree)
+  if (__builtin_expect(__ballot(q < 0x1p-900) != 0ull, 0) && q < 0x1p-900) {
+    x0 *= 0x1p800;
+    q0 = q1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      u[j].x *= 0x1p800;
+      u[j].y *= 0x1p800;
+      q0 = fma(u[j].x, u[j].x, q0);
+      q1 = fma(u[j].y, u[j].y, q1);
+    }
+    const double qq = row_sum(q0 + q1), n = qq * rsqrt_step(qq), ss = copysign(n, x0);
+    if (qq > 0.0) {
+      sc = rsqrt_step(n * (n + fabs(x0)));
+      diag = -ss * 0x1p-800;
+      head = (x0 + ss) * sc;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     const int c = 2 * l16 + 32 * j;
@@ -210,7 +235,8 @@ __device__ __forceinline__ void panel_rows(double* lds, double* ub, double* ubuf
 
 __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restrict__ secs,
                                                          const int32_t* __restrict__ list, double* D,
-                                                         double* scratch, int32_t* rowpos, int panel) {
+                                                         double* scratch, int32_t* rowpos, int32_t* ctrl,
+                                                         int panel) {
   const SvdSec S = secs[list[blockIdx.x]];
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m;
   const int k0 = panel * S.nb;
@@ -231,6 +257,7 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
   int32_t* const pos = rowpos + S.p_off;   // [0, p): sorted place of a row; [p, 2p): its inverse
   int32_t* const pos_c = pos + 2 * p;      // the same of the r columns
   const int l16 = tid & 15;
+  int ex = 0;   // X is held times 2^-ex
   if (panel == 0) {
     // |row|^2 and the largest element of every column
     constexpr int NC = kSvdRegRows2 / 16;   // columns of a lane, at most
@@ -241,13 +268,15 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
 #pragma unroll
     for (int j = 0; j < NC; ++j) cm[j] = 0.0;
     for (int q = tid >> 4; q < p; q += 64) {
-      double a = 0.0;
+      double a = 0.0, v[NC];
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        if (16 * j < r) v[j] = X0[(int64_t)q * ld + min(l16 + 16 * j, r - 1)];
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
         if (16 * j >= r) break;
-        const double v = l16 + 16 * j < r ? X0[(int64_t)q * ld + l16 + 16 * j] : 0.0;
-        a = fma(v, v, a);
-        cm[j] = fmax(cm[j], fabs(v));
+        a = l16 + 16 * j < r ? fma(v[j], v[j], a) : a;
+        cm[j] = fmax(cm[j], fabs(v[j]));
       }
       a = row_sum(a);
       if (l16 == 0) nrm[q] = a;
@@ -260,13 +289,35 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
     __syncthreads();
     // four lanes per row (column) count those before it
     const int q = tid >> 2;
-    const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull, kc = q < r ? cmax[q] : 0ull;
+    const unsigned long long kc = q < r ? cmax[q] : 0ull;
     int rank = 0, rank_c = 0;
+    unsigned long long top = 0ull;   // the largest element, in every lane
+    for (int i = tid & 3; i < r; i += 4) {
+      rank_c += (cmax[i] > kc || (cmax[i] == kc && i < q)) ? 1 : 0;
+      top = max(top, cmax[i]);
+    }
+    top = max(top, (unsigned long long)__shfl_xor(top, 1, 4));
+    top = max(top, (unsigned long long)__shfl_xor(top, 2, 4));
+    const double t = __longlong_as_double((long long)top);
+    if (t > 0.0 && t <= DBL_MAX && (t < 0x1p-128 || t > 0x1p128)) {
+      ex = ilogb(t);
+      for (int i = tid >> 4; i < p; i += 64) {
+        double a = 0.0;
+        for (int c = l16; c < r; c += 16) {
+          const double v = ldexp(X0[(int64_t)i * ld + c], -ex);
+          a = fma(v, v, a);
+        }
+        a = row_sum(a);
+        if (l16 == 0) nrm[i] = a;
+      }
+      __syncthreads();
+    }
+    if (tid == 0) ctrl[kSvdCtrl * blockIdx.x + 2] = ex;
+    const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull;
     for (int i = tid & 3; i < p; i += 4) {
       const unsigned long long w = order_key(nrm[i]);
       rank += (w > k || (w == k && i < q)) ? 1 : 0;
     }
-    for (int i = tid & 3; i < r; i += 4) rank_c += (cmax[i] > kc || (cmax[i] == kc && i < q)) ? 1 : 0;
     rank += __shfl_xor(rank, 1, 4);
     rank += __shfl_xor(rank, 2, 4);
     rank_c += __shfl_xor(rank_c, 1, 4);
@@ -289,11 +340,16 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
     const bool unit = panel == 0 && g >= p;   // a row of P
     const double* const src = panel == 0 ? X0 + (int64_t)inv[min(g, p - 1)] * ld : X + (int64_t)g * ld;
     const int one = unit ? cpos[g - p] : -1;
+    double2 x[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+      if (32 * j < ldl) x[j] = *reinterpret_cast<const double2*>(src + min(2 * l16 + 32 * j, ld - 2));
 #pragma unroll
     for (int j = 0; j < 7; ++j) {
       const int c = 2 * l16 + 32 * j;
       if (32 * j >= ldl) break;
-      double2 v = *reinterpret_cast<const double2*>(src + min(c, ld - 2));
+      double2 v = x[j];
+      if (ex != 0) v = double2{ldexp(v.x, -ex), ldexp(v.y, -ex)};
       if (unit) v = double2{c == one ? 1.0 : 0.0, c + 1 == one ? 1.0 : 0.0};
       if (c >= r) v.x = 0.0;
       if (c + 1 >= r) v.y = 0.0;
@@ -326,7 +382,7 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
 namespace {
 template <int E>
 __device__ __forceinline__ void trail_rows(const SvdSec& S, double* X, const double* X0, const int32_t* pos,
-                                           const double* ul, int panel, int nref, int q0) {
+                                           int ex, const double* ul, int panel, int nref, int q0) {
   constexpr int LDL = 32 * E;
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m, ld = S.ld;
   const int l16 = threadIdx.x & 15;
@@ -349,7 +405,11 @@ __device__ __forceinline__ void trail_rows(const SvdSec& S, double* X, const dou
 #pragma unroll
       for (int j = 0; j < E; ++j) {
         const int c = 2 * l16 + 32 * j;
-        const double v0 = src[pos_c[r + min(c, r - 1)]], v1 = src[pos_c[r + min(c + 1, r - 1)]];
+        double v0 = src[pos_c[r + min(c, r - 1)]], v1 = src[pos_c[r + min(c + 1, r - 1)]];
+        if (ex != 0) {
+          v0 = ldexp(v0, -ex);
+          v1 = ldexp(v1, -ex);
+        }
         x[t][j].x = unit ? (c == one ? 1.0 : 0.0) : c < r ? v0 : 0.0;
         x[t][j].y = unit ? (c + 1 == one ? 1.0 : 0.0) : c + 1 < r ? v1 : 0.0;
       }
@@ -374,7 +434,8 @@ __device__ __forceinline__ void trail_rows(const SvdSec& S, double* X, const dou
 
 __global__ __launch_bounds__(256) void svd_trail_kernel(const SvdSec* __restrict__ secs,
                                                         const int32_t* __restrict__ list, double* D,
-                                                        const double* scratch, const int32_t* rowpos, int panel) {
+                                                        const double* scratch, const int32_t* rowpos,
+                                                        const int32_t* ctrl, int panel) {
   __shared__ __attribute__((aligned(16))) double ul[kSvdPanelRefl * 32 * 7];
   const SvdSec S = secs[list[blockIdx.y]];
   const int p = S.m >= S.n ? S.m : S.n, r = S.m >= S.n ? S.n : S.m;
@@ -387,6 +448,7 @@ __global__ __launch_bounds__(256) void svd_trail_kernel(const SvdSec* __restrict
   const double* const X0 = scratch + S.log_off;
   const double* const ubuf = scratch + S.log_off + (int64_t)p * ld;
   const int32_t* const pos = rowpos + S.p_off;
+  const int ex = ctrl[kSvdCtrl * blockIdx.y + 2];
   const int ldl = svd_panel_ld(ld);
   for (int i = threadIdx.x >> 4; i < nref; i += 16) {
     const double* const src = ubuf + (int64_t)(k0 + i) * ld;
@@ -401,10 +463,10 @@ __global__ __launch_bounds__(256) void svd_trail_kernel(const SvdSec* __restrict
   }
   __syncthreads();
   const int q0 = b0 + 2 * (threadIdx.x >> 4);
-  if (ldl == 32) trail_rows<1>(S, X, X0, pos, ul, panel, nref, q0);
-  else if (ldl == 64) trail_rows<2>(S, X, X0, pos, ul, panel, nref, q0);
-  else if (ldl == 128) trail_rows<4>(S, X, X0, pos, ul, panel, nref, q0);
-  else trail_rows<7>(S, X, X0, pos, ul, panel, nref, q0);
+  if (ldl == 32) trail_rows<1>(S, X, X0, pos, ex, ul, panel, nref, q0);
+  else if (ldl == 64) trail_rows<2>(S, X, X0, pos, ex, ul, panel, nref, q0);
+  else if (ldl == 128) trail_rows<4>(S, X, X0, pos, ex, ul, panel, nref, q0);
+  else trail_rows<7>(S, X, X0, pos, ex, ul, panel, nref, q0);
 }
 
 // ---- Jacobi in registers ---------------------------------------------------
@@ -785,6 +847,13 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
     }
   }
   norms();
+  const int ex = __builtin_amdgcn_readfirstlane(ctrl[2]);   // X back to its own scale
+  if (ex != 0) {
+#pragma unroll
+    for (int j = 0; j < 2 * U; ++j)
+#pragma unroll
+      for (int i = 0; i < RW; ++i) v[j][i] = ldexp(v[j][i], ex);
+  }
   store_rows<U, RW>(v, X, wave * RW, p, N, k, false);
   // zero columns that only pad: r .. N - 1 at the start, mirrored with every sweep
   const int pad = N - r, lo = turns & 1 ? pad : 0, hi = turns & 1 ? N : r;
@@ -799,8 +868,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
       rank += (w > key || (w == key && i < c)) ? 1 : 0;
     }
     perm[rank] = c;
-    sorted[rank] = sg[c];
-    sig[c - lo] = sg[c];
+    sorted[rank] = sig[c - lo] = ldexp(sg[c], ex);
   }
   if (tid == 0) {
     *sweeps = sw;
@@ -825,7 +893,7 @@ __global__ __launch_bounds__(64 * kSvdRegWaves) void svd_reg_kernel(const SvdSec
   auto go = [&](auto u, auto rw, auto w) {
     constexpr int W = decltype(w)::value;
     if (W < kSvdRegWaves && threadIdx.x >= 64 * W) return;
-    jacobi_reg<decltype(u)::value, decltype(rw)::value, W>(sh, X, p, r, S.ld, log, logcap, ctrl + 2 * blockIdx.x,
+    jacobi_reg<decltype(u)::value, decltype(rw)::value, W>(sh, X, p, r, S.ld, log, logcap, ctrl + kSvdCtrl * blockIdx.x,
                                                            sweeps + id, sig + S.s_off, sorted + S.s_off,
                                                            perm + S.s_off);
   };
@@ -861,8 +929,8 @@ __global__ __launch_bounds__(256) void svd_apply_kernel(const SvdSec* __restrict
   if (q >= r) return;
   double* const V = D + S.x_off + (int64_t)p * S.ld;
   const double* const log = scratch + S.log_off;
-  const int sweeps = ctrl[2 * blockIdx.y];
-  const bool rev = ctrl[2 * blockIdx.y + 1] != 0;
+  const int sweeps = ctrl[kSvdCtrl * blockIdx.y];
+  const bool rev = ctrl[kSvdCtrl * blockIdx.y + 1] != 0;
   if (S.pairs == 1)
     apply_log<1, kSvdApplyRows>(V, q, r, S.ld, lane, log, sweeps, rev);
   else
@@ -874,10 +942,11 @@ hipError_t launch_svd_reg(const SvdLaunch& l, hipStream_t s) {
   if (l.nreg > 65535 || l.logcap < 1) return hipErrorInvalidValue;
   const unsigned n = (unsigned)l.nreg;
   for (int q = 0; q < l.panels; ++q) {
-    hipLaunchKernelGGL(svd_panel_kernel, dim3(n), dim3(1024), 0, s, l.secs, l.reg, l.X, l.scratch, l.rowpos, q);
+    hipLaunchKernelGGL(svd_panel_kernel, dim3(n), dim3(1024), 0, s, l.secs, l.reg, l.X, l.scratch, l.rowpos,
+                       l.ctrl, q);
     if (l.trail_rows > 0)
       hipLaunchKernelGGL(svd_trail_kernel, dim3((unsigned)((l.trail_rows + kSvdTrailRows - 1) / kSvdTrailRows), n), dim3(256), 0, s, l.secs,
-                         l.reg, l.X, l.scratch, l.rowpos, q);
+                         l.reg, l.X, l.scratch, l.rowpos, l.ctrl, q);
   }
   hipLaunchKernelGGL(svd_reg_kernel, dim3(n), dim3(64 * kSvdRegWaves), 0, s, l.secs, l.reg, l.X, l.scratch, l.logcap,
                      l.ctrl, l.sweeps, l.sig, l.sorted, l.perm);

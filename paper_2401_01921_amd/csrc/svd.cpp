@@ -294,7 +294,7 @@ void build(SvdPlanData& P) {
   P.ws_x = take(sizeof(double) * (size_t)xo);
   P.ws_scratch = take(sizeof(double) * (size_t)lo);
   P.ws_rowpos = take(sizeof(int32_t) * (size_t)po);
-  P.ws_ctrl = take(sizeof(int32_t) * 2 * P.reg.size());
+  P.ws_ctrl = take(sizeof(int32_t) * kSvdCtrl * P.reg.size());
   P.ws_sig = take(sizeof(double) * (size_t)so);
   P.ws_sorted = take(sizeof(double) * (size_t)so);
   P.ws_perm = take(sizeof(int32_t) * (size_t)so);

@@ -78,6 +78,7 @@ constexpr int kSvdRegRows2 = 208;                       // two
 constexpr int kSvdPanelLds = 144 * 1024;   // rows of a Householder panel
 constexpr int kSvdLogSweeps = 12;          // logged before V is updated in between (5 to 10 are usual)
 constexpr int kSvdPanelRefl = 32;          // reflections of a panel of a sector that does not fit whole
+constexpr int kSvdCtrl = 4;                // words of a sector's control record
 constexpr int kSvdTrailRows = 32;          // rows of one workgroup after it
 // row stride of a panel in LDS: whole groups of 16 lanes' pairs, a count that
 // the kernels are built for
@@ -98,7 +99,7 @@ struct SvdLaunch {
   int32_t* rowpos;    // register path: row and column orders
   // register path: its sectors, most panels and rows left after a panel (0:
   // every sector in one launch), most columns, logged sweeps, and per sector
-  // [sweeps in the log, order reversed since]
+  // [sweeps in the log, order reversed since, binary exponent taken out of X, -]
   const int32_t* reg;
   int32_t nreg, panels;
   int64_t trail_rows, reg_cols;

@@ -17,12 +17,14 @@ def _gpu():
     require_gpu()
 
 
-def _factors(O, keep=1 << 30):
-    """U, V^dagger and the singular values of every sector as matrices."""
+def _factors(O):
+    """U, V^dagger and the singular values of every sector as matrices, all of
+    them (a truncation would not keep a NaN)."""
     plan = bst.Svd(bst.Tensor(O.labels, O.legs), 1)
     ws = bst.workspace(plan.workspace_bytes)
     plan.execute(dev(O.data), ws)
-    kept, _ = plan.truncate(keep, 0.0, None, ws)
+    plan.truncate(1 << 30, 0.0, None, ws)
+    kept = [min(plan.sector(k)[1:]) for k in range(plan.nsectors)]
     Ut, Vt = plan.factors(kept, "m")
     U, V, S = (torch.full((n,), np.nan, dtype=torch.float64, device="cuda") for n in (Ut.numel, Vt.numel, sum(kept)))
     plan.write(kept, 0, U, S, V, ws)
