@@ -243,7 +243,7 @@ struct GemmLaunch {
   void* const* ptrs;
   int64_t ntiles;
   HCoefLaunch coef{};          // float64 / float32 staged tiles: computed beside the GEMM
-  bool b_complex = false;      // the same: segs read a complex B, not its expanded copy
+  int b_complex = -1;          // the same: slot of the complex B, read instead of its expanded copy
 };
 hipError_t launch_gemm(const GemmLaunch& g, hipStream_t s);
 hipError_t launch_gemm_direct(const GemmLaunch& g, int bm, int bn, hipStream_t s);

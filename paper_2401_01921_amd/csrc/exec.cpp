@@ -31,7 +31,10 @@ std::vector<void*> build_ptrs(PlanData& P, const void* const* in, void* const* o
     if ((!out || !out[k]) && !empty) fail(BST_E_INVALID, "null output pointer " + std::to_string(k));
     ptrs[P.out_slots[k]] = out ? out[k] : nullptr;
   }
-  for (const auto& ib : P.internals) ptrs[ib.slot] = static_cast<char*>(ws) + ib.ws_off;
+  for (const auto& ib : P.internals) {
+    ptrs[ib.slot] = static_cast<char*>(ws) + ib.ws_off;
+    if (ib.also >= 0) ptrs[ib.also] = ptrs[ib.slot];
+  }
   return ptrs;
 }
 
@@ -265,8 +268,8 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
         g.tiles = reinterpret_cast<const GemmTile*>(blob + list.first);
         g.ntiles = list.second;
         g.probs = reinterpret_cast<const GemmProb*>(blob + st.off0);
-        g.b_complex = reads_complex(st, prec);
-        g.segs = reinterpret_cast<const GemmSeg*>(blob + (g.b_complex ? st.off4 : st.off1));
+        g.b_complex = reads_complex(st, prec) ? st.cplx_slot : -1;
+        g.segs = reinterpret_cast<const GemmSeg*>(blob + st.off1);
         g.ptrs = dptrs;
         g.coef = prep.coef;
         prep.coef = HCoefLaunch{};
@@ -318,7 +321,7 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
           f.nwg = st.fused.nwg;
           f.ptrs = dptrs;
           f.coef = reinterpret_cast<const float*>(wsb + P.ws_coef32_off);
-          f.planes = reinterpret_cast<const HPlane*>(blob + st.fused_planes_off);
+          f.planes = reinterpret_cast<const HPlane*>(blob + st.off4);
           f.out_slot = st.tasks_alt.empty() ? 11 : st.tasks_alt[0].out_buf;
           e = launch_lh_fused(f, s);
           break;
@@ -675,7 +678,7 @@ bst_status bst_plan_autotune(bst_plan* p, const void* const* in, void* const* ou
       int best_i = pl ? planes_tile(st, form) : default_tile(st, f);
       for (size_t i = 0; i < shapes.size(); ++i) {
         // a complex B is expanded only for the direct kernels, which costs as much as the GEMM
-        if (shapes[i].direct == 1 && !st.segs_cplx.empty()) continue;
+        if (shapes[i].direct == 1 && st.cplx_slot >= 0) continue;
         st.tile_choice[key] = (int)i;
         run_steps_impl(P, ws, table, P.prec, s, false, (int)k, nullptr);
         const double ms = time_runs((int)k);

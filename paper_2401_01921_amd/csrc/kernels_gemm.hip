@@ -277,8 +277,8 @@ template <int FORM, typename TA, typename TC, int BL, int BM, int BN, int D>
 __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmTile* __restrict__ tiles,
                                                                      const GemmProb* __restrict__ probs,
                                                                      const GemmSeg* __restrict__ segs,
-                                                                     void* const* __restrict__ ptrs, int hb,
-                                                                     HCoefLaunch coef) {
+                                                                     void* const* __restrict__ ptrs, int bslot,
+                                                                     int hb, HCoefLaunch coef) {
   constexpr bool F64 = (FORM == BST_FP64), TRANSB = (BL == kBTrans), CPLX = (BL == kBComplex);
   constexpr int BK = 16, WM = BM / 2, WN = BN / 2, SM = WM / 16, SN = WN / 16;
   constexpr int EA = BM / 32, EB = BN / 32;               // pairs per lane and k-step
@@ -332,7 +332,9 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
   auto begin = [&]() {   // the segment in nxt becomes current
     const GemmSeg g = nxt;
     if (g.a_buf != a_buf) A = (const BST_G TA*)(ptrs[a_buf = g.a_buf]);
-    if (g.b_buf != b_buf) B = (const BST_G double*)(ptrs[b_buf = g.b_buf]);
+    const int gb = CPLX ? bslot : g.b_buf;
+    const int64_t b_off = g.b_off >> CPLX;
+    if (gb != b_buf) B = (const BST_G double*)(ptrs[b_buf = gb]);
     if (ls + 1 < p.seg_count) nxt = segs[p.seg_begin + ls + 1];
     lk = 0;
     lK = g.K;
@@ -342,9 +344,9 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_block_kernel(const GemmT
 #pragma unroll
     for (int e = 0; e < EB; ++e) {
       if constexpr (TRANSB)
-        pb[e] = B + g.b_off + (int64_t)min(n0 + bn + 32 * e, p.N - 1) * g.ldb + bk;
+        pb[e] = B + b_off + (int64_t)min(n0 + bn + 32 * e, p.N - 1) * g.ldb + bk;
       else
-        pb[e] = B + g.b_off + (int64_t)((bk + KB * e) >> CPLX) * g.ldb + min(n0 + bn, p.N - 1);
+        pb[e] = B + b_off + (int64_t)((bk + KB * e) >> CPLX) * g.ldb + min(n0 + bn, p.N - 1);
     }
   };
   TA2 ra[D][EA];
@@ -527,7 +529,7 @@ template <int BL>
 __global__ __launch_bounds__(256, kMfmaWaves) void gemm_ksplit_kernel(const GemmTile* __restrict__ tiles,
                                                                       const GemmProb* __restrict__ probs,
                                                                       const GemmSeg* __restrict__ segs,
-                                                                      void* const* __restrict__ ptrs) {
+                                                                      void* const* __restrict__ ptrs, int bslot) {
   constexpr int BK = 16, D = 2;
   typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
   __shared__ double sum[4][32 * 33];
@@ -577,7 +579,8 @@ __global__ __launch_bounds__(256, kMfmaWaves) void gemm_ksplit_kernel(const Gemm
   auto begin = [&](int k0) {   // the segment in nxt becomes current, from k0 on
     const GemmSeg g = nxt;
     const BST_G double* A = (const BST_G double*)(ptrs[g.a_buf]) + g.a_off + k0 + 4 * lg;
-    const BST_G double* B = (const BST_G double*)(ptrs[g.b_buf]) + g.b_off;
+    const BST_G double* B = BL == kBComplex ? (const BST_G double*)(ptrs[bslot]) + (g.b_off >> 1)
+                                            : (const BST_G double*)(ptrs[g.b_buf]) + g.b_off;
     if (ls + 1 < p.seg_count) nxt = segs[p.seg_begin + ls + 1];
     lk = k0;
     lK = g.K;
@@ -713,7 +716,7 @@ static hipError_t launch_shape(int bm, int bn, const GemmLaunch& g, hipStream_t 
   if (bm == BM_ && bn == BN_) {                                                                  \
     if constexpr (FORM == BST_FP64 || FORM == BST_FP32)                                          \
       hipLaunchKernelGGL((gemm_block_kernel<FORM, TA, TC, BL, BM_, BN_, kBlockDepth<FORM, BM_, BN_>>), grid, block, 0, s, \
-                         g.tiles, g.probs, g.segs, g.ptrs, (int)hb, g.coef);                     \
+                         g.tiles, g.probs, g.segs, g.ptrs, g.b_complex, (int)hb, g.coef);                     \
     else                                                                                         \
       hipLaunchKernelGGL((gemm_grouped_kernel<FORM, TA, TC, BL == kBTrans, BM_, BN_>), grid, block, 0,   \
                          s, g.tiles, g.probs, g.segs, g.ptrs);                                   \
@@ -741,23 +744,24 @@ static hipError_t launch_form(const GemmLaunch& g, hipStream_t s) {
       if (g.coef.nentries > 0 || g.ta != ElemType::F64 || g.tb != ElemType::F64 || g.tc != ElemType::F64)
         return hipErrorInvalidValue;
       const dim3 grid((unsigned)g.ntiles), block(256);
-      if (g.b_complex)
-        hipLaunchKernelGGL(gemm_ksplit_kernel<kBComplex>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+      if (g.b_complex >= 0)
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBComplex>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs,
+                           g.b_complex);
       else if (g.transb)
-        hipLaunchKernelGGL(gemm_ksplit_kernel<kBTrans>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBTrans>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs, -1);
       else
-        hipLaunchKernelGGL(gemm_ksplit_kernel<kBPlain>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs);
+        hipLaunchKernelGGL(gemm_ksplit_kernel<kBPlain>, grid, block, 0, s, g.tiles, g.probs, g.segs, g.ptrs, -1);
       return hipGetLastError();
     }
   }
   if (shapes[g.tile].direct)
-    return g.coef.nentries > 0 || g.b_complex ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
+    return g.coef.nentries > 0 || g.b_complex >= 0 ? hipErrorInvalidValue : launch_gemm_direct(g, bm, bn, s);
   const bool a64 = g.ta == ElemType::F64, c64 = g.tc == ElemType::F64;
   if (g.tb != ElemType::F64) return hipErrorInvalidValue;
   if (a64 && c64) {
     if constexpr (FORM == BST_FP64 || FORM == BST_FP32)
-      if (g.b_complex) return launch_shape<FORM, double, double, kBComplex>(bm, bn, g, s);
-    if (g.b_complex) return hipErrorInvalidValue;
+      if (g.b_complex >= 0) return launch_shape<FORM, double, double, kBComplex>(bm, bn, g, s);
+    if (g.b_complex >= 0) return hipErrorInvalidValue;
     return g.transb ? launch_shape<FORM, double, double, kBTrans>(bm, bn, g, s)
                     : launch_shape<FORM, double, double, kBPlain>(bm, bn, g, s);
   }

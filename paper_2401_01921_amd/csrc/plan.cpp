@@ -428,17 +428,13 @@ static void contract_c128_plan(const TensorDesc& A, const TensorDesc& B, PlanDat
     for (int64_t st0 = 0; st0 < K * N; st0 += 4096) ex.xwork.push_back({jid, (int32_t)st0});
   }
   ex.bytes = ex.bytes32 = 16.0 * (double)Bp->numel + 32.0 * (double)Bp->numel;
-  // the contraction now reads B' from its internal slot, or B itself
-  std::map<int64_t, int64_t> at;   // expanded block -> the complex one
-  for (const auto& j : ex.xjobs) at[j.out_off] = j.in_off;
+  // the contraction now reads B' from its internal slot, or B itself: its blocks
+  // stand in the same order, each half as long
+  for (const auto& j : ex.xjobs)
+    if (j.out_off != 2 * j.in_off) fail(BST_E_INVALID, "internal: expanded block out of order");
   for (auto& st : P.steps) {
     if (st.kind != StepKind::Gemm) continue;
-    st.segs_cplx = st.segs;
-    for (auto& g : st.segs_cplx)
-      if (g.b_buf == 1) {
-        g.b_off = at.at(g.b_off);
-        g.b_buf = src;
-      }
+    st.cplx_slot = src;
     for (auto& g : st.segs)
       if (g.b_buf == 1) g.b_buf = xslot;
   }
@@ -584,7 +580,7 @@ static void add_split_jobs(Step& st, const TensorDesc& T, int split, bool transp
 }
 
 static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDesc& W2,
-                      const TensorDesc& R, const TensorDesc& psi, PlanData& P) {
+                      const TensorDesc& R, const TensorDesc& psi, PlanData& P, bool pad = true) {
   if (L.rank() != 3 || W1.rank() != 4 || W2.rank() != 4 || R.rank() != 3 || psi.rank() != 4)
     fail(BST_E_STRUCTURE, "H_eff needs L[a,w,a'], W[wl,s,s',wr] (x2), R[b,w,b'], psi[a,s1,s2,b]");
   check_contractible(L.legs[2], psi.legs[0], "L.a' / psi.a");
@@ -622,23 +618,23 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
   // Both are the plan's own, so their rows are padded to 16 elements: a row's
   // 16 k of a GEMM step (and a row of 16 results) is then one 128-byte line of
   // float64 instead of parts of two, and the number of lines requested is what
-  // bounds those steps.  Block b starts at off[b], its rows are ld[b] apart.
+  // bounds those steps.  Block b starts at off[b], its rows are ld[b] apart.  (pad
+  // = false where that would take more than sharing T3's buffer saves: below.)
   struct Rows {
     std::vector<int64_t> off, ld;
     int64_t total = 0;
-    Rows(const TensorDesc& T, int split) {
+    Rows(const TensorDesc& T, int split, bool pad) {
       for (int64_t b = 0; b < T.nblocks; ++b) {
         int64_t rows = 1, cols = 1;
         for (int i = 0; i < T.rank(); ++i) (i < split ? rows : cols) *= T.block_shape(b)[i];
         off.push_back(total);
-        ld.push_back((cols + 15) / 16 * 16);
+        ld.push_back(pad && cols <= 0x7FFFFFF0 ? (cols + 15) / 16 * 16 : cols);
         total += rows * ld.back();
       }
     }
   };
-  const Rows T1r(*T1, 2), T3r(*T3, 3);
+  const Rows T1r(*T1, 2, pad), T3r(*T3, 3, pad);
   P.internals.push_back({6, (size_t)T1r.total * 8, 0});
-  P.internals.push_back({7, (size_t)T3r.total * 8, 0});
   // bfloat16 planes for the split forms: L [(a w) x a'], R [b x (w b')],
   // psi transposed to [(t1 t2 b') x a'], T3 [(a s1 s2) x (w3 b')]
   P.has_planes = true;
@@ -681,11 +677,12 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
     sink_need = std::max(sink_need, sh[0] * sh[4]);
   }
   const int64_t t3ps = pad32(std::max<int64_t>(t3tot + sink_need, 32));   // positions per plane
-  // 8 bytes per position: three bfloat16 planes or one of float64
+  // 8 bytes per position: three bfloat16 planes or one of float64.  An apply
+  // writes T3 once and in one of its forms, so both share a buffer.
   P.internals.push_back({8, (size_t)Lp.total * 8, 0});
   P.internals.push_back({9, (size_t)Rp.total * 8, 0});
   P.internals.push_back({10, (size_t)Pp.total * 8, 0});
-  P.internals.push_back({11, (size_t)t3ps * 8, 0});
+  P.internals.push_back({11, (size_t)std::max(t3ps, T3r.total) * 8, 0, 7});
   Step spL, spR, spP;
   spL.name = "split_L";
   spR.name = "split_R";
@@ -789,6 +786,7 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
     }
     // T1 blocks that no (L, psi) pair reaches stay zero: each gets a region
     // of its own, written (as zeros) by a problem without segments
+    int64_t plain = cum;   // cum without padded rows
     t1zero.assign(T1->nblocks, -1);
     for (int64_t cb = 0; cb < T1->nblocks; ++cb) {
       if (s1.probs[cb].seg_count > 0) continue;
@@ -799,11 +797,19 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
       p.seg_count = 0;
       s1.probs_alt.push_back(p);
       cum += (int64_t)p.M * p.ldc;
+      plain += (int64_t)p.M * p.N;
     }
     // the T1 buffer holds the float64 block layout or this merged one (float32
     // for the split forms, float64 for the float64 panels)
     for (auto& ib : P.internals)
       if (ib.slot == 6) ib.bytes = std::max(ib.bytes, (size_t)cum * 8);
+    // narrow blocks (sectors of a column or two) would grow up to 16 times: rows are
+    // padded only where T1 and T3 then take no more than unpadded in three buffers
+    if (pad && std::max(T1r.total, cum) + std::max(T3r.total, t3ps) >
+                   std::max(T1->numel, plain) + T3->numel + t3ps) {
+      P = PlanData();
+      return heff_plan(L, W1, W2, R, psi, P, false);
+    }
     s1.bytes = 8.0 * ((double)L.numel + (double)psi.numel + (double)T1->numel);
     s1.bytes32 = 8.0 * ((double)L.numel + (double)psi.numel) + 4.0 * (double)T1->numel;
   }
@@ -1109,7 +1115,8 @@ static void heff_batch(const std::vector<const PlanData*>& subs, PlanData& P) {
     for (auto s : S.out_slots) P.out_slots.push_back(base + s);
     for (auto n : S.in_numel) P.in_numel.push_back(n);
     for (auto n : S.out_numel) P.out_numel.push_back(n);
-    for (auto ib : S.internals) P.internals.push_back({base + ib.slot, ib.bytes, 0});
+    for (auto ib : S.internals)
+      P.internals.push_back({base + ib.slot, ib.bytes, 0, ib.also < 0 ? -1 : base + ib.also});
     if (P.steps.empty()) {
       for (const auto& st : S.steps) {
         Step e;
@@ -1262,16 +1269,21 @@ static int64_t tile_total(const std::vector<GemmProb>& probs, int bm, int bn) {
 static int64_t tile_run(int64_t total) { return std::max<int64_t>(1, (total + 31) / 32); }
 static int64_t tile_list_cap(int64_t total) { return total * 3 / 2 / kXcds + tile_run(total) + 1; }
 
-static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
-                                        const std::vector<GemmSeg>& segs, int bm, int bn,
-                                        const std::vector<uint8_t>& shared = {}, int part = kAllProbs) {
-  const int64_t total = tile_total(probs, bm, bn), run = tile_run(total), cap = tile_list_cap(total);
-  struct Run {
-    double cost;
-    int32_t prob;
-    int64_t first, count;
-  };
-  std::vector<Run> runs;
+// A run of one problem's tiles and its place: entries 8 (pos + e) + xcd.
+struct TileRun {
+  double cost;
+  int32_t prob;
+  int64_t first, count;
+  int xcd;
+  int64_t pos;
+};
+// whole: every problem is one run, on whichever XCD has the least load (no bound
+// on a list's length, but mostly a shorter list).  Returns the list's length.
+static int64_t place_runs(const std::vector<GemmProb>& probs, const std::vector<GemmSeg>& segs, int bm, int bn,
+                          const std::vector<uint8_t>& shared, int part, bool whole, std::vector<TileRun>& runs) {
+  const int64_t total = tile_total(probs, bm, bn), run = whole ? std::max<int64_t>(total, 1) : tile_run(total),
+                cap = whole ? total : tile_list_cap(total);
+  runs.clear();
   runs.reserve(probs.size() + 32);
   for (size_t pi = 0; pi < probs.size(); ++pi) {
     const auto& p = probs[pi];
@@ -1282,32 +1294,50 @@ static std::vector<GemmTile> make_tiles(const std::vector<GemmProb>& probs,
     const int64_t parts = (nt + run - 1) / run;
     for (int64_t q = 0; q < parts; ++q) {
       const int64_t t0 = nt * q / parts, t1 = nt * (q + 1) / parts;
-      runs.push_back({(double)(t1 - t0) * (double)(k + 16), (int32_t)pi, t0, t1 - t0});
+      runs.push_back({(double)(t1 - t0) * (double)(k + 16), (int32_t)pi, t0, t1 - t0, 0, 0});
     }
   }
-  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
-  int64_t count[kXcds] = {};
+  std::stable_sort(runs.begin(), runs.end(), [](const TileRun& a, const TileRun& b) { return a.cost > b.cost; });
+  int64_t count[kXcds] = {}, length = 0;
   double load[kXcds] = {};
-  std::vector<GemmTile> out;
-  out.reserve((size_t)(total + total / 4));
-  for (const auto& q : runs) {
+  for (auto& q : runs) {
     int x = -1;
     for (int i = 0; i < kXcds; ++i)
       if (count[i] + q.count <= cap && (x < 0 || load[i] < load[x])) x = i;
     load[x] += q.cost;
+    q.xcd = x;
+    q.pos = count[x];
+    count[x] += q.count;
+    length = std::max(length, kXcds * (count[x] - 1) + x + 1);
+  }
+  return length;
+}
+
+static int64_t tile_list_length(const PlanData& P, const std::vector<GemmProb>& probs,
+                                const std::vector<GemmSeg>& segs, int bm, int bn,
+                                const std::vector<uint8_t>& shared = {}, int part = kAllProbs) {
+  std::vector<TileRun> runs;
+  return place_runs(probs, segs, bm, bn, shared, part, P.whole_lists, runs);
+}
+
+static std::vector<GemmTile> make_tiles(const PlanData& P, const std::vector<GemmProb>& probs,
+                                        const std::vector<GemmSeg>& segs, int bm, int bn,
+                                        const std::vector<uint8_t>& shared, int part) {
+  std::vector<TileRun> runs;
+  std::vector<GemmTile> out((size_t)place_runs(probs, segs, bm, bn, shared, part, P.whole_lists, runs),
+                            GemmTile{-1, 0, 0, 0});
+  for (const auto& q : runs) {
     const auto& p = probs[q.prob];
     const int32_t seg = p.seg_count > 0 ? p.seg_begin : 0;
-    const int64_t nn = (p.N + bn - 1) / bn, last = kXcds * (count[x] + q.count - 1) + x;
-    if ((int64_t)out.size() <= last) out.resize((size_t)last + 1, GemmTile{-1, 0, 0, 0});
+    const int64_t nn = (p.N + bn - 1) / bn;
     int64_t m = q.first / nn, n = q.first % nn;
     for (int64_t e = 0; e < q.count; ++e) {
-      out[(size_t)(kXcds * (count[x] + e) + x)] = {q.prob, (int32_t)(m * bm), (int32_t)(n * bn), seg};
+      out[(size_t)(kXcds * (q.pos + e) + q.xcd)] = {q.prob, (int32_t)(m * bm), (int32_t)(n * bn), seg};
       if (++n == nn) {
         n = 0;
         ++m;
       }
     }
-    count[x] += q.count;
   }
   return out;
 }
@@ -1317,7 +1347,7 @@ std::pair<size_t, int64_t> tile_list(PlanData& P, Step& st, bool alt, int bm, in
   const std::pair<int, int> key(bm + 4096 * part, bn);
   auto it = lists.find(key);
   if (it == lists.end()) {
-    const auto tl = make_tiles(alt ? st.probs_alt : st.probs, alt ? st.segs_alt : st.segs, bm, bn, st.shared, part);
+    const auto tl = make_tiles(P, alt ? st.probs_alt : st.probs, alt ? st.segs_alt : st.segs, bm, bn, st.shared, part);
     const size_t off = put(P.blob, tl);
     P.blob.resize(align256(P.blob.size()));
     if (P.ws_blob_off + P.blob.size() > P.ws_coef64_off) fail(BST_E_INVALID, "internal: tile lists outgrow their space");
@@ -1615,7 +1645,7 @@ int default_tile(const Step& st, bst_precision form) {
 }
 
 bool reads_complex(const Step& st, bst_precision prec) {
-  if (st.segs_cplx.empty() || (prec != BST_FP64 && prec != BST_FP32)) return false;
+  if (st.cplx_slot < 0 || (prec != BST_FP64 && prec != BST_FP32)) return false;
   const int kind = gemm_tile_shapes(prec)[default_tile(st, prec)].direct;
   return kind == 0 || kind == 4;
 }
@@ -1679,12 +1709,41 @@ static int planes_auto_tile(const Step& st, int np) {
   return kPlanesDefaultTile;
 }
 
+// Space for every tile list of a plan, each built on first use (an MPO contraction
+// has thousands of tiles; six lists of them took longer to build and upload than
+// everything else): a bound that needs no list, or their exact lengths.
+static size_t list_reserve(const PlanData& P, bool exact) {
+  size_t bytes = 0;
+  for (const auto& st : P.steps) {
+    if (st.kind != StepKind::Gemm) continue;
+    auto add = [&](bool alt, int bm, int bn, int part) {
+      const auto& probs = alt ? st.probs_alt : st.probs;
+      const int64_t n = exact ? tile_list_length(P, probs, alt ? st.segs_alt : st.segs, bm, bn, st.shared, part)
+                              : kXcds * tile_list_cap(tile_total(probs, bm, bn));
+      bytes += align256((size_t)n * sizeof(GemmTile));
+    };
+    std::set<std::pair<int, int>> shapes, shapes_alt;
+    for (int f = 0; f < 4; ++f)
+      for (const auto& sh : gemm_tile_shapes((bst_precision)f)) shapes.insert({sh.bm, sh.bn});
+    for (const auto& b : shapes) add(false, b.first, b.second, kAllProbs);
+    // a batch of both kinds: the shared tiles' list and the others' (default_tile's shapes)
+    if (std::find(st.shared.begin(), st.shared.end(), 0) != st.shared.end()) {
+      add(false, 32, 32, kSharedProbs);
+      add(false, 32, 32, kOtherProbs);
+      add(false, 64, 32, kOtherProbs);
+    }
+    if (!st.has_alt) continue;
+    for (int np = 1; np <= 3; ++np)
+      for (const auto& sh : gemm_planes_shapes(np))
+        if (sh.direct != 3) shapes_alt.insert({sh.bm, sh.bn});
+    for (const auto& b : shapes_alt) add(true, b.first, b.second, kAllProbs);
+  }
+  return bytes;
+}
+
 void finalize(PlanData& P) {
   P.blob.clear();
-  size_t reserve = 0;
-  auto list_bytes = [](const std::vector<GemmProb>& probs, int bm, int bn) {
-    return align256((size_t)(kXcds * tile_list_cap(tile_total(probs, bm, bn))) * sizeof(GemmTile));
-  };
+  P.whole_lists = false;
   P.coef_entries = 0;
   P.fused_ok = false;
   for (auto& st : P.steps) {
@@ -1693,7 +1752,6 @@ void finalize(PlanData& P) {
         st.off0 = put(P.blob, st.probs);
         if (st.segs.empty()) st.segs.push_back(GemmSeg{});   // (kernels read a tile's first before its count)
         st.off1 = put(P.blob, st.segs);
-        if (!st.segs_cplx.empty()) st.off4 = put(P.blob, st.segs_cplx);
         st.tile_lists.clear();
         st.tile_lists_alt.clear();
         st.tiles64x32 = st.tiles64x64 = 0;
@@ -1714,38 +1772,20 @@ void finalize(PlanData& P) {
           st.shared.clear();
           if (tiles < 2 * kStreamCUs && ksteps >= 3 * tiles) st.shared.assign(st.probs.size(), 1);
         }
-        // space for every tile list; each is built on first use (an MPO
-        // contraction has thousands of tiles, six lists of them took longer to
-        // build and upload than everything else)
-        {
-          std::set<std::pair<int, int>> shapes;
-          for (int f = 0; f < 4; ++f)
-            for (const auto& sh : gemm_tile_shapes((bst_precision)f)) shapes.insert({sh.bm, sh.bn});
-          for (const auto& b : shapes) reserve += list_bytes(st.probs, b.first, b.second);
-          // a batch of both kinds: the shared tiles' list and the others' (default_tile's shapes)
-          if (std::find(st.shared.begin(), st.shared.end(), 0) != st.shared.end())
-            reserve += 2 * list_bytes(st.probs, 32, 32) + list_bytes(st.probs, 64, 32);
-        }
         if (st.has_alt) {
           if (st.segs_alt.empty()) st.segs_alt.push_back(GemmSeg{});
           st.off2 = put(P.blob, st.segs_alt);
           st.off3 = put(P.blob, st.probs_alt);
           st.off5 = put(P.blob, st.rowmap);
           st.streams_alt.clear();
-          std::set<std::pair<int, int>> shapes_alt;
           for (int np = 1; np <= 3; ++np) {
             const auto& shapes = gemm_planes_shapes(np);
             for (size_t i = 0; i < shapes.size(); ++i) {
               const auto& sh = shapes[i];
-              if (sh.direct == 3) {
-                st.streams_alt[np * 64 + (int)i] = make_stream(P.blob, st, np, sh);
-                continue;
-              }
-              shapes_alt.insert({sh.bm, sh.bn});
+              if (sh.direct == 3) st.streams_alt[np * 64 + (int)i] = make_stream(P.blob, st, np, sh);
             }
             st.planes_default[np - 1] = planes_auto_tile(st, np);
           }
-          for (const auto& b : shapes_alt) reserve += list_bytes(st.probs_alt, b.first, b.second);
         }
         break;
       }
@@ -1856,11 +1896,10 @@ void finalize(PlanData& P) {
         st.n1 = (int64_t)wgrp.size();
         if (st.has_alt) {
           st.off3 = put(P.blob, st.tasks_alt);
-          st.off4 = put(P.blob, st.planes_alt);
           // the fused kernel copies nmax output planes per tile: spare records
           std::vector<HPlane> pl = st.planes_alt;
           pl.resize(pl.size() + (size_t)st.nmax, HPlane{0, 0});
-          st.fused_planes_off = put(P.blob, pl);
+          st.off4 = put(P.blob, pl);
           st.fused = make_fused(P.blob, st, st.nmax);
           if (st.fused.ok) P.fused_ok = true;
         }
@@ -1881,29 +1920,44 @@ void finalize(PlanData& P) {
         break;
     }
   }
-  size_t off = 0;
-  P.ws_ptr_off = off;
-  off = align256(off + sizeof(void*) * (size_t)std::max(P.nslots, 1));
-  P.ws_blob_off = off;
   P.blob.resize(align256(P.blob.size()));
-  off = align256(off + P.blob.size() + reserve);
-  P.ws_coef64_off = off;
-  off = align256(off + sizeof(double) * (size_t)std::max(P.coef_entries, 1));
-  P.ws_coef32_off = off;
-  off = align256(off + sizeof(float) * (size_t)std::max(P.coef_entries, 1));
-  P.ws_cnt_off = off;
-  off = align256(off + sizeof(int32_t) * (size_t)std::max(P.coef_entries, 1));
-  P.ws_idx_off = off;
-  off = align256(off + sizeof(int32_t) * (size_t)std::max(P.coef_entries, 1));
-  P.ws_val64_off = off;
-  off = align256(off + sizeof(double) * (size_t)std::max(P.coef_entries, 1));
-  P.ws_val32_off = off;
-  off = align256(off + sizeof(float) * (size_t)std::max(P.coef_entries, 1));
-  for (auto& ib : P.internals) {
-    ib.ws_off = off;
-    off = align256(off + std::max<size_t>(ib.bytes, 8));
+  auto layout = [&](size_t reserve) {
+    size_t off = 0;
+    P.ws_ptr_off = off;
+    off = align256(off + sizeof(void*) * (size_t)std::max(P.nslots, 1));
+    P.ws_blob_off = off;
+    off = align256(off + P.blob.size() + reserve);
+    P.ws_coef64_off = off;
+    off = align256(off + sizeof(double) * (size_t)std::max(P.coef_entries, 1));
+    P.ws_coef32_off = off;
+    off = align256(off + sizeof(float) * (size_t)std::max(P.coef_entries, 1));
+    P.ws_cnt_off = off;
+    off = align256(off + sizeof(int32_t) * (size_t)std::max(P.coef_entries, 1));
+    P.ws_idx_off = off;
+    off = align256(off + sizeof(int32_t) * (size_t)std::max(P.coef_entries, 1));
+    P.ws_val64_off = off;
+    off = align256(off + sizeof(double) * (size_t)std::max(P.coef_entries, 1));
+    P.ws_val32_off = off;
+    off = align256(off + sizeof(float) * (size_t)std::max(P.coef_entries, 1));
+    for (auto& ib : P.internals) {
+      ib.ws_off = off;
+      off = align256(off + std::max<size_t>(ib.bytes, 8));
+    }
+    P.ws_bytes = off;
+  };
+  const size_t reserve = list_reserve(P, false);
+  layout(reserve);
+  // bst_execute_static has a fixed array: a plan that only the bound keeps out of
+  // it takes whole runs and their exact lengths instead
+  const size_t limit = BST_STATIC_WORKSPACE_BYTES;
+  if (P.ws_bytes > limit && P.ws_bytes - reserve <= limit) {
+    P.whole_lists = true;
+    layout(list_reserve(P, true));
+    if (P.ws_bytes > limit) {
+      P.whole_lists = false;
+      layout(reserve);
+    }
   }
-  P.ws_bytes = off;
   P.f64_panels = P.has_planes;
   for (const auto& st : P.steps) {
     if (st.kind != StepKind::Gemm || !st.has_alt) continue;
@@ -2103,7 +2157,7 @@ bst_status bst_plan_info(const bst_plan* p, bst_plan_stats* st) {
       st->gemm_problems += (int64_t)s.probs.size();
       const int t = default_tile(s, P.prec);
       const auto& sh = gemm_tile_shapes(P.prec)[t];
-      st->gemm_tiles += (int64_t)make_tiles(s.probs, s.segs, sh.bm, sh.bn).size();
+      st->gemm_tiles += tile_list_length(P, s.probs, s.segs, sh.bm, sh.bn);
     }
   }
   st->launches = (int64_t)P.steps.size();
@@ -2125,7 +2179,7 @@ bst_status bst_plan_step_info(const bst_plan* p, int32_t step, bst_step_info* in
   if (s.kind == StepKind::Gemm) {
     const int t = default_tile(s, P.prec);
     const auto& sh = gemm_tile_shapes(P.prec)[t];
-    info->items = (int64_t)make_tiles(s.probs, s.segs, sh.bm, sh.bn).size();
+    info->items = tile_list_length(P, s.probs, s.segs, sh.bm, sh.bn);
   } else {
     info->items = s.n0;
   }

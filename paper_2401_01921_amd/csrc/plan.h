@@ -60,9 +60,10 @@ struct Step {
   // Permute
   std::vector<PermJob> jobs;
   std::vector<PermWork> pwork;
-  // complex contraction: the segments on B itself; the expanded copy is made
-  // only for GEMM kernels that cannot read them
-  std::vector<GemmSeg> segs_cplx;
+  // complex contraction: the slot of B itself, whose blocks have half the offsets
+  // that the segments give; the expanded copy is made only for GEMM kernels that
+  // cannot read it
+  int32_t cplx_slot = -1;
   // Expand (complex contraction)
   std::vector<ExpandJob> xjobs;
   std::vector<ExpandWork> xwork;
@@ -125,13 +126,13 @@ struct Step {
   };
   std::map<int, StreamList> streams_alt;
   StreamList fused;                  // HApply: k-step schedule of the fused kernel
-  size_t fused_planes_off = 0;       // tasks_alt planes with nmax spare records
 };
 
 struct InternalBuf {
   int32_t slot;
   size_t bytes;     // sized for float64
   size_t ws_off;
+  int32_t also = -1;   // a second slot in the same place
 };
 
 struct PlanData {
@@ -157,6 +158,7 @@ struct PlanData {
   bool sparse_mpo = true;       // MPO apply runs only the nonzero h entries
   // finalize
   std::vector<uint8_t> blob;     // tables; tile lists are appended when first used
+  bool whole_lists = false;      // tile lists of whole problems (finalize)
   size_t blob_uploaded = 0;      // bytes of it in uploaded_ws
   size_t ws_ptr_off = 0, ws_blob_off = 0, ws_coef64_off = 0, ws_coef32_off = 0, ws_bytes = 0;
   size_t ws_cnt_off = 0, ws_idx_off = 0, ws_val64_off = 0, ws_val32_off = 0;

@@ -1,0 +1,43 @@
+"""Workspace of a plan (no GPU): what the fixed array of bst_execute_static took
+before rows of the intermediates were padded and tile lists were given space by
+a bound, it still takes."""
+import pytest
+
+from paper_2401_01921_amd import bst, workloads as wl
+
+
+def _heff(va, vb, spin="1/2", model="heisenberg"):
+    T = {k: bst.Tensor(*s) for k, s in wl.heff_specs(spin, va, vb, model).items()}
+    return bst.heff_plan(T["L"], T["W1"], T["W2"], T["R"], T["psi"], "fp64")
+
+
+def _contract(nsec, m, k, n):
+    A = bst.Tensor(["i", "k"], [(1, [(q, m + q) for q in range(nsec)]), (-1, [(q, k) for q in range(nsec)])])
+    B = bst.Tensor(["k", "j"], [(1, [(q, k) for q in range(nsec)]), (-1, [(q, n) for q in range(nsec)])])
+    return bst.contract_plan(A, B, "fp64")[1]
+
+
+# (chi, qmax, model), bytes with T1 and both forms of T3 in buffers of their own
+# and unpadded rows, every tile list of its exact length
+@pytest.mark.parametrize("chi,qmax,model,was", [
+    (64, 4, "heisenberg", 1181184), (256, 6, "heisenberg", 5386496), (777, 11, "xx", 19577856),
+    (1024, 10, "heisenberg", 42898176), (1400, 12, "heisenberg", 66640128)])
+def test_heff_plans_take_no_more(chi, qmax, model, was):
+    v = wl.gaussian_sector_dims(chi, qmax)
+    assert _heff(v, v, model=model).workspace_bytes <= was <= bst.STATIC_WORKSPACE_BYTES
+
+
+@pytest.mark.parametrize("rows,nsec,was", [(40, 12, 3828736), (200, 6, 14889728)])
+def test_narrow_sectors_are_not_padded(rows, nsec, was):
+    """A right bond of one state per sector: a row padded to 16 elements would be
+    several times as long."""
+    p = _heff([(q, rows) for q in range(nsec)], [(q, 1) for q in range(nsec)])
+    assert p.workspace_bytes <= was
+
+
+def test_exact_lists_where_only_the_bound_is_too_much():
+    """64 outputs of 4300 x 4300: the lists of all shapes are 47 MB, the bound 83."""
+    assert _contract(64, 4300, 16, 4300).workspace_bytes == 47200000
+    small = _contract(64, 1000, 16, 1000)
+    assert small.workspace_bytes < 2 * 2711296
+    assert _contract(64, 5400, 16, 5400).workspace_bytes > bst.STATIC_WORKSPACE_BYTES
