@@ -181,7 +181,7 @@ struct SplitWork {
 };
 // A split work item with its job's fields copied in (the kernel's table:
 // one dependent read fewer before the first data load).
-constexpr int kSplitChunks = 512;   // 8-element output chunks of one item that is not transposed (first: r0)
+constexpr int kSplitChunks = 512;   // 8-element output chunks of one item that is not transposed (first: row r0, its chunk c0)
 struct SplitItem {
   int64_t in_off, out_off;
   int32_t in_buf, out_buf;

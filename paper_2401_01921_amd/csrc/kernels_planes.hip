@@ -67,17 +67,20 @@ __device__ __forceinline__ void split_tile(const SplitItem& j, void* const* __re
     typedef TI TI2u __attribute__((ext_vector_type(2), aligned(sizeof(TI))));
     typedef TI TI2 __attribute__((ext_vector_type(2)));
     constexpr int G = kSplitChunks / 256;
-    const uint32_t per = (uint32_t)j.out_ld / 8, n = (uint32_t)j.rows * per;
+    const uint32_t per = (uint32_t)j.out_ld / 8;
     TI v[G][8];
     int nv[G];
+    bool on[G];   // (chunks past the block read its last one)
     int64_t pos[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const uint32_t e = min((uint32_t)j.r0 + tid + 256u * g, n - 1), r = e / per;
-      const int c = 8 * (int)(e - r * per);
+      const uint32_t e = (uint32_t)j.c0 + tid + 256u * g, row = e / per, r = (uint32_t)j.r0 + row;
+      on[g] = r < (uint32_t)j.rows;
+      const int64_t rr = on[g] ? r : j.rows - 1;
+      const int c = 8 * (int)(on[g] ? e - row * per : per - 1);
       nv[g] = j.cols - c;
-      pos[g] = j.out_off + 8 * (int64_t)e;
-      const BST_G TI* const src = in + (int64_t)r * j.cols + c;
+      pos[g] = j.out_off + rr * j.out_ld + c;
+      const BST_G TI* const src = in + rr * j.cols + c;
       if (nv[g] >= 8) {
 #pragma unroll
         for (int q = 0; q < 8; q += 2) {
@@ -92,7 +95,7 @@ __device__ __forceinline__ void split_tile(const SplitItem& j, void* const* __re
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      if ((uint32_t)j.r0 + tid + 256u * g >= n) break;
+      if (!on[g]) break;
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if (q >= nv[g]) v[g][q] = (TI)0;

@@ -567,9 +567,9 @@ static void add_split_jobs(Step& st, const TensorDesc& T, int split, bool transp
     const int32_t jid = (int32_t)st.sjobs.size();
     st.sjobs.push_back(j);
     if (!transpose) {   // runs of 8-element output chunks, whatever the row length
-      const int64_t chunks = rows * (Lay.ld[b] / 8);
-      if (chunks > 0x7FFFFFFF - kSplitChunks) fail(BST_E_INVALID, "block too large for the bfloat16 split");
-      for (int64_t k = 0; k < chunks; k += kSplitChunks) st.swork.push_back({jid, (int32_t)k, 0, 0});
+      const int64_t per = Lay.ld[b] / 8, chunks = rows * per;
+      for (int64_t k = 0; k < chunks; k += kSplitChunks)
+        st.swork.push_back({jid, (int32_t)(k / per), (int32_t)(k % per), 0});
       continue;
     }
     for (int64_t r0 = 0; r0 < Lay.ld[b]; r0 += 64)

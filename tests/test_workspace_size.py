@@ -41,3 +41,15 @@ def test_exact_lists_where_only_the_bound_is_too_much():
     small = _contract(64, 1000, 16, 1000)
     assert small.workspace_bytes < 2 * 2711296
     assert _contract(64, 5400, 16, 5400).workspace_bytes > bst.STATIC_WORKSPACE_BYTES
+
+
+def test_blocks_of_more_than_2_to_34_elements():
+    """One sector of 131072 states: L alone is 137 GB, which one device holds.  (No
+    block of psi meets it here: the GEMM's tables would take gigabytes.)"""
+    n, one, other = 131072, [(0, 1)], [(9, 1)]
+    L = bst.Tensor(["a", "w", "a2"], [(1, [(0, n)]), (1, one), (-1, [(0, n)])])
+    W = [bst.Tensor(list("wxyz"), [(-1, one), (1, one), (-1, one), (1, one)]) for _ in range(2)]
+    R = bst.Tensor(["b", "w", "b2"], [(-1, other), (-1, one), (1, other)])
+    psi = bst.Tensor(list("abcd"), [(1, [(0, n)]), (1, one), (1, one), (-1, other)])
+    assert psi.numel == 0 and L.numel == n * n
+    assert bst.heff_plan(L, W[0], W[1], R, psi, "fp64").workspace_bytes > 8 * n * n
