@@ -580,7 +580,7 @@ static void add_split_jobs(Step& st, const TensorDesc& T, int split, bool transp
 }
 
 static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDesc& W2,
-                      const TensorDesc& R, const TensorDesc& psi, PlanData& P, bool pad = true) {
+                      const TensorDesc& R, const TensorDesc& psi, PlanData& P) {
   if (L.rank() != 3 || W1.rank() != 4 || W2.rank() != 4 || R.rank() != 3 || psi.rank() != 4)
     fail(BST_E_STRUCTURE, "H_eff needs L[a,w,a'], W[wl,s,s',wr] (x2), R[b,w,b'], psi[a,s1,s2,b]");
   check_contractible(L.legs[2], psi.legs[0], "L.a' / psi.a");
@@ -615,26 +615,6 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
                          lab(W2.legs[3], "w3"), lab(psi.legs[3], "y")});
   P.t1_numel = T1->numel;
   P.t3_numel = T3->numel;
-  // Both are the plan's own, so their rows are padded to 16 elements: a row's
-  // 16 k of a GEMM step (and a row of 16 results) is then one 128-byte line of
-  // float64 instead of parts of two, and the number of lines requested is what
-  // bounds those steps.  Block b starts at off[b], its rows are ld[b] apart.  (pad
-  // = false where that would take more than sharing T3's buffer saves: below.)
-  struct Rows {
-    std::vector<int64_t> off, ld;
-    int64_t total = 0;
-    Rows(const TensorDesc& T, int split, bool pad) {
-      for (int64_t b = 0; b < T.nblocks; ++b) {
-        int64_t rows = 1, cols = 1;
-        for (int i = 0; i < T.rank(); ++i) (i < split ? rows : cols) *= T.block_shape(b)[i];
-        off.push_back(total);
-        ld.push_back(pad && cols <= 0x7FFFFFF0 ? (cols + 15) / 16 * 16 : cols);
-        total += rows * ld.back();
-      }
-    }
-  };
-  const Rows T1r(*T1, 2, pad), T3r(*T3, 3, pad);
-  P.internals.push_back({6, (size_t)T1r.total * 8, 0});
   // bfloat16 planes for the split forms: L [(a w) x a'], R [b x (w b')],
   // psi transposed to [(t1 t2 b') x a'], T3 [(a s1 s2) x (w3 b')]
   P.has_planes = true;
@@ -677,11 +657,46 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
     sink_need = std::max(sink_need, sh[0] * sh[4]);
   }
   const int64_t t3ps = pad32(std::max<int64_t>(t3tot + sink_need, 32));   // positions per plane
+  // T1 and T3 are the plan's own, so their rows are padded to 16 elements: a row's
+  // 16 k of a GEMM step (and a row of 16 results) is then one 128-byte line of
+  // float64 instead of parts of two, and the number of lines requested is what
+  // bounds those steps.  Block b starts at off[b], its rows are ld[b] apart.
+  struct Rows {
+    std::vector<int64_t> off, ld;
+    int64_t total = 0;
+    Rows(const TensorDesc& T, int split, bool pad) {
+      for (int64_t b = 0; b < T.nblocks; ++b) {
+        int64_t rows = 1, cols = 1;
+        for (int i = 0; i < T.rank(); ++i) (i < split ? rows : cols) *= T.block_shape(b)[i];
+        off.push_back(total);
+        ld.push_back(pad && cols <= 0x7FFFFFF0 ? (cols + 15) / 16 * 16 : cols);
+        total += rows * ld.back();
+      }
+    }
+  };
+  Rows T1r(*T1, 2, true), T3r(*T3, 3, true);
+  // Narrow blocks (sectors of a column or two) would grow up to 16 times: rows are
+  // padded only where T1 and T3 then take no more than unpadded in three buffers.
+  // (t1m: T1's merged layout of the split forms, which shares its buffer; blocks
+  // that it has in addition count the same on both sides.)
+  int64_t t1m = 0;
+  {
+    std::vector<int64_t> ncol(psi.legs[0].q.size(), 0);
+    for (int64_t b = 0; b < psi.nblocks; ++b) ncol[psi.block_qn(b)[0]] += psi.block_size(b) / psi.block_shape(b)[0];
+    for (size_t k = 0; k < ncol.size(); ++k) t1m += Lg.gm[k] * ((ncol[k] + 15) / 16 * 16);
+  }
+  if (std::max(T1r.total, t1m) + std::max(T3r.total, t3ps) > std::max(T1->numel, t1m) + T3->numel + t3ps) {
+    T1r = Rows(*T1, 2, false);
+    T3r = Rows(*T3, 3, false);
+  }
   // 8 bytes per position: three bfloat16 planes or one of float64.  An apply
   // writes T3 once and in one of its forms, so both share a buffer.
   P.internals.push_back({8, (size_t)Lp.total * 8, 0});
   P.internals.push_back({9, (size_t)Rp.total * 8, 0});
   P.internals.push_back({10, (size_t)Pp.total * 8, 0});
+  // (The MPO step, which streams T1 and T3, depends on where they lie: chi = 4096,
+  // T1 before the operands' planes 42.7 us, last but T3 40.4.)
+  P.internals.push_back({6, (size_t)T1r.total * 8, 0});
   P.internals.push_back({11, (size_t)std::max(t3ps, T3r.total) * 8, 0, 7});
   Step spL, spR, spP;
   spL.name = "split_L";
@@ -786,30 +801,22 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
     }
     // T1 blocks that no (L, psi) pair reaches stay zero: each gets a region
     // of its own, written (as zeros) by a problem without segments
-    int64_t plain = cum;   // cum without padded rows
     t1zero.assign(T1->nblocks, -1);
     for (int64_t cb = 0; cb < T1->nblocks; ++cb) {
       if (s1.probs[cb].seg_count > 0) continue;
       t1zero[cb] = cum;
       GemmProb p = s1.probs[cb];
       p.c_off = cum;
+      p.ldc = p.N;
       p.seg_begin = (int32_t)s1.segs_alt.size();
       p.seg_count = 0;
       s1.probs_alt.push_back(p);
-      cum += (int64_t)p.M * p.ldc;
-      plain += (int64_t)p.M * p.N;
+      cum += T1->block_size(cb);
     }
     // the T1 buffer holds the float64 block layout or this merged one (float32
     // for the split forms, float64 for the float64 panels)
     for (auto& ib : P.internals)
       if (ib.slot == 6) ib.bytes = std::max(ib.bytes, (size_t)cum * 8);
-    // narrow blocks (sectors of a column or two) would grow up to 16 times: rows are
-    // padded only where T1 and T3 then take no more than unpadded in three buffers
-    if (pad && std::max(T1r.total, cum) + std::max(T3r.total, t3ps) >
-                   std::max(T1->numel, plain) + T3->numel + t3ps) {
-      P = PlanData();
-      return heff_plan(L, W1, W2, R, psi, P, false);
-    }
     s1.bytes = 8.0 * ((double)L.numel + (double)psi.numel + (double)T1->numel);
     s1.bytes32 = 8.0 * ((double)L.numel + (double)psi.numel) + 4.0 * (double)T1->numel;
   }
@@ -867,10 +874,10 @@ static void heff_plan(const TensorDesc& L, const TensorDesc& W1, const TensorDes
               for (int64_t c = 0; c < gw; ++c)
                 for (int64_t e1 = 0; e1 < g1; ++e1)
                   for (int64_t e2 = 0; e2 < g2; ++e2) {
-                    const int64_t in_blk = c * T1r.ld[b] + (e1 * g2 + e2) * gy;
-                    ins.push_back({T1r.off[b] + in_blk, gw * T1r.ld[b]});
+                    const int64_t col = (e1 * g2 + e2) * gy, row = g1 * g2 * gy;
+                    ins.push_back({T1r.off[b] + c * T1r.ld[b] + col, gw * T1r.ld[b]});
                     if (t1zero[b] >= 0) {
-                      ins_alt.push_back({t1zero[b] + in_blk, gw * T1r.ld[b]});
+                      ins_alt.push_back({t1zero[b] + c * row + col, gw * row});
                       fin.push_back({0, 0, 0, 0, 0, 0});
                     } else {
                       const int64_t ld = t1m_ld[kx];
