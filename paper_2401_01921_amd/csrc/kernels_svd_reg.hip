@@ -35,6 +35,7 @@
 // rowpos: the place of every row of X and the inverse, then of every column.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cfloat>
 #include <type_traits>
 
@@ -938,20 +939,24 @@ __global__ __launch_bounds__(256) void svd_apply_kernel(const SvdSec* __restrict
 }
 
 hipError_t launch_svd_reg(const SvdLaunch& l, hipStream_t s) {
-  if (l.nreg <= 0) return hipSuccess;
-  if (l.nreg > 65535 || l.logcap < 1) return hipErrorInvalidValue;
-  const unsigned n = (unsigned)l.nreg;
-  for (int q = 0; q < l.panels; ++q) {
-    hipLaunchKernelGGL(svd_panel_kernel, dim3(n), dim3(1024), 0, s, l.secs, l.reg, l.X, l.scratch, l.rowpos,
-                       l.ctrl, q);
-    if (l.trail_rows > 0)
-      hipLaunchKernelGGL(svd_trail_kernel, dim3((unsigned)((l.trail_rows + kSvdTrailRows - 1) / kSvdTrailRows), n), dim3(256), 0, s, l.secs,
-                         l.reg, l.X, l.scratch, l.rowpos, l.ctrl, q);
+  if (l.logcap < 1) return hipErrorInvalidValue;
+  // a grid's second dimension holds 65535 sectors
+  for (int32_t k = 0; k < l.nreg; k += 65535) {
+    const unsigned n = (unsigned)std::min(l.nreg - k, 65535);
+    const int32_t* const list = l.reg + k;
+    int32_t* const ctrl = l.ctrl + (int64_t)kSvdCtrl * k;
+    const unsigned trail = (unsigned)((l.trail_rows + kSvdTrailRows - 1) / kSvdTrailRows);
+    const unsigned apply = (unsigned)((l.reg_cols + 4 * kSvdApplyRows - 1) / (4 * kSvdApplyRows));
+    for (int q = 0; q < l.panels; ++q) {
+      hipLaunchKernelGGL(svd_panel_kernel, dim3(n), dim3(1024), 0, s, l.secs, list, l.X, l.scratch, l.rowpos, ctrl, q);
+      if (trail > 0)
+        hipLaunchKernelGGL(svd_trail_kernel, dim3(trail, n), dim3(256), 0, s, l.secs, list, l.X, l.scratch, l.rowpos,
+                           ctrl, q);
+    }
+    hipLaunchKernelGGL(svd_reg_kernel, dim3(n), dim3(64 * kSvdRegWaves), 0, s, l.secs, list, l.X, l.scratch, l.logcap,
+                       ctrl, l.sweeps, l.sig, l.sorted, l.perm);
+    hipLaunchKernelGGL(svd_apply_kernel, dim3(apply, n), dim3(256), 0, s, l.secs, list, l.X, l.scratch, ctrl);
   }
-  hipLaunchKernelGGL(svd_reg_kernel, dim3(n), dim3(64 * kSvdRegWaves), 0, s, l.secs, l.reg, l.X, l.scratch, l.logcap,
-                     l.ctrl, l.sweeps, l.sig, l.sorted, l.perm);
-  hipLaunchKernelGGL(svd_apply_kernel, dim3((unsigned)((l.reg_cols + 4 * kSvdApplyRows - 1) / (4 * kSvdApplyRows)), n), dim3(256), 0, s, l.secs, l.reg,
-                     l.X, l.scratch, l.ctrl);
   return hipGetLastError();
 }
 

@@ -243,7 +243,6 @@ void build(SvdPlanData& P) {
     P.vmax = std::max(P.vmax, r * r);
   }
   if (P.big.size() > 65535) fail(BST_E_INVALID, "more than 65535 sector matrices above the LDS budget");
-  if (P.reg.size() > 65535) fail(BST_E_INVALID, "more than 65535 sector matrices");
   // gather jobs: every block of T into its sector matrix
   std::vector<SvdGather> gj;
   std::vector<SvdWork> gw;
