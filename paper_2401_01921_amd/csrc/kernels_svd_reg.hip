@@ -659,7 +659,8 @@ __device__ __forceinline__ void double_steps(double (&v)[2 * U][RW], Step&& step
 }
 
 // `sweeps` logged sweeps on rows row0 .. row0 + RW - 1 of base (one wave).
-// Log of a sweep: N steps of U x 64 pairs (beta, alpha), then N factors.
+// Log of a sweep: N steps of U x LL pairs (beta, alpha) of the wave's last LL
+// lanes (svd_log_lanes), then N factors.
 template <int U, int RW>
 __device__ __forceinline__ void apply_log(double* base, int row0, int nrows, int N, int lane, const double* log, int sweeps,
                           bool reversed) {
@@ -667,18 +668,19 @@ __device__ __forceinline__ void apply_log(double* base, int row0, int nrows, int
   double v[2 * U][RW];
   load_rows<U, RW>(v, base, row0, nrows, N, k);
   const int64_t stride = svd_log_sweep(N, U);
+  const int LL = svd_log_lanes(N, U);
   // The log of the next AHEAD groups of 2U steps is in flight: a group takes
   // some 150 cycles, the load several times that.
   constexpr int PER = 2 * U, AHEAD = 4 / U;
   const int groups = N / PER;
   for (int s = 0; s < sweeps; ++s) {
-    const double2* const cf = reinterpret_cast<const double2*>(log + s * stride) + lane;
-    const double* const fac = log + s * stride + (int64_t)N * U * 128;
+    const double2* const cf = reinterpret_cast<const double2*>(log + s * stride) + max(lane - (64 - LL), 0);
+    const double* const fac = log + s * stride + (int64_t)N * U * LL * 2;
     double2 c[AHEAD][PER * U];
 #pragma unroll
     for (int a = 0; a < AHEAD; ++a)
 #pragma unroll
-      for (int q = 0; q < PER * U; ++q) c[a][q] = cf[64 * (min(a, groups - 1) * PER * U + q)];
+      for (int q = 0; q < PER * U; ++q) c[a][q] = cf[LL * (min(a, groups - 1) * PER * U + q)];
     for (int g = 0; g < groups; g += AHEAD) {
 #pragma unroll
       for (int a = 0; a < AHEAD; ++a) {
@@ -689,7 +691,7 @@ __device__ __forceinline__ void apply_log(double* base, int row0, int nrows, int
         });
         const int next = min(g + a + AHEAD, groups - 1);
 #pragma unroll
-        for (int q = 0; q < PER * U; ++q) c[a][q] = cf[64 * (next * PER * U + q)];
+        for (int q = 0; q < PER * U; ++q) c[a][q] = cf[LL * (next * PER * U + q)];
       }
     }
 #pragma unroll
@@ -753,6 +755,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
   };
   int sw = 0, logged = 0, turns = 0;
   const int64_t stride = svd_log_sweep(N, U);
+  const int LL = svd_log_lanes(N, U);
   for (; sw < kSvdMaxSweeps && r > 1; ++sw) {
     norms();
     double2* const lg = reinterpret_cast<double2*>(log + logged * stride);
@@ -787,7 +790,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
               st[0] = st[1];
             }
           }
-          if (wave == W - 1) lg[64 * (s0 + w) + lane] = c;
+          if (wave == W - 1 && lane >= 64 - LL) lg[LL * (s0 + w) + lane - (64 - LL)] = c;
           lift<RW>(v[0], v[1], c);
           if (w == 1) {
             move<kWaveShr1>(v[0]);
@@ -807,7 +810,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
             double2 c;
             rot |= __ballot(pair_params<U>(sh, wave, lb, f, N, w & 1, tol, c));
             sh.cf[wave][lb] = c;
-            lg[64 * ((s0 + w) * U + wave) + lb] = c;
+            if (lb >= 64 - LL) lg[LL * ((s0 + w) * U + wave) + lb - (64 - LL)] = c;
           }
           __syncthreads();
           const int lc = fresh_lane();
@@ -827,7 +830,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
     __syncthreads();
     const bool again = sh.rotated[0] || (U == 2 && sh.rotated[1]);
     if (!again) break;
-    for (int c = tid; c < N; c += 64 * W) log[logged * stride + (int64_t)N * U * 128 + c] = sh.d[c];
+    for (int c = tid; c < N; c += 64 * W) log[logged * stride + (int64_t)N * U * LL * 2 + c] = sh.d[c];
 #pragma unroll
     for (int j = 0; j < 2 * U; ++j) {
       const double dj = k >= 0 ? sh.d[2 * U * k + j] : 0.0;

@@ -213,7 +213,9 @@ void build(SvdPlanData& P) {
       if (!whole) P.trail_rows = std::max(P.trail_rows, p + rr - d.nb);
       P.reg_cols = std::max(P.reg_cols, rr);
       d.log_off = lo;
-      lo += (std::max((p + rr) * ld, P.logcap * svd_log_sweep(ld, d.pairs)) + 31) / 32 * 32;
+      // (one column does not rotate)
+      const int64_t log = rr > 1 ? P.logcap * svd_log_sweep(ld, d.pairs) : 0;
+      lo += (std::max((p + rr) * ld, log) + 31) / 32 * 32;
       d.p_off = po;
       po += 2 * (p + rr);
       P.reg.push_back((int32_t)k);

@@ -83,8 +83,16 @@ constexpr int kSvdTrailRows = 32;          // rows of one workgroup after it
 // row stride of a panel in LDS: whole groups of 16 lanes' pairs, a count that
 // the kernels are built for
 __host__ __device__ inline int svd_panel_ld(int64_t ld) { return ld <= 32 ? 32 : ld <= 64 ? 64 : ld <= 128 ? 128 : 224; }
-// doubles of one sweep's log: N steps of `pairs` x 64 pairs (beta, alpha), N factors
-__host__ __device__ inline int64_t svd_log_sweep(int64_t n, int64_t pairs) { return n * pairs * 128 + n; }
+// Lanes of a wave that the log stores: those with columns, the one before them,
+// which hands a column back, and one that stands for the rest (zeros).
+__host__ __device__ inline int svd_log_lanes(int64_t n, int64_t pairs) {
+  const int64_t l = n / (2 * pairs) + 2;
+  return (int)(l < 64 ? l : 64);
+}
+// doubles of one sweep's log: N steps of `pairs` x lanes pairs (beta, alpha), N factors
+__host__ __device__ inline int64_t svd_log_sweep(int64_t n, int64_t pairs) {
+  return n * pairs * svd_log_lanes(n, pairs) * 2 + n;
+}
 constexpr int kSvdGatherChunk = 256 * 16;
 
 struct SvdLaunch {
