@@ -46,10 +46,12 @@ void* upload_table(PlanData& P, const std::vector<void*>& ptrs, void* ws, size_t
   return table;
 }
 
-static bool capturing(hipStream_t s) {
+// The id of the capture that s is part of, 0 if none.
+static unsigned long long capture_of(hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  check_hip(hipStreamIsCapturing(s, &cap), "capture state");
-  return cap != hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  check_hip(hipStreamGetCaptureInfo(s, &cap, &id), "capture state");
+  return cap == hipStreamCaptureStatusNone ? 0 : id;
 }
 
 void upload_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {
@@ -60,19 +62,23 @@ void upload_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {
 
 void upload_blob(PlanData& P, void* ws, hipStream_t s) {
   if (P.blob_uploaded >= P.blob.size()) return;
-  char* dst = static_cast<char*>(ws) + P.ws_blob_off + P.blob_uploaded;
-  const uint8_t* src = P.blob.data() + P.blob_uploaded;
-  const size_t bytes = P.blob.size() - P.blob_uploaded;
+  char* dst = static_cast<char*>(ws) + P.ws_blob_off;
   // a list first used under a capture (the form was changed since the last
-  // call) is written by the graph itself, through kernel arguments, and counts
-  // as absent outside it (outside captures these are no faster than a copy)
-  if (P.blob_uploaded > 0 && capturing(s)) {
+  // call) is written by the graph itself, once, through kernel arguments, and
+  // counts as absent outside it (outside captures these are no faster than a copy)
+  const unsigned long long id = P.blob_uploaded > 0 ? capture_of(s) : 0;
+  if (id != 0) {
+    const size_t from = std::max(P.blob_uploaded, P.capture_id == id ? P.capture_size : 0);
+    const size_t bytes = P.blob.size() - from;
+    if (bytes == 0) return;
     std::vector<void*> words((bytes + 7) / 8, nullptr);
-    std::memcpy(words.data(), src, bytes);
-    check_hip(launch_set_ptrs(reinterpret_cast<void**>(dst), words.data(), (int)words.size(), s), "table upload");
+    std::memcpy(words.data(), P.blob.data() + from, bytes);
+    check_hip(launch_set_ptrs(reinterpret_cast<void**>(dst + from), words.data(), (int)words.size(), s), "table upload");
+    P.capture_id = id;
+    P.capture_size = P.blob.size();
     return;
   }
-  upload_bytes(dst, src, bytes, s);
+  upload_bytes(dst + P.blob_uploaded, P.blob.data() + P.blob_uploaded, P.blob.size() - P.blob_uploaded, s);
   P.blob_uploaded = P.blob.size();
 }
 

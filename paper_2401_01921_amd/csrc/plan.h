@@ -160,6 +160,8 @@ struct PlanData {
   std::vector<uint8_t> blob;     // tables; tile lists are appended when first used
   bool whole_lists = false;      // tile lists of whole problems (finalize)
   size_t blob_uploaded = 0;      // bytes of it in uploaded_ws
+  unsigned long long capture_id = 0;   // the last capture that wrote some of it,
+  size_t capture_size = 0;             // and up to where
   size_t ws_ptr_off = 0, ws_blob_off = 0, ws_coef64_off = 0, ws_coef32_off = 0, ws_bytes = 0;
   size_t ws_cnt_off = 0, ws_idx_off = 0, ws_val64_off = 0, ws_val32_off = 0;
   int32_t coef_entries = 0;
