@@ -56,12 +56,8 @@ __global__ __launch_bounds__(256) void svd_gather_kernel(const SvdGather* __rest
 
 #define BST_LDS __attribute__((address_space(3)))
 
-// The sweeps of one sector on X (p x r, column-major) and Vh (r x r): P is a
-// pointer to global memory or, for sectors held in LDS, an LDS-addressed
-// pointer (so that the compiler issues LDS accesses, not generic ones).
-// Returns the sweeps used.
-// Sum over groups of LP lanes (LP = 16, 32, 64; every lane of a group gets
-// the same value).
+// Sum over groups of LP lanes (LP = 32, 64; every lane of a group gets the
+// same value).
 template <int LP>
 __device__ __forceinline__ double group_allsum(double v) {
 #pragma unroll
@@ -69,13 +65,12 @@ __device__ __forceinline__ double group_allsum(double v) {
   return v;
 }
 
-// The sweeps of one sector on X (p x r, column-major) and Vh (r x r): PX
-// and PV are pointers to global memory or, for what is held in LDS,
-// LDS-addressed pointers (so that the compiler issues LDS accesses, not
-// generic ones).  One group of LP lanes per pair of a round.  Returns the
-// sweeps used.
-template <int LP, typename PX, typename PV>
-__device__ int jacobi_sweeps(PX x, PV vh, int p, int r, int* rotated) {
+// The sweeps of one sector on X (p x r, column-major, in LDS) and Vh (r x r):
+// PV is a pointer to global memory or, where Vh is held in LDS too, an
+// LDS-addressed one (so that the compiler issues LDS accesses, not generic
+// ones).  One group of LP lanes per pair of a round.  Returns the sweeps used.
+template <int LP, typename PV>
+__device__ int jacobi_sweeps(BST_LDS double* x, PV vh, int p, int r, int* rotated) {
   constexpr int NH = 64 * kSvdWaves / LP;   // lane groups of the workgroup
   const int tid = threadIdx.x, hl = tid % LP, half = tid / LP;
   const double tol = 4.0 * DBL_EPSILON * sqrt((double)p);
@@ -94,8 +89,8 @@ __device__ int jacobi_sweeps(PX x, PV vh, int p, int r, int* rotated) {
           j = q;
         }
         if (j >= r) continue;
-        PX xi = x + (int64_t)i * p;
-        PX xj = x + (int64_t)j * p;
+        BST_LDS double* xi = x + (int64_t)i * p;
+        BST_LDS double* xj = x + (int64_t)j * p;
         double a = 0.0, b = 0.0, g = 0.0;
         for (int e = hl; e < p; e += LP) {
           const double u = xi[e], v = xj[e];
@@ -150,10 +145,10 @@ __global__ __launch_bounds__(64 * kSvdWaves) void svd_jacobi_kernel(const SvdSec
   double* const vg = X + S.v_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ int rotated;
-  // X is rotated in LDS when it fits kSvdLdsBytes, and Vh with it when both
-  // fit; what does not fit works in global memory (the three dots of a pair
-  // read X only, so X in LDS keeps them off global latency).  Copied back
-  // at the end.
+  // X is rotated in LDS, and Vh with it when both fit; else Vh works in global
+  // memory (the three dots of a pair read X only, so X in LDS keeps them off
+  // global latency).  Copied back at the end.  X of a big sector, and a single
+  // column, which is not rotated, may be larger and stay where they are.
   __shared__ double lds[kSvdLdsBytes / sizeof(double)];
   const bool x_lds = (int64_t)p * r * (int64_t)sizeof(double) <= kSvdLdsBytes;
   const bool v_lds = x_lds && ((int64_t)p * r + (int64_t)r * r) * (int64_t)sizeof(double) <= kSvdLdsBytes;
@@ -169,24 +164,17 @@ __global__ __launch_bounds__(64 * kSvdWaves) void svd_jacobi_kernel(const SvdSec
     for (int64_t e = tid; e < (int64_t)r * r; e += NT) vg[e] = (e % r == e / r) ? 1.0 : 0.0;
   if (tid == 0) rotated = 0;
   __syncthreads();
-  // the widest lane groups that still give every pair of a round its own
-  // group (wide groups for few long columns, narrow ones for many short)
+  // the widest lane groups that still give every pair of a round its own group:
+  // 32 lanes do for all, as X has more rows than the register path takes
+  static_assert(kSvdLdsBytes / 8 / (kSvdRegMaxRows + 1) <= 2 * (NT / 32), "pairs of a round");
   const int npairs = (r + 1) / 2;
-  auto sweeps_lp = [&](auto lp) {
-    constexpr int L = decltype(lp)::value;
-    if (v_lds) return jacobi_sweeps<L>(xl, vl, p, r, &rotated);
-    if (x_lds) return jacobi_sweeps<L>(xl, vg, p, r, &rotated);
-    return jacobi_sweeps<L>(xg, vg, p, r, &rotated);
-  };
-  int sw;
+  int sw = 0;
   if (pre)
     sw = sweeps[blockIdx.x];
   else if (npairs <= NT / 64)
-    sw = sweeps_lp(std::integral_constant<int, 64>());
-  else if (npairs <= NT / 32)
-    sw = sweeps_lp(std::integral_constant<int, 32>());
+    sw = v_lds ? jacobi_sweeps<64>(xl, vl, p, r, &rotated) : jacobi_sweeps<64>(xl, vg, p, r, &rotated);
   else
-    sw = sweeps_lp(std::integral_constant<int, 16>());
+    sw = v_lds ? jacobi_sweeps<32>(xl, vl, p, r, &rotated) : jacobi_sweeps<32>(xl, vg, p, r, &rotated);
   // sigma_j = |x_j| (one column per wave), from where the sweeps left X
   for (int j = wave; j < r; j += kSvdWaves) {
     double a = 0.0;
