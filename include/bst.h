@@ -229,12 +229,12 @@ typedef struct {
   double bytes;          /* algorithmic HBM bytes at float64 storage          */
   int64_t gemm_problems;
   int64_t gemm_tiles;
-  int64_t launches;      /* kernels enqueued per execute                      */
-  int32_t nsteps;        /* steps (kernel launches) of one execute            */
+  int64_t launches;      /* kernels enqueued per execute in the plan's form   */
+  int32_t nsteps;        /* steps; a form runs some, and some share a launch  */
 } bst_plan_stats;
 bst_status bst_plan_info(const bst_plan* p, bst_plan_stats* st);
 
-/* One step (one kernel launch) of a plan: its name, algorithmic flops, and
+/* One step of a plan (a kernel launch, where none is shared): its name, algorithmic flops, and
  * algorithmic HBM bytes (each operand read once, each result written once)
  * with float64 intermediates and with float32 intermediates. */
 typedef struct {

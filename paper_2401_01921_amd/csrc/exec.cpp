@@ -172,6 +172,43 @@ int planes_tile(const Step& st, bst_precision prec) {
   return st.planes_default[plane_count(prec) - 1];
 }
 
+// The MPO coefficients, if nothing else waits for a launch, run beside this step.
+static bool carries_coef(const PlanData& P, const Step& st, bst_precision prec) {
+  if (st.kind != StepKind::Gemm || (uses_planes(P, prec) && st.has_alt)) return false;
+  const bst_precision form = st.fixed_fp64 ? BST_FP64 : prec;
+  return (form == BST_FP64 || form == BST_FP32) && gemm_tile_shapes(form)[default_tile(st, form)].direct == 0 &&
+         !st.probs.empty();
+}
+
+int64_t count_launches(const PlanData& P) {
+  int64_t n = 0;
+  int lists = 0;
+  bool waiting = false;   // splits or coefficients not launched yet
+  auto flush = [&]() {
+    n += waiting ? 1 : 0;
+    waiting = false;
+    lists = 0;
+  };
+  for (const auto& st : P.steps) {
+    if (!step_runs(P, st, P.prec, false)) continue;
+    if (st.kind == StepKind::Split) {
+      if (lists == 3) flush();
+      ++lists;
+      waiting = waiting || st.n0 > 0;
+    } else if (st.kind == StepKind::HCoef) {
+      waiting = waiting || st.n0 > 0;
+    } else {
+      if (lists == 0 && carries_coef(P, st, P.prec)) waiting = false;
+      flush();
+      if (st.kind != StepKind::Gemm) n += st.n0 > 0 ? 1 : 0;
+      else if (uses_planes(P, P.prec) && st.has_alt) n += st.probs_alt.empty() ? 0 : 1;
+      else n += st.probs.empty() ? 0 : shares_some(st, st.fixed_fp64 ? BST_FP64 : P.prec) ? 2 : 1;
+    }
+  }
+  flush();
+  return n;
+}
+
 void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision prec, hipStream_t s,
                     bool skip_const, int only_step,
                     std::vector<std::pair<hipEvent_t, hipEvent_t>>* ev) {
@@ -201,13 +238,7 @@ void run_steps_impl(PlanData& P, void* ws, void* const* dptrs, bst_precision pre
     if (ev) check_hip(hipEventRecord((*ev)[k].first, s), "event");
     hipError_t e = hipSuccess;
     if (st.kind != StepKind::Split && st.kind != StepKind::HCoef) {
-      bool beside = false;   // the coefficients go with this step's launch
-      if (prep.nlists == 0 && st.kind == StepKind::Gemm && !(planes && st.has_alt)) {
-        const bst_precision form = st.fixed_fp64 ? BST_FP64 : prec;
-        const TileShape& sh = gemm_tile_shapes(form)[default_tile(st, form)];
-        beside = (form == BST_FP64 || form == BST_FP32) && sh.direct == 0 && !st.probs.empty();
-      }
-      if (!beside) check_hip(flush(), "preparation");
+      if (prep.nlists > 0 || !carries_coef(P, st, prec)) check_hip(flush(), "preparation");
     }
     switch (st.kind) {
       case StepKind::Split: {

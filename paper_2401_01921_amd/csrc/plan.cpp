@@ -2167,7 +2167,7 @@ bst_status bst_plan_info(const bst_plan* p, bst_plan_stats* st) {
       st->gemm_tiles += tile_list_length(P, s.probs, s.segs, sh.bm, sh.bn);
     }
   }
-  st->launches = (int64_t)P.steps.size();
+  st->launches = count_launches(P);
   st->nsteps = (int32_t)P.steps.size();
   BST_CATCH
 }

@@ -213,6 +213,9 @@ bool uses_planes(const PlanData& p, bst_precision prec);
 int plane_count(bst_precision prec);
 // Plane count of a tile-choice key of the padded-layout variant (10 + form).
 int plane_count_of_key(int key);
+// Kernels that one execute in the plan's form enqueues (without the pointer
+// table, which is written when the pointers change).
+int64_t count_launches(const PlanData& p);
 bool step_runs(const PlanData& p, const Step& st, bst_precision prec, bool skip_const);
 bool fused_active(const PlanData& p, bst_precision prec);
 int planes_tile(const Step& st, bst_precision prec);
