@@ -263,8 +263,7 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
     // |row|^2 and the largest element of every column
     constexpr int NC = kSvdRegRows2 / 16;   // columns of a lane, at most
     static_assert(kSvdRegCols1 <= 16 * NC && kSvdRegMaxRows <= 256, "lanes of a row");
-    for (int c = tid; c < r; c += 1024) cmax[c] = 0ull;
-    __syncthreads();
+    if (tid < r) cmax[tid] = 0ull;
     double cm[NC];
 #pragma unroll
     for (int j = 0; j < NC; ++j) cm[j] = 0.0;
@@ -282,26 +281,32 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
       a = row_sum(a);
       if (l16 == 0) nrm[q] = a;
     }
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       if (16 * j >= r) break;
-      if (l16 + 16 * j < r) atomicMax(&cmax[l16 + 16 * j], order_key(cm[j]));
+      if (l16 + 16 * j < r && tid >> 4 < p) atomicMax(&cmax[l16 + 16 * j], order_key(cm[j]));
     }
     __syncthreads();
-    // four lanes per row (column) count those before it
+    // four lanes per row and column count those before it (p >= r)
     const int q = tid >> 2;
-    const unsigned long long kc = q < r ? cmax[q] : 0ull;
     int rank = 0, rank_c = 0;
     unsigned long long top = 0ull;   // the largest element, in every lane
-    for (int i = tid & 3; i < r; i += 4) {
-      rank_c += (cmax[i] > kc || (cmax[i] == kc && i < q)) ? 1 : 0;
-      top = max(top, cmax[i]);
+    {
+      const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull, kc = q < r ? cmax[q] : 0ull;
+      for (int i = tid & 3; i < p; i += 4) {
+        const unsigned long long w = order_key(nrm[i]), wc = i < r ? cmax[i] : 0ull;
+        rank += (w > k || (w == k && i < q)) ? 1 : 0;
+        rank_c += i < r && (wc > kc || (wc == kc && i < q)) ? 1 : 0;
+        top = max(top, wc);
+      }
     }
     top = max(top, (unsigned long long)__shfl_xor(top, 1, 4));
     top = max(top, (unsigned long long)__shfl_xor(top, 2, 4));
     const double t = __longlong_as_double((long long)top);
     if (t > 0.0 && t <= DBL_MAX && (t < 0x1p-128 || t > 0x1p128)) {
       ex = ilogb(t);
+      __syncthreads();   // (every lane has read the norms)
       for (int i = tid >> 4; i < p; i += 64) {
         double a = 0.0;
         for (int c = l16; c < r; c += 16) {
@@ -312,13 +317,14 @@ __global__ __launch_bounds__(1024) void svd_panel_kernel(const SvdSec* __restric
         if (l16 == 0) nrm[i] = a;
       }
       __syncthreads();
+      rank = 0;
+      const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull;
+      for (int i = tid & 3; i < p; i += 4) {
+        const unsigned long long w = order_key(nrm[i]);
+        rank += (w > k || (w == k && i < q)) ? 1 : 0;
+      }
     }
     if (tid == 0) ctrl[kSvdCtrl * blockIdx.x + 2] = ex;
-    const unsigned long long k = q < p ? order_key(nrm[q]) : 0ull;
-    for (int i = tid & 3; i < p; i += 4) {
-      const unsigned long long w = order_key(nrm[i]);
-      rank += (w > k || (w == k && i < q)) ? 1 : 0;
-    }
     rank += __shfl_xor(rank, 1, 4);
     rank += __shfl_xor(rank, 2, 4);
     rank_c += __shfl_xor(rank_c, 1, 4);
@@ -759,6 +765,8 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
   for (; sw < kSvdMaxSweeps && r > 1; ++sw) {
     norms();
     double2* const lg = reinterpret_cast<double2*>(log + logged * stride);
+    // this lane's place in it (lanes before the stored ones all write the first one's zeros)
+    double2* lw = lg + max(lane - (64 - LL), 0);
     unsigned long long rot = 0ull;   // lanes that rotated
     for (int s0 = 0; s0 < N; s0 += 2 * U) {
       if constexpr (U == 1) {
@@ -790,7 +798,8 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
               st[0] = st[1];
             }
           }
-          if (wave == W - 1 && lane >= 64 - LL) lg[LL * (s0 + w) + lane - (64 - LL)] = c;
+          if (wave == W - 1) *lw = c;
+          lw += LL;
           lift<RW>(v[0], v[1], c);
           if (w == 1) {
             move<kWaveShr1>(v[0]);
@@ -810,7 +819,7 @@ __device__ __forceinline__ void jacobi_reg(RegShared& sh, double* X, int p, int 
             double2 c;
             rot |= __ballot(pair_params<U>(sh, wave, lb, f, N, w & 1, tol, c));
             sh.cf[wave][lb] = c;
-            if (lb >= 64 - LL) lg[LL * ((s0 + w) * U + wave) + lb - (64 - LL)] = c;
+            (lg + (int64_t)LL * ((s0 + w) * U + wave))[(uint32_t)max(lb - (64 - LL), 0)] = c;
           }
           __syncthreads();
           const int lc = fresh_lane();
