@@ -20,9 +20,9 @@
 //    independent of each other and spread over the device.
 //
 // Measured, kernels only: a two-site spin-1/2 state at chi = 256 (15 sectors
-// to 52 x 52), 1.62 ms in the one-workgroup LDS kernel before, now 36 us (1) +
-// 175 us (2) + 27 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
-// round before, now 7 x (45 + 13) us (1) + 2.24 ms (2) + 0.13 ms (3).
+// to 52 x 52), 1.62 ms in the one-workgroup LDS kernel before, now 37 us (1) +
+// 164 us (2) + 27 us (3); at chi = 1024 (to 204 x 204), 23 ms of one launch per
+// round before, now 7 x (45 + 13) us (1) + 2.28 ms (2) + 0.14 ms (3).
 //
 // The squares of a row or column have to stay inside float64's range: below it a
 // reflection is not orthogonal, and V with it (entries of 1e-160: |V V^T - 1| =
@@ -932,7 +932,8 @@ constexpr int kSvdApplyRows = 2;
 // The logged rotations on the rows of V, two rows per wave.  Bound: latency
 // of a step (two dependent products and a move), hidden by the other waves of
 // the SIMD; the log is read once per wave, from L2: with 4, 2 and 1 rows a wave
-// 160, 128 and 188 us at chi = 1024, 31, 27 and 26 us at chi = 256.
+// 160, 128 and 188 us at chi = 1024, 31, 27 and 26 us at chi = 256 (a log of 64
+// lanes per step; of those with columns 143 and 27 us, 2 rows a wave).
 __global__ __launch_bounds__(256) void svd_apply_kernel(const SvdSec* __restrict__ secs,
                                                         const int32_t* __restrict__ list, double* D,
                                                         const double* scratch, const int32_t* __restrict__ ctrl) {
